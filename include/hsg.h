@@ -287,21 +287,19 @@ hsg_status hsg_set_tuning(hsg_lattice *h, int32_t slots_per_item);
  * pair in one launch where the whole plane fits a work-group (L <= 32), else
  * as 2; 4 = as 3, and the over-relaxation pairs of a sweep two by two in one
  * launch (four half-sweeps per read and write of the spins) where eleven
- * staged planes fit the work-group's LDS; 5 = where every replica of a sample
- * of every lattice size fits one work-group's LDS (L <= 12; the paper's
- * per-block shared-memory tiles, Sec. 3.1, taken to a whole sample) and no
- * series is recorded, hsg_sweep runs whole sweeps in one launch (up to 256
- * per launch), a sample per work-group: the half-sweeps, the energies, the
- * tempering walk (Eq. (4)) and the statistics, the spins staying in LDS;
- * otherwise, and for the per-call entry points, as 4; 0 = automatic
- * (currently 4, but 3 for quantised-angle storage, whose two-pair launch is
- * slower than two fused pairs). Energies computed in a variant-5 launch equal
- * the others' to rounding (another summation order). */
+ * staged planes fit the work-group's LDS; 5 = lattice sizes whose replica fits
+ * a work-group's LDS (12 bytes per site: L <= 22 with 160 KiB; the paper's per-block shared-memory tiles, Sec. 3.1, taken to a whole
+ * replica) run all half-sweeps and the energies of a sweep in one launch of
+ * hsg_sweep, the spins staying in LDS; the other sizes, and the per-call entry
+ * points, as 4; 0 = automatic (currently 5, with 3 in place of 4 for
+ * quantised-angle storage, whose two-pair launch is slower than two fused
+ * pairs). The energies computed by 5 equal the others' to rounding (another
+ * summation order). */
 hsg_status hsg_set_kernel(hsg_lattice *h, int32_t variant);
 
 /* Tuning (results do not depend on it): 1 = where every lattice size runs
- * the z-march, has at least two samples and no replica batches, and the
- * full-lattice chain is selected, hsg_sweep runs the two halves of every
+ * the z-march (none the LDS launch of variant 5), has at least two samples and
+ * no replica batches, and the full-lattice chain is selected, hsg_sweep runs the two halves of every
  * group's samples on two streams (the caller's and one of the library's,
  * joined before it returns), each half with its own device sweep counter
  * (the second copied from the first at the start of every call); one half's

@@ -329,8 +329,9 @@ struct hsg_lattice {
     uint64_t t = 0, pt_calls = 0;
     char *state = nullptr, *coup = nullptr, *field = nullptr, *scratch = nullptr;
     int32_t slots_per_item = 0;
-    // 0 automatic (= 4), 1 gather, 2 z-march, 3 z-march with fused pairs, 4 fused pairs and
-    // over-relaxation pairs fused two by two
+    // 0 automatic (= 5, but 3 in place of 4 for quantised angles), 1 gather, 2 z-march,
+    // 3 z-march with fused pairs, 4 fused pairs and over-relaxation pairs fused two by
+    // two, 5 small lattices with the spins in LDS, the others as 4
     int32_t kernel_variant = 0;
     size_t max_lds = 64 * 1024;  // LDS bytes per work-group the device allows
     int device = 0;              // the device current at init (the buffers live there)
@@ -579,32 +580,25 @@ hsg_status run_pair_of(hsg_lattice *h, int kind, int rep, bool energy, hipStream
     return HSG_OK;
 }
 
-// One pair for every group (only == nullptr) or for group *only.
-hsg_status run_pair(hsg_lattice *h, int kind, int rep, bool energy, hipStream_t s, const Group *only = nullptr,
-                    int64_t r0 = 0, int64_t r1 = -1, bool reduce = true)
-{
-    auto pick = [only](const Group &g) { return only == nullptr || &g == only; };
-    return run_pair_of(h, kind, rep, energy, s, pick, r0, r1, reduce);
-}
-
-// Two over-relaxation pairs: one z-march where use_quad allows it, two pairs
-// elsewhere. `energy`: the last pass computes the energies.
-hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, const Group *only = nullptr, int64_t r0 = 0,
-                       int64_t r1 = -1, bool reduce = true)
+// Two over-relaxation pairs of the groups `pick` selects: one z-march where
+// use_quad allows it, two pairs elsewhere. `energy`: the last pass computes the
+// energies.
+template <class Pick>
+hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, Pick pick, int64_t r0, int64_t r1, bool reduce)
 {
     bool any_quad = false, any_other = false;
     for (const Group &g : h->lay.g) {
-        if (only != nullptr && &g != only) continue;
+        if (!pick(g)) continue;
         any_quad = any_quad || use_quad(h, g);
         any_other = any_other || !use_quad(h, g);
     }
     if (any_quad) {
-        auto quad = [h, only](const Group &g) { return (only == nullptr || &g == only) && use_quad(h, g); };
+        auto quad = [h, &pick](const Group &g) { return pick(g) && use_quad(h, g); };
         hsg_status st = run_groups(h, 1, 0, 0, energy, 2, quad, s, r0, r1, reduce);
         if (st != HSG_OK) return st;
     }
     if (any_other) {
-        auto other = [h, only](const Group &g) { return (only == nullptr || &g == only) && !use_quad(h, g); };
+        auto other = [h, &pick](const Group &g) { return pick(g) && !use_quad(h, g); };
         hsg_status st = run_pair_of(h, 1, 0, false, s, other, r0, r1, reduce);
         if (st == HSG_OK) st = run_pair_of(h, 1, 0, energy, s, other, r0, r1, reduce);
         if (st != HSG_OK) return st;
@@ -612,106 +606,139 @@ hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, const Group *
     return HSG_OK;
 }
 
-// n_or over-relaxation pairs, two by two where possible; the last pass
-// computes the energies when `energy` is set.
-hsg_status run_or_rounds(hsg_lattice *h, int n_or, bool energy, hipStream_t s, const Group *only = nullptr,
-                         int64_t r0 = 0, int64_t r1 = -1, bool reduce = true)
+// n_or over-relaxation pairs of the groups `pick` selects, two by two where
+// possible; the last pass computes the energies when `energy` is set.
+template <class Pick>
+hsg_status run_or_rounds(hsg_lattice *h, int n_or, bool energy, hipStream_t s, Pick pick, int64_t r0 = 0,
+                         int64_t r1 = -1, bool reduce = true)
 {
     bool any_quad = false;
     for (const Group &g : h->lay.g)
-        if (only == nullptr || &g == only) any_quad = any_quad || use_quad(h, g);
+        if (pick(g)) any_quad = any_quad || use_quad(h, g);
     int r = 0;
     hsg_status st = HSG_OK;
     while (r < n_or && st == HSG_OK) {
         if (any_quad && r + 1 < n_or) {
-            st = run_or_quad(h, energy && r + 2 == n_or, s, only, r0, r1, reduce);
+            st = run_or_quad(h, energy && r + 2 == n_or, s, pick, r0, r1, reduce);
             r += 2;
         } else {
-            st = run_pair(h, 1, 0, energy && r + 1 == n_or, s, only, r0, r1, reduce);
+            st = run_pair_of(h, 1, 0, energy && r + 1 == n_or, s, pick, r0, r1, reduce);
             r += 1;
         }
     }
     return st;
 }
 
+// Threads per replica of the replica launch, at most cap: whole waves for
+// ZB = ceil(L / passes) planes at a time, in as few passes as fit. 0: not even
+// one plane fits.
+int32_t replica_threads(const Group &g, int cap, int32_t *zb)
+{
+    const int pp = (g.L / 2) * (g.L / 2);
+    for (int np = 1; np <= g.L; ++np) {
+        const int z = (g.L + np - 1) / np;
+        const int t = (z * pp + 63) / 64 * 64;
+        if (t > cap) continue;
+        if (zb) *zb = z;
+        return t;
+    }
+    return 0;
+}
+
+size_t replica_lds_bytes(const Group &g) { return (size_t)g.Nh * 24; }
+
+// Whole sweeps with a replica's spins in LDS (launch_replica): lattices whose two
+// parities, decoded, fit a work-group's LDS next to its static 128 bytes (L <= 22
+// with 160 KiB). Against the z-march at L = 16, float32: 28 us per sweep instead of
+// 153 with 16 replicas, 240 us instead of 385 with 4096 (2.9 and 4.6 ps per
+// update); at L = 18, which the z-march does not take, 392 us instead of 1844.
+bool use_replica(const hsg_lattice *h, const Group &g)
+{
+    if ((h->kernel_variant != 0 && h->kernel_variant != 5) || h->chain != 0) return false;
+    return replica_lds_bytes(g) + 256 <= h->max_lds && replica_threads(g, 1024, nullptr) > 0;
+}
+
+bool any_replica(const hsg_lattice *h)
+{
+    for (const Group &g : h->lay.g)
+        if (use_replica(h, g)) return true;
+    return false;
+}
+
 // Replicas per batch of the sweep for group g (0: no batching). A batch's pairs
 // run back to back, so the batch's spins stay in the last-level cache.
 int64_t batch_of(const hsg_lattice *h, const Group &g)
 {
-    if (h->batch < 0 || !use_stream(h, g)) return 0;
+    if (h->batch < 0 || !use_stream(h, g) || use_replica(h, g)) return 0;
     const int64_t per_rep = 2 * g.Nh * (int64_t)bytes_per_spin(h->storage);
     int64_t b = h->batch > 0 ? h->batch : (int64_t)(192ll << 20) / per_rep;
     if (b < 1) b = 1;
     return b < g.n_rep ? b : 0;
 }
 
-
-// Threads and replica groups of the resident launch for group g: G replica
-// groups of Nh / 2 threads each, at most 512 threads; 0 when a sample does
-// not fit.
-unsigned resident_threads(const hsg_lattice *h, const Group &g, int32_t *groups)
+// The half-sweeps and energies of one sweep of every group use_replica selects.
+hsg_status run_replica(hsg_lattice *h, hipStream_t s)
 {
-    const int64_t Q = g.Nh / 2;
-    const int R = g.O * g.T;
-    if (Q < 1 || Q > 512) return 0;
-    if (hsg::resident_lds_bytes(h->storage, g.Nh, R) > h->max_lds) return 0;
-    const int G = (int)std::min<int64_t>(R, 512 / Q);
-    if (groups) *groups = G;
-    return (unsigned)((G * Q + 63) / 64 * 64);
-}
-
-// Whole sweeps a sample per work-group with the spins in LDS (kernel variant
-// 5), where every lattice size allows it and no per-sweep series is recorded.
-bool use_resident(const hsg_lattice *h)
-{
-    if (h->kernel_variant != 5 || h->chain != 0 || h->series != nullptr) return false;
+    std::vector<const Group *> gs;
     for (const Group &g : h->lay.g)
-        if (resident_threads(h, g, nullptr) == 0) return false;
-    return true;
-}
-
-// n sweeps of every group with the resident kernel, then the device counter.
-hsg_status run_resident(hsg_lattice *h, int32_t n, hipStream_t s)
-{
-    for (const Group &g : h->lay.g) {
-        hsg::ResidentArgs a{};
-        int32_t G = 1;
-        const unsigned threads = resident_threads(h, g, &G);
-        a.spins = h->state + g.o_spins;
-        a.J6 = reinterpret_cast<const float *>(h->coup + g.o_J6);
-        a.Hp = g.field ? reinterpret_cast<const float *>(h->field + g.o_H) : nullptr;
-        a.slot_at_temp = reinterpret_cast<int32_t *>(h->state + g.o_sat);
-        a.temp_of_slot = reinterpret_cast<int32_t *>(h->state + g.o_tos);
-        a.E = reinterpret_cast<double *>(h->state + g.o_E);
-        a.beta32 = reinterpret_cast<const float *>(h->coup + g.o_b32);
-        a.beta64 = reinterpret_cast<const double *>(h->coup + g.o_b64);
-        a.accepts = reinterpret_cast<unsigned long long *>(h->state + g.o_acc);
-        a.stat_sum = reinterpret_cast<double *>(h->state + g.o_ssum);
-        a.stat_flag = reinterpret_cast<int32_t *>(h->state + g.o_sflag);
-        a.stat_trips = reinterpret_cast<uint32_t *>(h->state + g.o_strips);
-        a.tptr = dev_counter(h);
-        a.Nh = g.Nh;
-        a.L = g.L;
-        a.Lh = g.L / 2;
-        a.D = g.D;
-        a.O = g.O;
-        a.T = g.T;
-        a.slots_per_sample = g.O * g.T;
-        a.groups = G;
-        a.n_sweeps = n;
-        a.n_hb = h->n_hb;
-        a.n_or = h->n_or;
-        a.pt_every = h->pt_every;
-        a.stats = h->stats ? 1 : 0;
-        a.key0 = (uint32_t)(h->seed & 0xFFFFFFFFu);
-        a.key1 = (uint32_t)(h->seed >> 32);
-        a.uid_base = g.uid_base;
-        const size_t lds = hsg::resident_lds_bytes(h->storage, g.Nh, g.O * g.T);
-        const hipError_t e = hsg::launch_resident(a, h->storage, g.field, h->hw_math, threads, lds, s);
-        if (e != hipSuccess) return hip_fail(e, "resident sweep launch");
+        if (use_replica(h, g)) gs.push_back(&g);
+    for (size_t k0 = 0; k0 < gs.size(); k0 += hsg::kMaxStreamGroups) {
+        const size_t k1 = std::min(gs.size(), k0 + hsg::kMaxStreamGroups);
+        size_t lds = 0;
+        int64_t reps = 0;
+        for (size_t k = k0; k < k1; ++k) {
+            lds = std::max(lds, replica_lds_bytes(*gs[k]));
+            reps += gs[k]->n_rep;
+        }
+        // The kernel's registers allow 1024 threads per CU: they are shared by the
+        // replicas that a CU gets (256 CUs) and can hold, not below 256 each. With
+        // 4096 replicas of L = 16 (three fit a CU), 1024 threads each take 342 us
+        // per sweep, 512 247 us, 256 240 us and 128 368 us; with 16 replicas 28 us
+        // (1024) against 36 us (256).
+        const int64_t share =
+            std::min<int64_t>((int64_t)(h->max_lds / (lds + 256)), std::max<int64_t>(1, (reps + 255) / 256));
+        const int cap = share <= 1 ? 1024 : share == 2 ? 512 : 256;
+        int32_t threads = 0;
+        for (size_t k = k0; k < k1; ++k) threads = std::max(threads, replica_threads(*gs[k], cap, nullptr));
+        hsg::MultiReplicaArgs m{};
+        int64_t blocks = 0;
+        for (size_t k = k0; k < k1; ++k) {
+            const Group &g = *gs[k];
+            hsg::ReplicaArgs a{};
+            a.spins = h->state + g.o_spins;
+            a.J6 = reinterpret_cast<const float *>(h->coup + g.o_J6);
+            a.Jbits = g.ckind == 1 ? reinterpret_cast<const uint8_t *>(h->coup + g.o_Jbits) : nullptr;
+            a.Hp = g.field ? reinterpret_cast<const float *>(h->field + g.o_H) : nullptr;
+            a.temp_of_slot = reinterpret_cast<const int32_t *>(h->state + g.o_tos);
+            a.beta32 = reinterpret_cast<const float *>(h->coup + g.o_b32);
+            a.E = reinterpret_cast<double *>(h->state + g.o_E);
+            a.tptr = dev_counter(h);
+            a.Nh = g.Nh;
+            a.n_rep = g.n_rep;
+            a.L = g.L;
+            a.Lh = g.L / 2;
+            a.pp = (g.L / 2) * (g.L / 2);
+            a.tpr = replica_threads(g, cap, &a.ZB);
+            a.RB = (int32_t)std::min<size_t>((size_t)(threads / a.tpr), lds / replica_lds_bytes(g));
+            a.slots_per_sample = g.O * g.T;
+            a.T = g.T;
+            a.n_hb = h->n_hb;
+            a.n_or = h->n_or;
+            a.key0 = (uint32_t)(h->seed & 0xFFFFFFFFu);
+            a.key1 = (uint32_t)(h->seed >> 32);
+            a.uid_base = g.uid_base;
+            const int64_t nb = (g.n_rep + a.RB - 1) / a.RB;
+            if (blocks + nb > 0x7FFFFFFFll) return fail(HSG_E_SIZE, "grid too large");
+            a.n_blocks = (int32_t)nb;
+            m.block_start[m.n_groups] = (int32_t)blocks;
+            m.g[m.n_groups++] = a;
+            blocks += nb;
+        }
+        m.block_start[m.n_groups] = (int32_t)blocks;
+        m.n_blocks = (int32_t)blocks;
+        const hipError_t e = hsg::launch_replica(m, h->storage, h->hw_math, (unsigned)threads, lds, s);
+        if (e != hipSuccess) return hip_fail(e, "replica sweep launch");
     }
-    const hipError_t e = hsg::launch_set_u32(dev_counter(h), (uint32_t)(h->t + (uint64_t)n), s);
-    if (e != hipSuccess) return hip_fail(e, "counter launch");
     return HSG_OK;
 }
 
@@ -931,12 +958,16 @@ hsg_status enqueue_sweep(hsg_lattice *h, bool pt, hipStream_t s)
     const int last_kind = h->n_or > 0 ? 1 : 0;
     bool batched = false;
     for (const Group &g : h->lay.g) batched = batched || batch_of(h, g) > 0;
+    if (any_replica(h)) {
+        hsg_status st = run_replica(h, s);
+        if (st != HSG_OK) return st;
+    }
     if (!batched) {
-        for (int r = 0; r < h->n_hb; ++r) {
-            hsg_status st = run_pair(h, 0, r, last_kind == 0 && r == h->n_hb - 1, s);
-            if (st != HSG_OK) return st;
-        }
-        hsg_status st = run_or_rounds(h, h->n_or, true, s);
+        hsg_status st = HSG_OK;
+        auto rest = [h](const Group &g) { return !use_replica(h, g); };
+        for (int r = 0; r < h->n_hb && st == HSG_OK; ++r)
+            st = run_pair_of(h, 0, r, last_kind == 0 && r == h->n_hb - 1, s, rest, 0, -1, true);
+        if (st == HSG_OK) st = run_or_rounds(h, h->n_or, true, s, rest);
         if (st != HSG_OK) return st;
     } else {
         // Replicas never interact within the pairs of a sweep: all pairs of one
@@ -944,15 +975,18 @@ hsg_status enqueue_sweep(hsg_lattice *h, bool pt, hipStream_t s)
         // cache), then the next batch; the same updates in the same order per
         // replica, so the same bits.
         for (const Group &g : h->lay.g) {
+            if (use_replica(h, g)) continue;
             const int64_t b = batch_of(h, g);
             const int64_t step = b > 0 ? b : g.n_rep;
+            auto only = [&g](const Group &x) { return &x == &g; };
             for (int64_t r0 = 0; r0 < g.n_rep; r0 += step) {
                 const int64_t r1 = std::min<int64_t>(g.n_rep, r0 + step);
                 for (int r = 0; r < h->n_hb; ++r) {
-                    hsg_status st = run_pair(h, 0, r, last_kind == 0 && r == h->n_hb - 1, s, &g, r0, r1, b == 0);
+                    hsg_status st =
+                        run_pair_of(h, 0, r, last_kind == 0 && r == h->n_hb - 1, s, only, r0, r1, b == 0);
                     if (st != HSG_OK) return st;
                 }
-                hsg_status st = run_or_rounds(h, h->n_or, true, s, &g, r0, r1, b == 0);
+                hsg_status st = run_or_rounds(h, h->n_or, true, s, only, r0, r1, b == 0);
                 if (st != HSG_OK) return st;
             }
             if (b > 0) {  // one reduction over every batch's partial sums
@@ -1157,7 +1191,7 @@ hsg_status hsg_init_lattice(const hsg_desc *desc, const float *d_spins0, const f
 // the same counters as in one stream, so the results are the same bits.
 bool overlap_ok(const hsg_lattice *h)
 {
-    if (!h->overlap || h->chain != 0 || h->series != nullptr || use_resident(h)) return false;
+    if (!h->overlap || h->chain != 0 || h->series != nullptr || any_replica(h)) return false;
     for (const Group &g : h->lay.g) {
         if (!use_stream(h, g) || g.D < 2 || batch_of(h, g) > 0) return false;
     }
@@ -1184,8 +1218,9 @@ hsg_status enqueue_half_sweep(hsg_lattice *h, int c, bool pt, hipStream_t s, hip
     for (const Group &g : h->lay.g) {
         int64_t d0, d1, r0, r1;
         half_range(g, c, d0, d1, r0, r1);
+        auto only = [&g](const Group &x) { return &x == &g; };
         for (int r = 0; r < h->n_hb && st == HSG_OK; ++r)
-            st = run_pair(h, 0, r, last_kind == 0 && r == h->n_hb - 1, s, &g, r0, r1, false);
+            st = run_pair_of(h, 0, r, last_kind == 0 && r == h->n_hb - 1, s, only, r0, r1, false);
     }
     hipError_t e = st == HSG_OK ? hipEventRecord(hb_done, s) : hipSuccess;
     if (e != hipSuccess) st = hip_fail(e, "event record");
@@ -1193,7 +1228,8 @@ hsg_status enqueue_half_sweep(hsg_lattice *h, int c, bool pt, hipStream_t s, hip
         if (st != HSG_OK) break;
         int64_t d0, d1, r0, r1;
         half_range(g, c, d0, d1, r0, r1);
-        st = run_or_rounds(h, h->n_or, true, s, &g, r0, r1, false);
+        auto only = [&g](const Group &x) { return &x == &g; };
+        st = run_or_rounds(h, h->n_or, true, s, only, r0, r1, false);
         if (st != HSG_OK) break;
         const int n_pb = use_pair(h, g) ? 1 : g.s_ytiles * g.s_zslabs;
         e = hsg::launch_reduce_partials(reinterpret_cast<double *>(h->scratch + g.o_scr) + r0 * n_pb, n_pb,
@@ -1297,16 +1333,7 @@ hsg_status hsg_sweep(hsg_lattice *h, int32_t n_sweeps, hsg_stream_t stream)
     hipStream_t s = S(stream);
     const bool graphs = h->use_graphs && h->pt_every <= 1;
     int done = 0;
-    if (n_sweeps > 0 && use_resident(h)) {
-        constexpr int kMaxPerLaunch = 256;  // bounded launches for long runs
-        while (done < n_sweeps) {
-            const int n = std::min(kMaxPerLaunch, n_sweeps - done);
-            hsg_status st = run_resident(h, n, s);
-            if (st != HSG_OK) return st;
-            done += n;
-            h->t += (uint64_t)n;
-        }
-    } else if (n_sweeps > 0 && overlap_ok(h)) {
+    if (n_sweeps > 0 && overlap_ok(h)) {
         hsg_status st = overlapped_sweeps(h, n_sweeps, s);
         if (st != HSG_OK) return st;
         done = n_sweeps;
@@ -1350,14 +1377,14 @@ hsg_status hsg_pair_sweep(hsg_lattice *h, int32_t kind, int32_t rep, hsg_stream_
     if (h == nullptr) return fail(HSG_E_INVALID, "handle is NULL");
     if (kind != 0 && kind != 1) return fail(HSG_E_INVALID, "kind = %d, need 0 (HB) or 1 (OR)", kind);
     if (rep < 0 || rep > 15) return fail(HSG_E_SIZE, "rep = %d, need 0..15", rep);
-    return run_pair(h, kind, rep, false, S(stream));
+    return run_pair_of(h, kind, rep, false, S(stream), [](const Group &) { return true; }, 0, -1, true);
 }
 
 hsg_status hsg_or_pairs(hsg_lattice *h, int32_t n_pairs, hsg_stream_t stream)
 {
     if (h == nullptr) return fail(HSG_E_INVALID, "handle is NULL");
     if (n_pairs < 1 || n_pairs > 1000) return fail(HSG_E_INVALID, "n_pairs = %d, need 1..1000", n_pairs);
-    return run_or_rounds(h, n_pairs, false, S(stream));
+    return run_or_rounds(h, n_pairs, false, S(stream), [](const Group &) { return true; });
 }
 
 hsg_status hsg_pt_exchange(hsg_lattice *h, hsg_stream_t stream)
@@ -1780,9 +1807,9 @@ hsg_status hsg_autotune(hsg_lattice *h, int32_t n_sweeps, void *d_backup, int32_
     {
         const int32_t v0 = h->kernel_variant;
         h->kernel_variant = 5;
-        const bool resident = use_resident(h);
+        const bool replica = any_replica(h);
         h->kernel_variant = v0;
-        if (resident) cands.push_back({5, 0, false});
+        if (replica) cands.push_back({5, 0, false});
     }
     if (any_pair) {
         const int32_t v0 = h->kernel_variant;

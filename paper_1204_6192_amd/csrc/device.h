@@ -322,12 +322,12 @@ __device__ __forceinline__ v3 heat_bath(v3 h, float beta, uint32_t w0, uint32_t 
 // leaves s unchanged. The spin must be a unit vector to float32 precision (the
 // reflection keeps |s|). RENORM = false (compressed storage, which renormalises
 // on load) skips the final renormalisation, as in heat_bath.
-template <bool RENORM = true>
-__device__ __forceinline__ v3 over_relax(v3 s, v3 h)
+//
+// The pair form computes both reflections before it looks at the rare zero
+// fields, so that the two chains of dependent operations run side by side.
+template <bool RENORM>
+__device__ __forceinline__ v3 reflect(v3 s, v3 h, float hh)
 {
-    const float hh = dot3(h, h);
-    // A field with |h|^2 below 1e-30 counts as zero (its direction is noise).
-    if (!(hh >= 1e-30f)) return s;
     // 2 (s.h) / (h.h) from the hardware reciprocal refined by one Newton step:
     // within about an ulp (the result is renormalised below in any case).
     float rh = __builtin_amdgcn_rcpf(hh);
@@ -335,6 +335,27 @@ __device__ __forceinline__ v3 over_relax(v3 s, v3 h)
     const float f = 2.0f * dot3(s, h) * rh;
     v3 r{fmaf(f, h.x, -s.x), fmaf(f, h.y, -s.y), fmaf(f, h.z, -s.z)};
     return RENORM ? renorm_unit(r) : r;
+}
+
+// A field with |h|^2 below 1e-30 counts as zero (its direction is noise).
+template <bool RENORM = true>
+__device__ __forceinline__ v3 over_relax(v3 s, v3 h)
+{
+    const float hh = dot3(h, h);
+    if (!(hh >= 1e-30f)) return s;
+    return reflect<RENORM>(s, h, hh);
+}
+
+template <bool RENORM>
+__device__ __forceinline__ void over_relax_pair(v3 s0, v3 h0, v3 s1, v3 h1, v3 &r0, v3 &r1)
+{
+    const float hh0 = dot3(h0, h0), hh1 = dot3(h1, h1);
+    r0 = reflect<RENORM>(s0, h0, hh0);
+    r1 = reflect<RENORM>(s1, h1, hh1);
+    if (__builtin_expect(!(hh0 >= 1e-30f && hh1 >= 1e-30f), 0)) {
+        if (!(hh0 >= 1e-30f)) r0 = s0;
+        if (!(hh1 >= 1e-30f)) r1 = s1;
+    }
 }
 
 // ---------------------------------------------------------------- storage

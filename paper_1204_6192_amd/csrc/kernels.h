@@ -54,7 +54,6 @@ struct StreamArgs {
     int32_t n_zslabs, zlen;
     int32_t slots_per_sample, T;
     const uint32_t *tptr;  // device sweep counter
-    uint32_t t_offset;     // added to it (sweeps of a persistent launch; 0 otherwise)
     uint32_t rep, parity;
     uint32_t key0, key1, uid_base;
 };
@@ -98,6 +97,33 @@ struct MultiStreamArgs {
 hipError_t launch_half_sweep_stream(const MultiStreamArgs &m, int storage, int kind, bool energy, int fuse,
                                     unsigned threads, size_t lds_bytes, hipStream_t s);
 
+// One sweep of small lattices with the spins in LDS (replica.hip): a replica per
+// tpr threads (whole waves), ZB planes of pp = (L/2)^2 site pairs per parity at a
+// time, RB replicas per work-group; n_hb heat-bath pairs, then n_or
+// over-relaxation pairs, then the energies into E. Launch with at least
+// RB * tpr threads and RB * 24 Nh bytes of LDS.
+struct ReplicaArgs {
+    void *spins;
+    const float *J6;
+    const uint8_t *Jbits;
+    const float *Hp;
+    const int32_t *temp_of_slot;
+    const float *beta32;
+    double *E;             // [replica]
+    const uint32_t *tptr;  // device sweep counter
+    int64_t Nh, n_rep;
+    int32_t L, Lh, pp, ZB, tpr, RB, n_blocks;
+    int32_t slots_per_sample, T, n_hb, n_or;
+    uint32_t key0, key1, uid_base;
+};
+struct MultiReplicaArgs {
+    int32_t n_groups, n_blocks;
+    int32_t block_start[kMaxStreamGroups + 1];
+    ReplicaArgs g[kMaxStreamGroups];
+};
+hipError_t launch_replica(const MultiReplicaArgs &m, int storage, bool hw, unsigned threads, size_t lds,
+                          hipStream_t s);
+
 // *flag = 1 if any of the n values is not exactly +1 or -1, else 0.
 hipError_t launch_check_pm1(const float *v, int64_t n, int32_t *flag, hipStream_t s);
 
@@ -132,35 +158,6 @@ struct StatsArgs {
 };
 hipError_t launch_stats(const StatsArgs &a, bool clear, hipStream_t s);
 
-
-// Whole sweeps of small lattices, a sample per work-group with its spins in LDS
-// (resident.hip): n_sweeps sweeps of the D samples of one group, each with
-// n_hb heat-bath pairs, n_or over-relaxation pairs, the energy of the last
-// pass, tempering when (t + 1) % pt_every == 0 and (stats) the run statistics;
-// t = *tptr + i for sweep i. The caller advances the device counter. `groups`
-// replica groups of Nh / 2 threads each; launch with groups * Nh / 2 <= threads.
-struct ResidentArgs {
-    void *spins;
-    const float *J6;
-    const float *Hp;
-    int32_t *slot_at_temp, *temp_of_slot;  // [D][O][T]
-    double *E;                             // [D][O][T] by slot
-    const float *beta32;
-    const double *beta64;
-    unsigned long long *accepts;           // [D][O][T-1]
-    double *stat_sum;                      // [D][O][T][2]
-    int32_t *stat_flag;
-    uint32_t *stat_trips;
-    const uint32_t *tptr;
-    int64_t Nh;
-    int32_t L, Lh, D, O, T, slots_per_sample, groups;
-    int32_t n_sweeps, n_hb, n_or, pt_every, stats;
-    uint32_t key0, key1, uid_base;
-};
-// LDS bytes a work-group of the resident kernel needs.
-size_t resident_lds_bytes(int storage, int64_t Nh, int32_t slots_per_sample);
-hipError_t launch_resident(const ResidentArgs &a, int storage, bool field, bool hw, unsigned threads, size_t lds,
-                           hipStream_t s);
 
 struct PackArgs {
     void *spins_int;

@@ -1,6 +1,5 @@
-// ladder.h -- per-ladder steps after the updates of a sweep, shared by the
-// separate kernels and the persistent launch: the tempering walk of Eq. (4)
-// and the run statistics.
+// ladder.h -- per-ladder steps after the updates of a sweep: the tempering walk of
+// Eq. (4) and the run statistics.
 #pragma once
 #include "device.h"
 #include "kernels.h"

@@ -84,7 +84,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int lb, f
     for (int n = 0; n < 6; ++n) Jp[n] = Jb + n * (int64_t)Nh;
     float beta = 0.0f;
     uint32_t c2 = 0, uid = 0;
-    const uint32_t tsweep = *a.tptr + a.t_offset;
+    const uint32_t tsweep = *a.tptr;
     if (active) {
         beta = a.beta32[a.temp_of_slot[r]];
         const int o = sis / a.T, ts = sis - o * a.T;
@@ -370,7 +370,7 @@ __device__ __forceinline__ void pair_body(const StreamArgs &a, const int lb, flo
     }
     float beta = 0.0f;
     uint32_t c2A = 0, c2B = 0, uid = 0;
-    const uint32_t tsweep = *a.tptr + a.t_offset;
+    const uint32_t tsweep = *a.tptr;
     if (active) {
         beta = a.beta32[a.temp_of_slot[r]];
         const int o = sis / a.T, ts = sis - o * a.T;
