@@ -417,8 +417,9 @@ hsg_status hsg_get_stats(const hsg_lattice *h, double *d_sums, uint32_t *d_trips
  * (about 192 MiB of spins per batch); > 0: replicas per batch. */
 hsg_status hsg_set_batch(hsg_lattice *h, int64_t replicas);
 
-/* Replay whole sweeps as captured HIP graphs (default on; used when tempering
- * runs every sweep or never). Results do not depend on it. */
+/* Replay eight sweeps at a time as a captured HIP graph (default on; used when
+ * tempering runs every sweep or never; fewer sweeps, and what is left of a call,
+ * are launched one by one). Results do not depend on it. */
 hsg_status hsg_set_graphs(hsg_lattice *h, int32_t enable);
 
 /* Wait for `stream` and report any device error. */

@@ -356,8 +356,8 @@ struct hsg_lattice {
     hipStream_t stream2 = nullptr;
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};  // fork, half 0 HB, half 1 HB, join
     hipStream_t capture_stream = nullptr;
-    hipGraph_t graph[2] = {nullptr, nullptr};         // 1 sweep, kGraphSweeps sweeps
-    hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
+    hipGraph_t graph = nullptr;  // kGraphSweeps sweeps
+    hipGraphExec_t graph_exec = nullptr;
 };
 
 namespace {
@@ -370,12 +370,10 @@ uint32_t *dev_counter(const hsg_lattice *h) { return reinterpret_cast<uint32_t *
 
 void drop_graphs(hsg_lattice *h)
 {
-    for (int k = 0; k < 2; ++k) {
-        if (h->graph_exec[k]) (void)hipGraphExecDestroy(h->graph_exec[k]);
-        if (h->graph[k]) (void)hipGraphDestroy(h->graph[k]);
-        h->graph_exec[k] = nullptr;
-        h->graph[k] = nullptr;
-    }
+    if (h->graph_exec) (void)hipGraphExecDestroy(h->graph_exec);
+    if (h->graph) (void)hipGraphDestroy(h->graph);
+    h->graph_exec = nullptr;
+    h->graph = nullptr;
 }
 
 int chunk_for(const hsg_lattice *h, const Group &g)
@@ -486,11 +484,10 @@ hsg::StreamArgs stream_args(const hsg_lattice *h, const Group &g, int parity, ui
 // `pick` selects, over replicas [r0, r1) of each (r1 < 0: all). The z-march
 // groups go into as few launches as possible (up to kMaxStreamGroups per
 // launch); the others use the gather kernel one group at a time. With energy,
-// the partial sums are reduced into E unless reduce is false (the caller
-// reduces once every replica range is done).
+// the partial sums are left in the scratch buffer (run_sweep_end reduces them).
 template <class Pick>
 hsg_status run_groups(hsg_lattice *h, int kind, int parity, int rep, bool energy, int fuse, Pick pick,
-                      hipStream_t s, int64_t r0 = 0, int64_t r1 = -1, bool reduce = true)
+                      hipStream_t s, int64_t r0 = 0, int64_t r1 = -1)
 {
     if (kind == 0 && h->hw_math) kind = 2;
     hsg::MultiStreamArgs m{};
@@ -534,18 +531,7 @@ hsg_status run_groups(hsg_lattice *h, int kind, int parity, int rep, bool energy
             if (e != hipSuccess) return hip_fail(e, "half-sweep launch");
         }
     }
-    hsg_status st = flush();
-    if (st != HSG_OK) return st;
-    if (energy && reduce) {
-        for (const Group &g : h->lay.g) {
-            if (!pick(g)) continue;
-            const int n_pb = fuse ? 1 : use_stream(h, g) ? g.s_ytiles * g.s_zslabs : g.n_pb_sweep;
-            const hipError_t e = hsg::launch_reduce_partials(reinterpret_cast<double *>(h->scratch + g.o_scr), n_pb,
-                                                             g.n_rep, reinterpret_cast<double *>(h->state + g.o_E), s);
-            if (e != hipSuccess) return hip_fail(e, "energy reduction launch");
-        }
-    }
-    return HSG_OK;
+    return flush();
 }
 
 hsg_status run_half_sweep(hsg_lattice *h, int kind, int parity, int rep, bool energy, hipStream_t s)
@@ -558,7 +544,7 @@ hsg_status run_half_sweep(hsg_lattice *h, int kind, int parity, int rep, bool en
 // otherwise. `energy`: the parity-1 pass computes the energies.
 template <class Pick>
 hsg_status run_pair_of(hsg_lattice *h, int kind, int rep, bool energy, hipStream_t s, Pick pick, int64_t r0,
-                       int64_t r1, bool reduce)
+                       int64_t r1)
 {
     bool any_pair = false, any_single = false;
     for (const Group &g : h->lay.g) {
@@ -568,13 +554,13 @@ hsg_status run_pair_of(hsg_lattice *h, int kind, int rep, bool energy, hipStream
     }
     if (any_pair) {
         auto fused = [h, &pick](const Group &g) { return pick(g) && use_pair(h, g); };
-        hsg_status st = run_groups(h, kind, 0, rep, energy, 1, fused, s, r0, r1, reduce);
+        hsg_status st = run_groups(h, kind, 0, rep, energy, 1, fused, s, r0, r1);
         if (st != HSG_OK) return st;
     }
     if (any_single) {
         auto single = [h, &pick](const Group &g) { return pick(g) && !use_pair(h, g); };
-        hsg_status st = run_groups(h, kind, 0, rep, false, 0, single, s, r0, r1, reduce);
-        if (st == HSG_OK) st = run_groups(h, kind, 1, rep, energy, 0, single, s, r0, r1, reduce);
+        hsg_status st = run_groups(h, kind, 0, rep, false, 0, single, s, r0, r1);
+        if (st == HSG_OK) st = run_groups(h, kind, 1, rep, energy, 0, single, s, r0, r1);
         if (st != HSG_OK) return st;
     }
     return HSG_OK;
@@ -584,7 +570,7 @@ hsg_status run_pair_of(hsg_lattice *h, int kind, int rep, bool energy, hipStream
 // use_quad allows it, two pairs elsewhere. `energy`: the last pass computes the
 // energies.
 template <class Pick>
-hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, Pick pick, int64_t r0, int64_t r1, bool reduce)
+hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, Pick pick, int64_t r0, int64_t r1)
 {
     bool any_quad = false, any_other = false;
     for (const Group &g : h->lay.g) {
@@ -594,13 +580,13 @@ hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, Pick pick, in
     }
     if (any_quad) {
         auto quad = [h, &pick](const Group &g) { return pick(g) && use_quad(h, g); };
-        hsg_status st = run_groups(h, 1, 0, 0, energy, 2, quad, s, r0, r1, reduce);
+        hsg_status st = run_groups(h, 1, 0, 0, energy, 2, quad, s, r0, r1);
         if (st != HSG_OK) return st;
     }
     if (any_other) {
         auto other = [h, &pick](const Group &g) { return pick(g) && !use_quad(h, g); };
-        hsg_status st = run_pair_of(h, 1, 0, false, s, other, r0, r1, reduce);
-        if (st == HSG_OK) st = run_pair_of(h, 1, 0, energy, s, other, r0, r1, reduce);
+        hsg_status st = run_pair_of(h, 1, 0, false, s, other, r0, r1);
+        if (st == HSG_OK) st = run_pair_of(h, 1, 0, energy, s, other, r0, r1);
         if (st != HSG_OK) return st;
     }
     return HSG_OK;
@@ -610,7 +596,7 @@ hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, Pick pick, in
 // possible; the last pass computes the energies when `energy` is set.
 template <class Pick>
 hsg_status run_or_rounds(hsg_lattice *h, int n_or, bool energy, hipStream_t s, Pick pick, int64_t r0 = 0,
-                         int64_t r1 = -1, bool reduce = true)
+                         int64_t r1 = -1)
 {
     bool any_quad = false;
     for (const Group &g : h->lay.g)
@@ -619,10 +605,10 @@ hsg_status run_or_rounds(hsg_lattice *h, int n_or, bool energy, hipStream_t s, P
     hsg_status st = HSG_OK;
     while (r < n_or && st == HSG_OK) {
         if (any_quad && r + 1 < n_or) {
-            st = run_or_quad(h, energy && r + 2 == n_or, s, pick, r0, r1, reduce);
+            st = run_or_quad(h, energy && r + 2 == n_or, s, pick, r0, r1);
             r += 2;
         } else {
-            st = run_pair_of(h, 1, 0, energy && r + 1 == n_or, s, pick, r0, r1, reduce);
+            st = run_pair_of(h, 1, 0, energy && r + 1 == n_or, s, pick, r0, r1);
             r += 1;
         }
     }
@@ -742,29 +728,81 @@ hsg_status run_replica(hsg_lattice *h, hipStream_t s)
     return HSG_OK;
 }
 
-// purpose 1: in-sweep pass, counter read from the device; 2: standalone pass.
-hsg_status run_pt(hsg_lattice *h, uint32_t ctr1, uint32_t purpose, hipStream_t s)
+// Energy partial sums per replica that the last half-sweep of a sweep leaves for
+// group g: 0 where the energies themselves are written.
+int energy_pb(const hsg_lattice *h, const Group &g)
 {
-    for (const Group &g : h->lay.g) {
-        hsg::PtArgs a{};
-        a.slot_at_temp = reinterpret_cast<int32_t *>(h->state + g.o_sat);
-        a.temp_of_slot = reinterpret_cast<int32_t *>(h->state + g.o_tos);
-        a.E = reinterpret_cast<const double *>(h->state + g.o_E);
+    if (h->chain == 1 || use_replica(h, g)) return 0;
+    return use_pair(h, g) ? 1 : use_stream(h, g) ? g.s_ytiles * g.s_zslabs : g.n_pb_sweep;
+}
+
+// Samples [d0, d1) of half c of group g (c < 0: all).
+void sample_range(const Group &g, int c, int64_t &d0, int64_t &d1)
+{
+    const int64_t half = g.D / 2;
+    d0 = c == 1 ? half : 0;
+    d1 = c == 0 ? half : g.D;
+}
+
+// After the updates of a sweep (purpose 1: counter read from the device), or a
+// standalone tempering pass (purpose 2, counter ctr1): reduces the energy partials
+// when `reduce`, tempers when `pt`, accumulates the statistics when `stats` and
+// steps the sweep counter when `advance`, for the samples of half c. One launch for
+// up to kMaxStreamGroups lattice sizes; the last one steps the counter.
+hsg_status run_sweep_end(hsg_lattice *h, bool reduce, bool pt, bool stats, bool advance, uint32_t ctr1,
+                         uint32_t purpose, int c, hipStream_t s)
+{
+    hsg::MultiLadderArgs m{};
+    m.tptr = purpose == 1 ? dev_counter(h) : nullptr;
+    m.ctr1 = ctr1;
+    m.purpose = purpose;
+    m.pt = pt ? 1u : 0u;
+    m.stats = stats ? 1u : 0u;
+    m.key0 = (uint32_t)(h->seed & 0xFFFFFFFFu);
+    m.key1 = (uint32_t)(h->seed >> 32);
+    int64_t blocks = 0;
+    auto flush = [&](bool last) -> hsg_status {
+        if (m.n_groups == 0) return HSG_OK;
+        m.block_start[m.n_groups] = (int32_t)blocks;
+        m.n_blocks = (int32_t)blocks;
+        m.advance = last && advance ? dev_counter(h) : nullptr;
+        m.ticket = dev_counter(h) + 2;
+        const hipError_t e = hsg::launch_sweep_end(m, s);
+        m.n_groups = 0;
+        blocks = 0;
+        if (e != hipSuccess) return hip_fail(e, "end of sweep launch");
+        return HSG_OK;
+    };
+    for (size_t gi = 0; gi < h->lay.g.size(); ++gi) {
+        const Group &g = h->lay.g[gi];
+        int64_t d0, d1;
+        sample_range(g, c, d0, d1);
+        const int64_t OT = (int64_t)g.O * g.T;
+        hsg::LadderArgs a{};
+        a.n_pb = reduce ? energy_pb(h, g) : 0;
+        a.slot_at_temp = reinterpret_cast<int32_t *>(h->state + g.o_sat) + d0 * OT;
+        a.temp_of_slot = reinterpret_cast<int32_t *>(h->state + g.o_tos) + d0 * OT;
+        a.E = reinterpret_cast<double *>(h->state + g.o_E) + d0 * OT;
+        a.partials = reinterpret_cast<const double *>(h->scratch + g.o_scr) + d0 * OT * a.n_pb;
         a.beta64 = reinterpret_cast<const double *>(h->coup + g.o_b64);
-        a.accepts = reinterpret_cast<unsigned long long *>(h->state + g.o_acc);
-        a.D = g.D;
+        a.accepts = reinterpret_cast<unsigned long long *>(h->state + g.o_acc) + d0 * g.O * (g.T - 1);
+        a.stat_sum = reinterpret_cast<double *>(h->state + g.o_ssum) + d0 * OT * 2;
+        a.stat_flag = reinterpret_cast<int32_t *>(h->state + g.o_sflag) + d0 * OT;
+        a.stat_trips = reinterpret_cast<uint32_t *>(h->state + g.o_strips) + d0 * OT;
         a.O = g.O;
         a.T = g.T;
-        a.tptr = purpose == 1 ? dev_counter(h) : nullptr;
-        a.ctr1 = ctr1;
-        a.purpose = purpose;
-        a.key0 = (uint32_t)(h->seed & 0xFFFFFFFFu);
-        a.key1 = (uint32_t)(h->seed >> 32);
-        a.uid_base = g.uid_base;
-        const hipError_t e = hsg::launch_pt(a, s);
-        if (e != hipSuccess) return hip_fail(e, "tempering launch");
+        a.uid_base = g.uid_base + (uint32_t)d0;
+        const int64_t nb = (d1 - d0) * g.O;
+        if (nb == 0) continue;
+        if (m.n_groups == hsg::kMaxStreamGroups || blocks + nb > 0x7FFFFFFFll) {
+            const hsg_status st = flush(false);
+            if (st != HSG_OK) return st;
+        }
+        m.block_start[m.n_groups] = (int32_t)blocks;
+        m.g[m.n_groups++] = a;
+        blocks += nb;
     }
-    return HSG_OK;
+    return flush(true);
 }
 
 hsg::PackArgs pack_args(const hsg_lattice *h, const Group &g)
@@ -781,29 +819,12 @@ hsg::PackArgs pack_args(const hsg_lattice *h, const Group &g)
 
 bool aligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & (kAlign - 1)) == 0; }
 
-// All launches of one sweep, kernels only (capturable): heat-bath pairs,
-// over-relaxation pairs with the energy fused into the last pass, tempering,
-// then the device sweep counter advances.
-hsg::StatsArgs stats_args(const hsg_lattice *h, const Group &g)
+hsg_status clear_stats(hsg_lattice *h, const Group &g, hipStream_t s)
 {
-    hsg::StatsArgs a{};
-    a.slot_at_temp = reinterpret_cast<const int32_t *>(h->state + g.o_sat);
-    a.E = reinterpret_cast<const double *>(h->state + g.o_E);
-    a.sum = reinterpret_cast<double *>(h->state + g.o_ssum);
-    a.flag = reinterpret_cast<int32_t *>(h->state + g.o_sflag);
-    a.trips = reinterpret_cast<uint32_t *>(h->state + g.o_strips);
-    a.D = g.D;
-    a.O = g.O;
-    a.T = g.T;
-    return a;
-}
-
-hsg_status run_stats(hsg_lattice *h, bool clear, hipStream_t s)
-{
-    for (const Group &g : h->lay.g) {
-        const hipError_t e = hsg::launch_stats(stats_args(h, g), clear, s);
-        if (e != hipSuccess) return hip_fail(e, "statistics launch");
-    }
+    const hipError_t e = hsg::launch_stats_clear(reinterpret_cast<double *>(h->state + g.o_ssum),
+                                                 reinterpret_cast<int32_t *>(h->state + g.o_sflag),
+                                                 reinterpret_cast<uint32_t *>(h->state + g.o_strips), g.n_rep, s);
+    if (e != hipSuccess) return hip_fail(e, "statistics launch");
     return HSG_OK;
 }
 
@@ -943,17 +964,27 @@ hsg_status run_tile_sweep(hsg_lattice *h, hipStream_t s)
     return run_energy(h, s);
 }
 
+// The rest of a sweep after its updates: energies, tempering, statistics, the
+// series' record (which reads the counter), and the step of the counter.
+hsg_status finish_sweep(hsg_lattice *h, bool pt, hipStream_t s)
+{
+    hsg_status st = run_sweep_end(h, true, pt, h->stats, h->series == nullptr, 0u, 1u, -1, s);
+    if (st != HSG_OK || h->series == nullptr) return st;
+    st = run_series(h, s);
+    if (st != HSG_OK) return st;
+    const hipError_t e = hsg::launch_advance(dev_counter(h), s);
+    if (e != hipSuccess) return hip_fail(e, "counter launch");
+    return HSG_OK;
+}
+
+// All launches of one sweep, kernels only (capturable): heat-bath pairs,
+// over-relaxation pairs with the energy fused into the last pass, tempering,
+// then the device sweep counter advances.
 hsg_status enqueue_sweep(hsg_lattice *h, bool pt, hipStream_t s)
 {
     if (h->chain == 1) {
-        hsg_status st = run_tile_sweep(h, s);
-        if (st == HSG_OK && pt) st = run_pt(h, 0u, 1u, s);
-        if (st == HSG_OK && h->stats) st = run_stats(h, false, s);
-        if (st == HSG_OK && h->series) st = run_series(h, s);
-        if (st != HSG_OK) return st;
-        const hipError_t e = hsg::launch_advance(dev_counter(h), s);
-        if (e != hipSuccess) return hip_fail(e, "counter launch");
-        return HSG_OK;
+        const hsg_status st = run_tile_sweep(h, s);
+        return st == HSG_OK ? finish_sweep(h, pt, s) : st;
     }
     const int last_kind = h->n_or > 0 ? 1 : 0;
     bool batched = false;
@@ -966,7 +997,7 @@ hsg_status enqueue_sweep(hsg_lattice *h, bool pt, hipStream_t s)
         hsg_status st = HSG_OK;
         auto rest = [h](const Group &g) { return !use_replica(h, g); };
         for (int r = 0; r < h->n_hb && st == HSG_OK; ++r)
-            st = run_pair_of(h, 0, r, last_kind == 0 && r == h->n_hb - 1, s, rest, 0, -1, true);
+            st = run_pair_of(h, 0, r, last_kind == 0 && r == h->n_hb - 1, s, rest, 0, -1);
         if (st == HSG_OK) st = run_or_rounds(h, h->n_or, true, s, rest);
         if (st != HSG_OK) return st;
     } else {
@@ -983,52 +1014,30 @@ hsg_status enqueue_sweep(hsg_lattice *h, bool pt, hipStream_t s)
                 const int64_t r1 = std::min<int64_t>(g.n_rep, r0 + step);
                 for (int r = 0; r < h->n_hb; ++r) {
                     hsg_status st =
-                        run_pair_of(h, 0, r, last_kind == 0 && r == h->n_hb - 1, s, only, r0, r1, b == 0);
+                        run_pair_of(h, 0, r, last_kind == 0 && r == h->n_hb - 1, s, only, r0, r1);
                     if (st != HSG_OK) return st;
                 }
-                hsg_status st = run_or_rounds(h, h->n_or, true, s, only, r0, r1, b == 0);
+                hsg_status st = run_or_rounds(h, h->n_or, true, s, only, r0, r1);
                 if (st != HSG_OK) return st;
-            }
-            if (b > 0) {  // one reduction over every batch's partial sums
-                const int n_pb = use_pair(h, g) ? 1 : g.s_ytiles * g.s_zslabs;
-                const hipError_t e = hsg::launch_reduce_partials(reinterpret_cast<double *>(h->scratch + g.o_scr),
-                                                                 n_pb, g.n_rep,
-                                                                 reinterpret_cast<double *>(h->state + g.o_E), s);
-                if (e != hipSuccess) return hip_fail(e, "energy reduction launch");
             }
         }
     }
-    if (pt) {
-        hsg_status st = run_pt(h, 0u, 1u, s);
-        if (st != HSG_OK) return st;
-    }
-    if (h->stats) {
-        hsg_status st = run_stats(h, false, s);
-        if (st != HSG_OK) return st;
-    }
-    if (h->series) {
-        hsg_status st = run_series(h, s);
-        if (st != HSG_OK) return st;
-    }
-    const hipError_t e = hsg::launch_advance(dev_counter(h), s);
-    if (e != hipSuccess) return hip_fail(e, "counter launch");
-    return HSG_OK;
+    return finish_sweep(h, pt, s);
 }
 
-// Graph k holds 1 (k = 0) or kGraphSweeps (k = 1) sweeps, each with tempering
-// when pt_every == 1. Captured once on a private stream, replayed on the
-// caller's stream.
-hsg_status launch_graph(hsg_lattice *h, int k, hipStream_t s)
+// A graph of kGraphSweeps sweeps, each with tempering when pt_every == 1. Captured
+// once on a private stream, replayed on the caller's stream.
+hsg_status launch_graph(hsg_lattice *h, hipStream_t s)
 {
-    if (h->graph_exec[k] == nullptr) {
+    if (h->graph_exec == nullptr) {
         hipError_t e = hipSuccess;
         if (h->capture_stream == nullptr) e = hipStreamCreateWithFlags(&h->capture_stream, hipStreamNonBlocking);
         if (e != hipSuccess) return hip_fail(e, "capture stream");
         e = hipStreamBeginCapture(h->capture_stream, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) return hip_fail(e, "begin capture");
-        const int n = k == 0 ? 1 : kGraphSweeps;
         hsg_status st = HSG_OK;
-        for (int i = 0; i < n && st == HSG_OK; ++i) st = enqueue_sweep(h, h->pt_every == 1, h->capture_stream);
+        for (int i = 0; i < kGraphSweeps && st == HSG_OK; ++i)
+            st = enqueue_sweep(h, h->pt_every == 1, h->capture_stream);
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(h->capture_stream, &g);
         if (st != HSG_OK) {
@@ -1042,10 +1051,10 @@ hsg_status launch_graph(hsg_lattice *h, int k, hipStream_t s)
             (void)hipGraphDestroy(g);
             return hip_fail(e, "graph instantiate");
         }
-        h->graph[k] = g;
-        h->graph_exec[k] = x;
+        h->graph = g;
+        h->graph_exec = x;
     }
-    const hipError_t e = hipGraphLaunch(h->graph_exec[k], s);
+    const hipError_t e = hipGraphLaunch(h->graph_exec, s);
     if (e != hipSuccess) return hip_fail(e, "graph launch");
     return HSG_OK;
 }
@@ -1165,10 +1174,10 @@ hsg_status hsg_init_lattice(const hsg_desc *desc, const float *d_spins0, const f
             e = hipMemsetAsync(h->state + g.o_E, 0, (size_t)g.n_rep * 8, s);
         if (e == hipSuccess)
             e = hipMemsetAsync(h->state + g.o_acc, 0, (size_t)g.D * g.O * (g.T > 1 ? g.T - 1 : 1) * 8, s);
-        if (e == hipSuccess) e = hsg::launch_stats(stats_args(h, g), true, s);
-        if (e != hipSuccess) {
+        if (e == hipSuccess) st = clear_stats(h, g, s);
+        if (e != hipSuccess || st != HSG_OK) {
             delete h;
-            return hip_fail(e, "init");
+            return e != hipSuccess ? hip_fail(e, "init") : st;
         }
         // the host copies above read stack vectors: wait before they go away
         e = hipStreamSynchronize(s);
@@ -1198,14 +1207,13 @@ bool overlap_ok(const hsg_lattice *h)
     return true;
 }
 
-// Replica and sample range [r0, r1), [d0, d1) of half c of group g.
-void half_range(const Group &g, int c, int64_t &d0, int64_t &d1, int64_t &r0, int64_t &r1)
+// Replica range [r0, r1) of half c of group g.
+void half_range(const Group &g, int c, int64_t &r0, int64_t &r1)
 {
-    const int64_t half = g.D / 2, spp = (int64_t)g.O * g.T;
-    d0 = c == 0 ? 0 : half;
-    d1 = c == 0 ? half : g.D;
-    r0 = d0 * spp;
-    r1 = d1 * spp;
+    int64_t d0, d1;
+    sample_range(g, c, d0, d1);
+    r0 = d0 * g.O * g.T;
+    r1 = d1 * g.O * g.T;
 }
 
 // One sweep of half c (heat-bath pairs, then the rest), on stream s; `hb_done`
@@ -1216,70 +1224,23 @@ hsg_status enqueue_half_sweep(hsg_lattice *h, int c, bool pt, hipStream_t s, hip
     const int last_kind = h->n_or > 0 ? 1 : 0;
     hsg_status st = HSG_OK;
     for (const Group &g : h->lay.g) {
-        int64_t d0, d1, r0, r1;
-        half_range(g, c, d0, d1, r0, r1);
+        int64_t r0, r1;
+        half_range(g, c, r0, r1);
         auto only = [&g](const Group &x) { return &x == &g; };
         for (int r = 0; r < h->n_hb && st == HSG_OK; ++r)
-            st = run_pair_of(h, 0, r, last_kind == 0 && r == h->n_hb - 1, s, only, r0, r1, false);
+            st = run_pair_of(h, 0, r, last_kind == 0 && r == h->n_hb - 1, s, only, r0, r1);
     }
     hipError_t e = st == HSG_OK ? hipEventRecord(hb_done, s) : hipSuccess;
     if (e != hipSuccess) st = hip_fail(e, "event record");
     for (const Group &g : h->lay.g) {
         if (st != HSG_OK) break;
-        int64_t d0, d1, r0, r1;
-        half_range(g, c, d0, d1, r0, r1);
+        int64_t r0, r1;
+        half_range(g, c, r0, r1);
         auto only = [&g](const Group &x) { return &x == &g; };
-        st = run_or_rounds(h, h->n_or, true, s, only, r0, r1, false);
+        st = run_or_rounds(h, h->n_or, true, s, only, r0, r1);
         if (st != HSG_OK) break;
-        const int n_pb = use_pair(h, g) ? 1 : g.s_ytiles * g.s_zslabs;
-        e = hsg::launch_reduce_partials(reinterpret_cast<double *>(h->scratch + g.o_scr) + r0 * n_pb, n_pb,
-                                        r1 - r0, reinterpret_cast<double *>(h->state + g.o_E) + r0, s);
-        if (e != hipSuccess) {
-            st = hip_fail(e, "energy reduction launch");
-            break;
-        }
-        const int64_t OT = (int64_t)g.O * g.T;
-        if (pt) {
-            hsg::PtArgs a{};
-            a.slot_at_temp = reinterpret_cast<int32_t *>(h->state + g.o_sat) + d0 * OT;
-            a.temp_of_slot = reinterpret_cast<int32_t *>(h->state + g.o_tos) + d0 * OT;
-            a.E = reinterpret_cast<const double *>(h->state + g.o_E) + d0 * OT;
-            a.beta64 = reinterpret_cast<const double *>(h->coup + g.o_b64);
-            a.accepts = reinterpret_cast<unsigned long long *>(h->state + g.o_acc) + d0 * g.O * (g.T - 1);
-            a.D = (int32_t)(d1 - d0);
-            a.O = g.O;
-            a.T = g.T;
-            a.tptr = dev_counter(h);
-            a.ctr1 = 0;
-            a.purpose = 1;
-            a.key0 = (uint32_t)(h->seed & 0xFFFFFFFFu);
-            a.key1 = (uint32_t)(h->seed >> 32);
-            a.uid_base = g.uid_base + (uint32_t)d0;
-            e = hsg::launch_pt(a, s);
-            if (e != hipSuccess) {
-                st = hip_fail(e, "tempering launch");
-                break;
-            }
-        }
-        if (h->stats) {
-            hsg::StatsArgs a = stats_args(h, g);
-            a.slot_at_temp += d0 * OT;
-            a.E += d0 * OT;
-            a.sum += d0 * OT * 2;
-            a.flag += d0 * OT;
-            a.trips += d0 * OT;
-            a.D = (int32_t)(d1 - d0);
-            e = hsg::launch_stats(a, false, s);
-            if (e != hipSuccess) {
-                st = hip_fail(e, "statistics launch");
-                break;
-            }
-        }
     }
-    if (st == HSG_OK) {
-        e = hsg::launch_advance(dev_counter(h), s);
-        if (e != hipSuccess) st = hip_fail(e, "counter launch");
-    }
+    if (st == HSG_OK) st = run_sweep_end(h, true, pt, h->stats, true, 0u, 1u, c, s);
     h->cohort = 0;
     return st;
 }
@@ -1337,20 +1298,16 @@ hsg_status hsg_sweep(hsg_lattice *h, int32_t n_sweeps, hsg_stream_t stream)
         hsg_status st = overlapped_sweeps(h, n_sweeps, s);
         if (st != HSG_OK) return st;
         done = n_sweeps;
-    } else if (graphs) {
-        while (n_sweeps - done >= kGraphSweeps) {
-            hsg_status st = launch_graph(h, 1, s);
+    } else {
+        // Replays for long runs, plain launches for what is left: launching a graph of
+        // one sweep costs the host about as much as ten plain launches, and a sweep
+        // has three to ten.
+        while (graphs && n_sweeps - done >= kGraphSweeps) {
+            hsg_status st = launch_graph(h, s);
             if (st != HSG_OK) return st;
             done += kGraphSweeps;
             h->t += kGraphSweeps;
         }
-        while (done < n_sweeps) {
-            hsg_status st = launch_graph(h, 0, s);
-            if (st != HSG_OK) return st;
-            done += 1;
-            h->t += 1;
-        }
-    } else {
         for (; done < n_sweeps; ++done) {
             const bool pt = h->pt_every > 0 && ((h->t + 1) % (uint64_t)h->pt_every) == 0;
             hsg_status st = enqueue_sweep(h, pt, s);
@@ -1377,7 +1334,7 @@ hsg_status hsg_pair_sweep(hsg_lattice *h, int32_t kind, int32_t rep, hsg_stream_
     if (h == nullptr) return fail(HSG_E_INVALID, "handle is NULL");
     if (kind != 0 && kind != 1) return fail(HSG_E_INVALID, "kind = %d, need 0 (HB) or 1 (OR)", kind);
     if (rep < 0 || rep > 15) return fail(HSG_E_SIZE, "rep = %d, need 0..15", rep);
-    return run_pair_of(h, kind, rep, false, S(stream), [](const Group &) { return true; }, 0, -1, true);
+    return run_pair_of(h, kind, rep, false, S(stream), [](const Group &) { return true; }, 0, -1);
 }
 
 hsg_status hsg_or_pairs(hsg_lattice *h, int32_t n_pairs, hsg_stream_t stream)
@@ -1391,7 +1348,7 @@ hsg_status hsg_pt_exchange(hsg_lattice *h, hsg_stream_t stream)
 {
     if (h == nullptr) return fail(HSG_E_INVALID, "handle is NULL");
     if (h->pt_calls >= 0x100000000ull) return fail(HSG_E_SIZE, "standalone tempering counter exhausted");
-    const hsg_status st = run_pt(h, (uint32_t)h->pt_calls, 2u, S(stream));
+    const hsg_status st = run_sweep_end(h, false, true, false, false, (uint32_t)h->pt_calls, 2u, -1, S(stream));
     if (st == HSG_OK) h->pt_calls += 1;
     return st;
 }
@@ -1847,9 +1804,9 @@ hsg_status hsg_autotune(hsg_lattice *h, int32_t n_sweeps, void *d_backup, int32_
         h->overlap = cands[k].overlap;
         if (h->overlap && !overlap_ok(h)) continue;  // this choice would run as the one without overlap
         drop_graphs(h);
-        // warm-up: captures and launches both sweep graphs (kGraphSweeps sweeps,
-        // then one sweep, twice), since a fresh graph's first launch is slower
-        // than the later ones
+        // warm-up: captures and launches the sweep graph (kGraphSweeps sweeps, then two
+        // single ones), since a fresh graph's first launch is slower than the later
+        // ones
         st = hsg_sweep(h, kGraphSweeps + 2, stream);
         if (st != HSG_OK) break;
         e = hipEventRecord(ev[0], s);
@@ -2016,7 +1973,9 @@ hsg_status hsg_set_stats(hsg_lattice *h, int32_t enable)
 hsg_status hsg_reset_stats(hsg_lattice *h, hsg_stream_t stream)
 {
     if (h == nullptr) return fail(HSG_E_INVALID, "handle is NULL");
-    hsg_status st = run_stats(h, true, S(stream));
+    hsg_status st = HSG_OK;
+    for (const Group &g : h->lay.g)
+        if (st == HSG_OK) st = clear_stats(h, g, S(stream));
     if (st == HSG_OK) h->n_stats = 0;
     return st;
 }

@@ -134,30 +134,37 @@ hipError_t launch_pack_jbits(const float *J_can, uint8_t *Jbits, int64_t D, int3
 hipError_t launch_reduce_partials(const double *partials, int n_pb, int64_t n_rep, double *E,
                                   hipStream_t s);
 
-struct PtArgs {
+// After the updates of a sweep, one work-group per (sample, copy) ladder of up to
+// kMaxStreamGroups groups (ladder.hip): E from n_pb partial sums per replica (0: E
+// is there already), with pt one tempering walk (draws at counter word *tptr, or
+// ctr1 where tptr is null, for the given purpose), with stats the run statistics,
+// and where advance is not null *advance = *tptr + 1, written by the last
+// work-group to finish; the ticket must be zero and is left so.
+struct LadderArgs {
     int32_t *slot_at_temp;       // [D][O][T]
     int32_t *temp_of_slot;       // [D][O][T]
-    const double *E;             // [D][O][T] by slot
+    double *E;                   // [D][O][T] by slot
+    const double *partials;      // [D][O][T][n_pb]
     const double *beta64;        // [T]
     unsigned long long *accepts; // [D][O][T-1]
-    int32_t D, O, T;
-    const uint32_t *tptr;  // in-sweep passes read the counter here; nullptr: use ctr1
-    uint32_t ctr1, purpose;
-    uint32_t key0, key1, uid_base;
+    double *stat_sum;            // [D][O][T][2] (E, E^2 by rung)
+    int32_t *stat_flag;          // [D][O][T] by slot
+    uint32_t *stat_trips;
+    int32_t O, T, n_pb;
+    uint32_t uid_base;
 };
-hipError_t launch_pt(const PtArgs &a, hipStream_t s);
-
-// Run statistics: sum [D][O][T][2] (E, E^2 by rung), flag and trips [D][O][T] by slot.
-struct StatsArgs {
-    const int32_t *slot_at_temp;
-    const double *E;
-    double *sum;
-    int32_t *flag;
-    uint32_t *trips;
-    int32_t D, O, T;
+struct MultiLadderArgs {
+    int32_t n_groups, n_blocks;
+    int32_t block_start[kMaxStreamGroups + 1];
+    const uint32_t *tptr;
+    uint32_t *advance, *ticket;
+    uint32_t ctr1, purpose, pt, stats, key0, key1;
+    LadderArgs g[kMaxStreamGroups];
 };
-hipError_t launch_stats(const StatsArgs &a, bool clear, hipStream_t s);
+hipError_t launch_sweep_end(const MultiLadderArgs &m, hipStream_t s);
 
+// Clear the run statistics of n replicas.
+hipError_t launch_stats_clear(double *sum, int32_t *flag, uint32_t *trips, int64_t n, hipStream_t s);
 
 struct PackArgs {
     void *spins_int;

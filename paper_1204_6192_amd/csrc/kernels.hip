@@ -8,7 +8,6 @@
 // layout conversion between the canonical and internal arrays.
 #include "device.h"
 #include "kernels.h"
-#include "ladder.h"
 
 namespace hsg {
 
@@ -191,51 +190,21 @@ hipError_t launch_reduce_partials(const double *partials, int n_pb, int64_t n_re
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- tempering
-// One thread per (sample, copy) ladder (pt_ladder in ladder.h).
-__global__ __launch_bounds__(64) void k_pt(PtArgs a)
-{
-    const int64_t lad = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (lad >= (int64_t)a.D * a.O) return;
-    pt_ladder(a, lad, a.tptr ? *a.tptr : a.ctr1);
-}
-
-hipError_t launch_pt(const PtArgs &a, hipStream_t s)
-{
-    const int64_t n = (int64_t)a.D * a.O;
-    if (a.T < 2 || n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pt, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s, a);
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------- run statistics
-// One thread per ladder (stats_ladder in ladder.h).
-__global__ __launch_bounds__(64) void k_stats(StatsArgs a)
-{
-    const int64_t lad = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (lad >= (int64_t)a.D * a.O) return;
-    stats_ladder(a, lad);
-}
-
-__global__ __launch_bounds__(256) void k_stats_clear(StatsArgs a)
+__global__ __launch_bounds__(256) void k_stats_clear(double *sum, int32_t *flag, uint32_t *trips, int64_t n)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t n = (int64_t)a.D * a.O * a.T;
     if (g >= n) return;
-    a.sum[2 * g] = 0.0;
-    a.sum[2 * g + 1] = 0.0;
-    a.flag[g] = 0;
-    a.trips[g] = 0u;
+    sum[2 * g] = 0.0;
+    sum[2 * g + 1] = 0.0;
+    flag[g] = 0;
+    trips[g] = 0u;
 }
 
-hipError_t launch_stats(const StatsArgs &a, bool clear, hipStream_t s)
+hipError_t launch_stats_clear(double *sum, int32_t *flag, uint32_t *trips, int64_t n, hipStream_t s)
 {
-    const int64_t n = (int64_t)a.D * a.O;
     if (n == 0) return hipSuccess;
-    if (clear)
-        hipLaunchKernelGGL(k_stats_clear, dim3((unsigned)((n * a.T + 255) / 256)), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_stats, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(k_stats_clear, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, sum, flag, trips, n);
     return hipGetLastError();
 }
 

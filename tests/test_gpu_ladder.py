@@ -1,0 +1,113 @@
+"""The end of a sweep in one launch (energies from their partial sums, tempering walk,
+run statistics, sweep counter) against a plain Python walk over the same energies
+and random numbers: rung counts around the wave size and at both ends of the range,
+one partial sum, several, or none per replica, more lattice sizes than one launch
+takes. Maps, acceptances and counters are whole numbers; sums of E and E^2 of one
+or two sweeps are single float64 additions, equal bit for bit."""
+
+import numpy as np
+import pytest
+
+from paper_1204_6192_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hsg():
+    from paper_1204_6192_amd import hsg as mod
+    return mod
+
+
+def _walk(hsg, g, E, sat, ctr, purpose, seed):
+    """Eq. (4) from the lowest rung up; returns the new map and the acceptances."""
+    D, O, T = g.n_samples, g.n_copies, g.n_temps
+    beta = 1.0 / g.temps
+    sat, acc = sat.copy(), np.zeros((D, O, max(T - 1, 0)), dtype=np.int64)
+    key = np.array([seed & 0xFFFFFFFF, seed >> 32], dtype=np.uint64).astype(np.uint32)
+    for d in range(D):
+        for o in range(O):
+            if T < 2:
+                continue
+            c = np.array([[k, ctr, (o << 8) | (purpose << 20), g.sample_uid_base + d] for k in range(T - 1)],
+                         dtype=np.uint32)
+            w = hsg.debug_philox(c, np.tile(key, (T - 1, 1))).astype(np.uint64)
+            u = (((w[:, 0] << np.uint64(21)) ^ (w[:, 1] >> np.uint64(11))) + np.uint64(1)).astype(np.float64) * 2.0 ** -53
+            for k in range(T - 1):
+                a, b = sat[d, o, k], sat[d, o, k + 1]
+                delta = (beta[k + 1] - beta[k]) * (E[d, o, b] - E[d, o, a])
+                if delta >= 0.0 or u[k] <= np.exp(delta):
+                    sat[d, o, k], sat[d, o, k + 1] = b, a
+                    acc[d, o, k] += 1
+    return sat, acc
+
+
+def _groups(rungs, L, D, O, t_max):
+    rng = np.random.Generator(np.random.Philox(inputs.INSTANCE_SEED_BASE + 92))
+    out, uid = [], 0
+    for T in rungs:
+        out.append(inputs.make_group(rng, L, D, O, inputs.geometric_ladder(0.2, t_max if T > 1 else 0.2, T),
+                                     sample_uid_base=uid))
+        uid += D
+    return out
+
+
+# variant 0: energies from LDS (none to reduce); 4: one partial per replica; 1: the
+# gather kernel's, several at L = 12 (432 site pairs, two blocks of 256)
+@pytest.mark.parametrize("variant,L", [(0, 4), (4, 8), (1, 12)])
+@pytest.mark.parametrize("rungs,t_max", [((1, 2, 3), 3.0), ((63, 64, 65), 2.0), ((66, 128, 129), 0.6),
+                                         ((130, 255, 256), 8.0), (tuple(range(1, 12)), 1.0)])
+def test_end_of_sweep(hsg, variant, L, rungs, t_max):
+    groups = _groups(rungs, L, 2, 2, t_max)
+    seed = inputs.PHILOX_KEY_BASE + 92
+    lat = hsg.Lattice(groups, n_hb=1, n_or=1, seed=seed)
+    lat.set_kernel(variant)
+    lat.set_stats(True)
+
+    def split(t, per):  # per group [D][O][per]
+        out, i = [], 0
+        for g in groups:
+            n = g.n_samples * g.n_copies * per(g)
+            out.append(t[i:i + n].cpu().numpy().reshape(g.n_samples, g.n_copies, per(g)))
+            i += n
+        return out
+
+    sat = [np.tile(np.arange(g.n_temps), (g.n_samples, g.n_copies, 1)) for g in groups]
+    acc = [np.zeros((g.n_samples, g.n_copies, g.n_temps - 1), dtype=np.int64) for g in groups]
+    s1 = [np.zeros((g.n_samples, g.n_copies, g.n_temps, 2)) for g in groups]
+    flag = [np.zeros(s.shape, dtype=int) for s in sat]
+    trips = [np.zeros(s.shape, dtype=int) for s in sat]
+    for t in range(2):
+        lat.sweep(1)
+        E = split(lat.get_energies(), lambda g: g.n_temps)
+        for k, g in enumerate(groups):
+            sat[k], a = _walk(hsg, g, E[k], sat[k], t, 1, seed)
+            acc[k] += a
+            e = np.take_along_axis(E[k], sat[k], axis=2)
+            s1[k] += np.stack([e, e * e], axis=-1)
+            if g.n_temps > 1:
+                for d in range(g.n_samples):
+                    for o in range(g.n_copies):
+                        lo, hi = sat[k][d, o, 0], sat[k][d, o, -1]
+                        trips[k][d, o, lo] += flag[k][d, o, lo] == 2
+                        flag[k][d, o, lo] = 1
+                        if flag[k][d, o, hi] == 1:
+                            flag[k][d, o, hi] = 2
+        for x, y in zip(split(lat.get_temp_map(), lambda g: g.n_temps), sat):
+            assert np.array_equal(x, y)
+    assert lat.get_state()[0] == 2
+    for x, y in zip(split(lat.get_pt_accepts(), lambda g: g.n_temps - 1), acc):
+        assert np.array_equal(x, y)
+    sums, tr, n = lat.get_stats()
+    assert n == 2
+    i = 0
+    for k, g in enumerate(groups):
+        m = g.n_slots
+        assert np.array_equal(sums[i:i + m].cpu().numpy().reshape(s1[k].shape), s1[k])
+        assert np.array_equal(tr[i:i + m].cpu().numpy().reshape(trips[k].shape), trips[k])
+        i += m
+    lat.pt_exchange()  # standalone pass: call 0, the same energies
+    E = split(lat.get_energies(), lambda g: g.n_temps)
+    for k, (x, g) in enumerate(zip(split(lat.get_temp_map(), lambda g: g.n_temps), groups)):
+        assert np.array_equal(x, _walk(hsg, g, E[k], sat[k], 0, 2, seed)[0])
+    lat.close()
