@@ -711,11 +711,63 @@ __device__ __forceinline__ float pm1_from_bit(uint32_t bits, int b)
     return __uint_as_float(((bits << (31 - b)) & 0x80000000u) | 0x3F800000u);
 }
 
-// The same for lattices addressed with 32-bit byte offsets, from one uniform
-// base per coupling plane (Jp[n] = the plane of bond n): each load is that base
-// plus the lane's byte offset, with no per-load address arithmetic.
+// Couplings of a parity, [3][Nh / 2] float4: per pair of sites (2q, 2q + 1) the
+// couplings +x and +y of both, then +z and -x, then -y and -z. The n-th coupling of
+// site j in neighbour order (+x, -x, +y, -y, +z, -z) is element coupling_at(n, j).
+//
+// Why float4: a wave's load keeps the vector memory path busy for 16 cycles whether a
+// lane takes 8 bytes or 16 (measured: 17.7 and 17.4 cycles per load and CU, 18 and
+// 36 TB/s from L2), and that path, not HBM, bounded the z-marches (busy 94 to 100 %
+// of the launch): six 8-byte loads per pair and half-sweep became three.
+__device__ __forceinline__ int64_t coupling_at(int n, int64_t j, int64_t Nh)
+{
+    const int m = (n >> 1) + 3 * (n & 1);  // +x +y +z -x -y -z
+    return ((m >> 1) * (Nh >> 1) + (j >> 1)) * 4 + 2 * (m & 1) + (j & 1);
+}
+
+// Random field of a parity: [Nh / 2] float4 (x of the pair, y of the pair), then
+// [Nh / 2] float2 (z of the pair); component m of site j is element field_at(m, j).
+__device__ __forceinline__ int64_t field_at(int m, int64_t j, int64_t Nh)
+{
+    return m < 2 ? (j >> 1) * 4 + 2 * m + (j & 1) : 2 * Nh + j;
+}
+
+// The field of the pair at half-indices j0, j0 + 1 (j0 even).
+template <bool B32>
+__device__ __forceinline__ void load_field_pair(const float *H, uint32_t Nh, uint32_t j0, v3 &a, v3 &b)
+{
+    const float4 xy = *reinterpret_cast<const float4 *>(elem<B32>(H, 2 * j0));
+    const float2 z = *reinterpret_cast<const float2 *>(elem<B32>(H, 2 * Nh + j0));
+    a = v3{xy.x, xy.z, z.x};
+    b = v3{xy.y, xy.w, z.y};
+}
+
+// The field term of the energy at a pair of sites s0, s1, added to e.
+template <bool B32>
+__device__ __forceinline__ void field_energy(v3 s0, v3 s1, const float *H, uint32_t Nh, uint32_t j0, double &e)
+{
+    v3 f0, f1;
+    load_field_pair<B32>(H, Nh, j0, f0, f1);
+    e -= (double)f0.x * s0.x + (double)f0.y * s0.y + (double)f0.z * s0.z;
+    e -= (double)f1.x * s1.x + (double)f1.y * s1.y + (double)f1.z * s1.z;
+}
+
+__device__ __forceinline__ void couplings_of(float4 u, float4 v, float4 w, float2 (&jc)[6])
+{
+    jc[0] = make_float2(u.x, u.y);
+    jc[2] = make_float2(u.z, u.w);
+    jc[4] = make_float2(v.x, v.y);
+    jc[1] = make_float2(v.z, v.w);
+    jc[3] = make_float2(w.x, w.y);
+    jc[5] = make_float2(w.z, w.w);
+}
+
+// The couplings and the field of the pair at half-indices j0, j0 + 1 (j0 even),
+// with 32-bit byte offsets from one uniform base per float4 plane (Jp[k] = plane k):
+// each load is that base plus the lane's byte offset, with no per-load address
+// arithmetic.
 template <bool JB, bool FIELD>
-__device__ __forceinline__ void load_couplings_planes(const float *const (&Jp)[6], const uint8_t *Jbb,
+__device__ __forceinline__ void load_couplings_planes(const float *const (&Jp)[3], const uint8_t *Jbb,
                                                       const float *Hb, bool jbits, bool field, uint32_t Nh,
                                                       uint32_t j0, float2 (&jc)[6], v3 &hs0, v3 &hs1)
 {
@@ -725,20 +777,16 @@ __device__ __forceinline__ void load_couplings_planes(const float *const (&Jp)[6
         for (int n = 0; n < 6; ++n)
             jc[n] = make_float2(pm1_from_bit(bits, n), pm1_from_bit(bits, 8 + n));
     } else {
-#pragma unroll
-        for (int n = 0; n < 6; ++n) jc[n] = *reinterpret_cast<const float2 *>(elem<true>(Jp[n], j0));
+        couplings_of(*reinterpret_cast<const float4 *>(elem<true>(Jp[0], 2 * j0)),
+                     *reinterpret_cast<const float4 *>(elem<true>(Jp[1], 2 * j0)),
+                     *reinterpret_cast<const float4 *>(elem<true>(Jp[2], 2 * j0)), jc);
     }
     hs0 = v3{0.f, 0.f, 0.f};
     hs1 = v3{0.f, 0.f, 0.f};
-    if (FIELD && field) {
-        const float2 hx = *reinterpret_cast<const float2 *>(elem<true>(Hb, j0));
-        const float2 hy = *reinterpret_cast<const float2 *>(elem<true>(Hb, Nh + j0));
-        const float2 hz = *reinterpret_cast<const float2 *>(elem<true>(Hb, 2 * Nh + j0));
-        hs0 = v3{hx.x, hy.x, hz.x};
-        hs1 = v3{hx.y, hy.y, hz.y};
-    }
+    if (FIELD && field) load_field_pair<true>(Hb, Nh, j0, hs0, hs1);
 }
 
+// The same from the parity's base alone.
 template <bool JB, bool FIELD, bool B32 = false>
 __device__ __forceinline__ void load_couplings(const float *Jb, const uint8_t *Jbb, const float *Hb, bool jbits,
                                                bool field, uint32_t Nh, uint32_t j0, float2 (&jc)[6], v3 &hs0,
@@ -750,18 +798,13 @@ __device__ __forceinline__ void load_couplings(const float *Jb, const uint8_t *J
         for (int n = 0; n < 6; ++n)
             jc[n] = make_float2(pm1_from_bit(bits, n), pm1_from_bit(bits, 8 + n));
     } else {
-#pragma unroll
-        for (int n = 0; n < 6; ++n) jc[n] = *reinterpret_cast<const float2 *>(elem<B32>(Jb, n * Nh + j0));
+        couplings_of(*reinterpret_cast<const float4 *>(elem<B32>(Jb, 2 * j0)),
+                     *reinterpret_cast<const float4 *>(elem<B32>(Jb, 2 * Nh + 2 * j0)),
+                     *reinterpret_cast<const float4 *>(elem<B32>(Jb, 4 * Nh + 2 * j0)), jc);
     }
     hs0 = v3{0.f, 0.f, 0.f};
     hs1 = v3{0.f, 0.f, 0.f};
-    if (FIELD && field) {
-        const float2 hx = *reinterpret_cast<const float2 *>(elem<B32>(Hb, j0));
-        const float2 hy = *reinterpret_cast<const float2 *>(elem<B32>(Hb, Nh + j0));
-        const float2 hz = *reinterpret_cast<const float2 *>(elem<B32>(Hb, 2 * Nh + j0));
-        hs0 = v3{hx.x, hy.x, hz.x};
-        hs1 = v3{hx.y, hy.y, hz.y};
-    }
+    if (FIELD && field) load_field_pair<B32>(Hb, Nh, j0, hs0, hs1);
 }
 
 // ---------------------------------------------------------------- reductions

@@ -12,9 +12,10 @@ constexpr int kBlock = 256;  // work-group size of the sweep and reduction kerne
 //   spins  [r][parity][3][Nh]      storage type per codec, Nh = L^3 / 2,
 //                                  element j of parity p = canonical site i with
 //                                  parity(i) = p and i >> 1 = j
-//   J6     [d][parity][6][Nh]      float32, the six couplings of each site in
-//                                  neighbour order +x, -x, +y, -y, +z, -z
-//   Hp     [d][parity][3][Nh]      float32
+//   J6     [d][parity][6 Nh]       float32, the six couplings of each site (neighbour
+//                                  order +x, -x, +y, -y, +z, -z) as coupling_at places
+//                                  them: three float4 per pair of sites
+//   Hp     [d][parity][3 Nh]       float32, as field_at places them
 struct SweepArgs {
     void *spins;
     const float *J6;

@@ -70,13 +70,13 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
             neighbours(j, a.L, a.Lh, p, nb[k]);
             const float *Jb = a.J6 + ((int64_t)d * 2 + p) * 6 * Nh;
 #pragma unroll
-            for (int n = 0; n < 6; ++n) Jc[k][n] = Jb[n * Nh + j];
+            for (int n = 0; n < 6; ++n) Jc[k][n] = Jb[coupling_at(n, j, Nh)];
             if (FIELD) {
                 const float *Hb = a.Hp + ((int64_t)d * 2 + p) * 3 * Nh;
-                Hs[k] = v3{Hb[j], Hb[Nh + j], Hb[2 * Nh + j]};
+                Hs[k] = v3{Hb[field_at(0, j, Nh)], Hb[field_at(1, j, Nh)], Hb[field_at(2, j, Nh)]};
                 if (ENERGY) {  // the field on the other parity at the same half-index
                     const float *Ho = a.Hp + ((int64_t)d * 2 + (1 - p)) * 3 * Nh;
-                    He[k] = v3{Ho[j], Ho[Nh + j], Ho[2 * Nh + j]};
+                    He[k] = v3{Ho[field_at(0, j, Nh)], Ho[field_at(1, j, Nh)], Ho[field_at(2, j, Nh)]};
                 }
             }
         }
@@ -271,12 +271,12 @@ __global__ __launch_bounds__(256) void k_pack_couplings(PackArgs a)
     const int64_t j = i >> 1;
     const float *Jc = a.J_can + d * 3 * N;
     float *J6 = a.J6 + (d * 2 + p) * 6 * Nh;
-    J6[0 * Nh + j] = Jc[0 * N + i];
-    J6[1 * Nh + j] = Jc[0 * N + index_of(c.x - 1, c.y, c.z, a.L)];
-    J6[2 * Nh + j] = Jc[1 * N + i];
-    J6[3 * Nh + j] = Jc[1 * N + index_of(c.x, c.y - 1, c.z, a.L)];
-    J6[4 * Nh + j] = Jc[2 * N + i];
-    J6[5 * Nh + j] = Jc[2 * N + index_of(c.x, c.y, c.z - 1, a.L)];
+    J6[coupling_at(0, j, Nh)] = Jc[0 * N + i];
+    J6[coupling_at(1, j, Nh)] = Jc[0 * N + index_of(c.x - 1, c.y, c.z, a.L)];
+    J6[coupling_at(2, j, Nh)] = Jc[1 * N + i];
+    J6[coupling_at(3, j, Nh)] = Jc[1 * N + index_of(c.x, c.y - 1, c.z, a.L)];
+    J6[coupling_at(4, j, Nh)] = Jc[2 * N + i];
+    J6[coupling_at(5, j, Nh)] = Jc[2 * N + index_of(c.x, c.y, c.z - 1, a.L)];
 }
 
 __global__ __launch_bounds__(256) void k_pack_field(PackArgs a)
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(256) void k_pack_field(PackArgs a)
     const int64_t j = i >> 1;
     const float *Hc = a.H_can + d * 3 * N;
     float *Hp = a.Hp + (d * 2 + p) * 3 * Nh;
-    for (int m = 0; m < 3; ++m) Hp[m * Nh + j] = Hc[m * N + i];
+    for (int m = 0; m < 3; ++m) Hp[field_at(m, j, Nh)] = Hc[m * N + i];
 }
 
 // Coupling sign bits: bit n of byte [d][p][j] is set when the n-th coupling of
@@ -409,14 +409,16 @@ __global__ __launch_bounds__(kBlock) void k_energy(EnergyArgs a)
         for (int n = 0; n < 6; ++n) {
             const v3 sn = C::load(base + C::kPlanes * Nh, Nh, nb[n]);
             const double sd = (double)s0.x * sn.x + (double)s0.y * sn.y + (double)s0.z * sn.z;
-            e -= (double)J6[n * Nh + j] * sd;
+            e -= (double)J6[coupling_at(n, j, Nh)] * sd;
         }
         if (a.Hp != nullptr) {
             const v3 s1 = C::load(base + C::kPlanes * Nh, Nh, j);
             const float *H0 = a.Hp + (d * 2 + 0) * 3 * Nh;
             const float *H1 = a.Hp + (d * 2 + 1) * 3 * Nh;
-            e -= (double)H0[j] * s0.x + (double)H0[Nh + j] * s0.y + (double)H0[2 * Nh + j] * s0.z;
-            e -= (double)H1[j] * s1.x + (double)H1[Nh + j] * s1.y + (double)H1[2 * Nh + j] * s1.z;
+            e -= (double)H0[field_at(0, j, Nh)] * s0.x + (double)H0[field_at(1, j, Nh)] * s0.y +
+                 (double)H0[field_at(2, j, Nh)] * s0.z;
+            e -= (double)H1[field_at(0, j, Nh)] * s1.x + (double)H1[field_at(1, j, Nh)] * s1.y +
+                 (double)H1[field_at(2, j, Nh)] * s1.z;
         }
     }
     const double tot = block_sum(e, red);
@@ -515,9 +517,12 @@ __global__ __launch_bounds__(kBlock) void k_energy_stream(EnergyArgs a)
         const int64_t jj = (int64_t)(z * L + y) * Lh + (x0 >> 1);
         float2 jc[3][2];
 #pragma unroll
-        for (int a3 = 0; a3 < 3; ++a3) {
-            jc[a3][0] = *reinterpret_cast<const float2 *>(J6 + ((int64_t)p0 * 6 + 2 * a3) * Nh + jj);
-            jc[a3][1] = *reinterpret_cast<const float2 *>(J6 + ((int64_t)(1 - p0) * 6 + 2 * a3) * Nh + jj);
+        for (int k = 0; k < 2; ++k) {  // +x and +y, +z of the pairs of either parity (coupling_at)
+            const float *Jk = J6 + (int64_t)(k ? 1 - p0 : p0) * 6 * Nh + 2 * jj;
+            const float4 u = *reinterpret_cast<const float4 *>(Jk);
+            jc[0][k] = make_float2(u.x, u.y);
+            jc[1][k] = make_float2(u.z, u.w);
+            jc[2][k] = *reinterpret_cast<const float2 *>(Jk + 2 * Nh);
         }
         __syncthreads();
         if (active) {
@@ -539,10 +544,9 @@ __global__ __launch_bounds__(kBlock) void k_energy_stream(EnergyArgs a)
             }
             if (H != nullptr) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int64_t hj = (int64_t)((u & 1) ? 1 - p0 : p0) * 3 * Nh + jj + (u >> 1);
-                    e -= (double)H[hj] * cur[u].x + (double)H[Nh + hj] * cur[u].y + (double)H[2 * Nh + hj] * cur[u].z;
-                }
+                for (int k = 0; k < 2; ++k)
+                    field_energy<false>(cur[k], cur[k + 2], H + (int64_t)(k ? 1 - p0 : p0) * 3 * Nh, (uint32_t)Nh,
+                                        (uint32_t)jj, e);
             }
         }
 #pragma unroll

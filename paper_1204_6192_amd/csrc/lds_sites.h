@@ -1,5 +1,5 @@
 // lds_sites.h -- updates of site pairs whose spins, decoded, are held in LDS as
-// three consecutive floats per site (replica.hip, wave_march.hip).
+// three consecutive floats per site (replica.hip).
 //
 // A pair of sites is three 8-byte LDS accesses from one address, and consecutive
 // lanes (24 bytes apart) fall into distinct banks. A plane holds (L/2)^2 pairs
@@ -148,17 +148,6 @@ __device__ __forceinline__ typename Codec<STORE>::R pair_update(const PairField<
         e -= (double)s1.x * f.x1 + (double)s1.y * f.y1 + (double)s1.z * f.z1;
     }
     return code;
-}
-
-// The field term of the even sites at the half-indices j0, j0 + 1 (their spins
-// g0, g1, their field planes Ho), added to e.
-__device__ __forceinline__ void field_energy(v3 g0, v3 g1, const float *Ho, uint32_t Nh, uint32_t j0, double &e)
-{
-    const float2 fx = *reinterpret_cast<const float2 *>(elem<true>(Ho, j0));
-    const float2 fy = *reinterpret_cast<const float2 *>(elem<true>(Ho, Nh + j0));
-    const float2 fz = *reinterpret_cast<const float2 *>(elem<true>(Ho, 2 * Nh + j0));
-    e -= (double)fx.x * g0.x + (double)fy.x * g0.y + (double)fz.x * g0.z;
-    e -= (double)fx.y * g1.x + (double)fy.y * g1.y + (double)fz.y * g1.z;
 }
 
 }  // namespace hsg

@@ -79,9 +79,7 @@ __device__ __forceinline__ void replica_body(const ReplicaArgs &a, const int lb,
         const float *Jb = a.J6 + (d * 2 + p) * 6 * (int64_t)Nh;
         const uint8_t *Jbb = jbits ? a.Jbits + (d * 2 + p) * (int64_t)Nh : nullptr;
         const float *Hb = field ? a.Hp + (d * 2 + p) * 3 * (int64_t)Nh : nullptr;
-        const float *Jp[6];
-#pragma unroll
-        for (int n = 0; n < 6; ++n) Jp[n] = Jb + n * (int64_t)Nh;
+        const float *const Jp[3] = {Jb, Jb + 2 * (int64_t)Nh, Jb + 4 * (int64_t)Nh};
         float *own = mem + (p ? 3 * Nh : 0u);
         const float *oth = mem + (p ? 0u : 3 * Nh);
 #pragma unroll 1
@@ -110,7 +108,7 @@ __device__ __forceinline__ void replica_body(const ReplicaArgs &a, const int lb,
             if (store) C::template store_raw_pair<true>(p ? sp1 : sp0, Nh, j0, code);
             if (ENERGY && field) {
                 pair_get(oth + 3 * j0, o0, o1);
-                field_energy(o0, o1, a.Hp + d * 2 * 3 * (int64_t)Nh, Nh, j0, e);
+                field_energy<true>(o0, o1, a.Hp + d * 2 * 3 * (int64_t)Nh, Nh, j0, e);
             }
         }
     };

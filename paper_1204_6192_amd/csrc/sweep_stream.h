@@ -79,9 +79,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int lb, f
     const uint8_t *Jbb = jbits ? a.Jbits + (d * 2 + p) * (int64_t)Nh : nullptr;
     const float *Hb = field ? a.Hp + (d * 2 + p) * 3 * (int64_t)Nh : nullptr;
     const float *Ho = field ? a.Hp + (d * 2 + (1 - p)) * 3 * (int64_t)Nh : nullptr;
-    const float *Jp[6];  // one base per coupling plane (uniform with UNI)
-#pragma unroll
-    for (int n = 0; n < 6; ++n) Jp[n] = Jb + n * (int64_t)Nh;
+    // one base per coupling plane (uniform with UNI)
+    const float *const Jp[3] = {Jb, Jb + 2 * (int64_t)Nh, Jb + 4 * (int64_t)Nh};
     float beta = 0.0f;
     uint32_t c2 = 0, uid = 0;
     const uint32_t tsweep = *a.tptr;
@@ -211,11 +210,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int lb, f
                 e -= (double)v0.x * hx0 + (double)v0.y * hy0 + (double)v0.z * hz0;
                 e -= (double)v1.x * hx1 + (double)v1.y * hy1 + (double)v1.z * hz1;
                 if (field) {  // field term of the even sites at my two half-indices
-                    const float2 fx = *reinterpret_cast<const float2 *>(elem<UNI>(Ho, j0));
-                    const float2 fy = *reinterpret_cast<const float2 *>(elem<UNI>(Ho, Nh + j0));
-                    const float2 fz = *reinterpret_cast<const float2 *>(elem<UNI>(Ho, 2 * Nh + j0));
-                    e -= (double)fx.x * cur0.x + (double)fy.x * cur0.y + (double)fz.x * cur0.z;
-                    e -= (double)fx.y * cur1.x + (double)fy.y * cur1.y + (double)fz.y * cur1.z;
+                    field_energy<UNI>(cur0, cur1, Ho, Nh, j0, e);
                 }
             }
         }
@@ -362,12 +357,9 @@ __device__ __forceinline__ void pair_body(const StreamArgs &a, const int lb, flo
     const uint8_t *Jb1 = jbits ? a.Jbits + (d * 2 + 1) * (int64_t)Nh : nullptr;
     const float *H0 = field ? a.Hp + (d * 2 + 0) * 3 * (int64_t)Nh : nullptr;
     const float *H1 = field ? a.Hp + (d * 2 + 1) * 3 * (int64_t)Nh : nullptr;
-    const float *Jp0[6], *Jp1[6];  // one uniform base per coupling plane
-#pragma unroll
-    for (int n = 0; n < 6; ++n) {
-        Jp0[n] = J0 + n * Nh;
-        Jp1[n] = J1 + n * Nh;
-    }
+    // one uniform base per coupling plane
+    const float *const Jp0[3] = {J0, J0 + 2 * Nh, J0 + 4 * Nh};
+    const float *const Jp1[3] = {J1, J1 + 2 * Nh, J1 + 4 * Nh};
     float beta = 0.0f;
     uint32_t c2A = 0, c2B = 0, uid = 0;
     const uint32_t tsweep = *a.tptr;
@@ -441,11 +433,7 @@ __device__ __forceinline__ void pair_body(const StreamArgs &a, const int lb, flo
                                                       hB1, o_prv0, o_prv1, rrB, beta, cB, sB0, sB1);
                 C::template store_raw_pair<true>(sp1, Nh, jB, cB);
                 if (ENERGY && field) {  // field on the parity-0 sites at the same half-indices
-                    const float2 fx = *reinterpret_cast<const float2 *>(elem<true>(H0, jB));
-                    const float2 fy = *reinterpret_cast<const float2 *>(elem<true>(H0, Nh + jB));
-                    const float2 fz = *reinterpret_cast<const float2 *>(elem<true>(H0, 2 * Nh + jB));
-                    e -= (double)fx.x * a_m10.x + (double)fy.x * a_m10.y + (double)fz.x * a_m10.z;
-                    e -= (double)fx.y * a_m11.x + (double)fy.y * a_m11.y + (double)fz.y * a_m11.z;
+                    field_energy<true>(a_m10, a_m11, H0, Nh, jB, e);
                 }
             }
             a_m20 = a_m10; a_m21 = a_m11;
@@ -496,16 +484,8 @@ __device__ __forceinline__ void pair_body(const StreamArgs &a, const int lb, flo
             C::template store_raw_pair<true>(sp1, Nh, jL, cL);
             C::template store_raw_pair<true>(sp1, Nh, j0, cZ);
             if (ENERGY && field) {
-                const float2 fx = *reinterpret_cast<const float2 *>(elem<true>(H0, jL));
-                const float2 fy = *reinterpret_cast<const float2 *>(elem<true>(H0, Nh + jL));
-                const float2 fz = *reinterpret_cast<const float2 *>(elem<true>(H0, 2 * Nh + jL));
-                e -= (double)fx.x * a_m10.x + (double)fy.x * a_m10.y + (double)fz.x * a_m10.z;
-                e -= (double)fx.y * a_m11.x + (double)fy.y * a_m11.y + (double)fz.y * a_m11.z;
-                const float2 gx = *reinterpret_cast<const float2 *>(elem<true>(H0, j0));
-                const float2 gy = *reinterpret_cast<const float2 *>(elem<true>(H0, Nh + j0));
-                const float2 gz = *reinterpret_cast<const float2 *>(elem<true>(H0, 2 * Nh + j0));
-                e -= (double)gx.x * n00.x + (double)gy.x * n00.y + (double)gz.x * n00.z;
-                e -= (double)gx.y * n01.x + (double)gy.y * n01.y + (double)gz.y * n01.z;
+                field_energy<true>(a_m10, a_m11, H0, Nh, jL, e);
+                field_energy<true>(n00, n01, H0, Nh, j0, e);
             }
         }
     }
@@ -593,12 +573,7 @@ __device__ __forceinline__ void quad_body(const StreamArgs &a, const int lb, flo
     const float *H1 = field ? a.Hp + (d * 2 + 1) * 3 * (int64_t)Nh : nullptr;
     // one base per coupling plane: uniform, so each load is that base plus the
     // lane's byte offset, with no per-load address arithmetic
-    const float *Jp[2][6];
-#pragma unroll
-    for (int n = 0; n < 6; ++n) {
-        Jp[0][n] = J0 + n * Nh;
-        Jp[1][n] = J1 + n * Nh;
-    }
+    const float *const Jp[2][3] = {{J0, J0 + 2 * Nh, J0 + 4 * Nh}, {J1, J1 + 2 * Nh, J1 + 4 * Nh}};
 
     // The loaded spins are addressed by the step modulo 4 (the march is
     // unrolled by four, so the indices are constants and a load lands where it
@@ -718,11 +693,7 @@ __device__ __forceinline__ void quad_body(const StreamArgs &a, const int lb, flo
                                                    zm1, jc[s], hs0[s], hs1[s], od0, od1, u32x4{0u, 0u, 0u, 0u}, 0.0f,
                                                    code, r0, r1);
                 if (ENERGY && field) {  // field on the parity-0 sites at the same half-indices: stage D - 2
-                    const float2 fx = *reinterpret_cast<const float2 *>(elem<true>(H0, jw));
-                    const float2 fy = *reinterpret_cast<const float2 *>(elem<true>(H0, Nh + jw));
-                    const float2 fz = *reinterpret_cast<const float2 *>(elem<true>(H0, 2 * Nh + jw));
-                    e -= (double)fx.x * c0.x + (double)fy.x * c0.y + (double)fz.x * c0.z;
-                    e -= (double)fx.y * c1.x + (double)fy.y * c1.y + (double)fz.y * c1.z;
+                    field_energy<true>(c0, c1, H0, Nh, jw, e);
                 }
             } else {
                 (void)update_pair<STORE, 1, false>(lds, lo, cstride, Lh, ty, lrm, lrp, xh0, o, c0, c1, zp0, zp1, zm0,
