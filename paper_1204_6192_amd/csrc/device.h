@@ -374,70 +374,76 @@ __device__ __forceinline__ T *elem(T *p, uint32_t i)
     }
 }
 
-// Spins of one replica, one parity: three component planes of Nh values.
+// Spins of one replica, one parity: kPlanes Nh elements of T, site j = half-index j
+// of the parity. The marches take pairs of sites (j0, j0 + 1), j0 even, and a wave's
+// load costs the vector memory path 16 cycles whatever its width (see coupling_at),
+// so a pair stands in as few pieces as possible:
+//   float32           [Nh / 2] float4 (x0, x1, y0, y1), then [Nh / 2] float2 (z0, z1)
+//   float16, bfloat16 [Nh / 2] of 12 bytes (x0, x1, y0, y1, z0, z1)
+//   quantised angle   [Nh] words
 template <int STORE>
 struct Codec;
 
 template <>
 struct Codec<0> {  // float32: stored renormalised, read as is
     using T = float;
-    static constexpr int kPlanes = 3;  // component planes per parity
+    static constexpr int kPlanes = 3;  // elements per site and parity
     __device__ static __forceinline__ v3 load(const T *p, int64_t cs, int64_t j)
     {
-        return v3{p[j], p[cs + j], p[2 * cs + j]};
+        const T *q = p + 4 * (j >> 1) + (j & 1);
+        return v3{q[0], q[2], p[2 * cs + j]};
     }
-    // the same with 32-bit byte offsets from a uniform base (3 cs sizeof(T) < 2^32)
-    __device__ static __forceinline__ v3 load32(const T *p, uint32_t cs, uint32_t j)
+    // site j of the array at element `at` of the base, with 32-bit byte offsets from
+    // that (uniform) base (everything within 4 GiB of it)
+    __device__ static __forceinline__ v3 load32(const T *p, uint32_t cs, uint32_t at, uint32_t j)
     {
-        return v3{*elem<true>(p, j), *elem<true>(p, cs + j), *elem<true>(p, 2 * cs + j)};
+        const uint32_t q = at + 4 * (j >> 1) + (j & 1);
+        return v3{*elem<true>(p, q), *elem<true>(p, q + 2), *elem<true>(p, at + 2 * cs + j)};
     }
     __device__ static __forceinline__ void store(T *p, int64_t cs, int64_t j, v3 s)
     {
-        p[j] = s.x;
-        p[cs + j] = s.y;
+        T *q = p + 4 * (j >> 1) + (j & 1);
+        q[0] = s.x;
+        q[2] = s.y;
         p[2 * cs + j] = s.z;
     }
     __device__ static __forceinline__ v3 stored_value(v3 s) { return s; }
-    // Two neighbouring sites j0, j0 + 1 (j0 even, 8-byte aligned): one 8-byte
-    // access per component plane; 32-bit offsets (3 Nh < 2^32 for L <= 1024).
-    template <bool B32 = false>
-    __device__ static __forceinline__ void load_pair(const T *p, uint32_t cs, uint32_t j0, v3 &a, v3 &b)
-    {
-        const float2 x = *reinterpret_cast<const float2 *>(elem<B32>(p, j0));
-        const float2 y = *reinterpret_cast<const float2 *>(elem<B32>(p, cs + j0));
-        const float2 z = *reinterpret_cast<const float2 *>(elem<B32>(p, 2 * cs + j0));
-        a = v3{x.x, y.x, z.x};
-        b = v3{x.y, y.y, z.y};
-    }
-    // The same pair split into the memory access and the decoding, so that a
-    // load can be issued a step before its value is used.
+    // A pair, split into the memory access and the decoding, so that a load can be
+    // issued a step before its value is used; 32-bit offsets (3 Nh < 2^32 for
+    // L <= 1024), with B32 in bytes.
     struct R {
-        float2 x, y, z;
+        float4 xy;
+        float2 z;
     };
     template <bool B32 = false>
     __device__ static __forceinline__ void load_raw_pair(const T *p, uint32_t cs, uint32_t j0, R &r)
     {
-        r.x = *reinterpret_cast<const float2 *>(elem<B32>(p, j0));
-        r.y = *reinterpret_cast<const float2 *>(elem<B32>(p, cs + j0));
+        r.xy = *reinterpret_cast<const float4 *>(elem<B32>(p, 2 * j0));
         r.z = *reinterpret_cast<const float2 *>(elem<B32>(p, 2 * cs + j0));
     }
     __device__ static __forceinline__ void decode_pair(const R &r, v3 &a, v3 &b)
     {
-        a = v3{r.x.x, r.y.x, r.z.x};
-        b = v3{r.x.y, r.y.y, r.z.y};
+        a = v3{r.xy.x, r.xy.z, r.z.x};
+        b = v3{r.xy.y, r.xy.w, r.z.y};
     }
     // The codes of a pair, and their store: a stored value is decode_pair of
     // encode_pair, so a caller that stores and reads back encodes once.
     __device__ static __forceinline__ R encode_pair(v3 a, v3 b)
     {
-        return R{make_float2(a.x, b.x), make_float2(a.y, b.y), make_float2(a.z, b.z)};
+        return R{make_float4(a.x, b.x, a.y, b.y), make_float2(a.z, b.z)};
     }
     template <bool B32 = false>
     __device__ static __forceinline__ void store_raw_pair(T *p, uint32_t cs, uint32_t j0, const R &r)
     {
-        *reinterpret_cast<float2 *>(elem<B32>(p, j0)) = r.x;
-        *reinterpret_cast<float2 *>(elem<B32>(p, cs + j0)) = r.y;
+        *reinterpret_cast<float4 *>(elem<B32>(p, 2 * j0)) = r.xy;
         *reinterpret_cast<float2 *>(elem<B32>(p, 2 * cs + j0)) = r.z;
+    }
+    template <bool B32 = false>
+    __device__ static __forceinline__ void load_pair(const T *p, uint32_t cs, uint32_t j0, v3 &a, v3 &b)
+    {
+        R r;
+        load_raw_pair<B32>(p, cs, j0, r);
+        decode_pair(r, a, b);
     }
     template <bool B32 = false>
     __device__ static __forceinline__ void store_pair(T *p, uint32_t cs, uint32_t j0, v3 a, v3 b)
@@ -446,73 +452,79 @@ struct Codec<0> {  // float32: stored renormalised, read as is
     }
 };
 
+// Three words of a 16-bit pair, 4-byte aligned: one 12-byte access.
+typedef uint32_t hsg_u32x3 __attribute__((ext_vector_type(3), aligned(4)));
+
 template <>
 struct Codec<1> {  // float16 components (round to nearest even), renormalised on load
     using T = __half;
     static constexpr int kPlanes = 3;
-    __device__ static __forceinline__ v3 load(const T *p, int64_t cs, int64_t j)
+    __device__ static __forceinline__ v3 load(const T *p, int64_t, int64_t j)
     {
-        return normalise_rsq(v3{__half2float(p[j]), __half2float(p[cs + j]), __half2float(p[2 * cs + j])});
+        const T *q = p + 6 * (j >> 1) + (j & 1);
+        return normalise_rsq(v3{__half2float(q[0]), __half2float(q[2]), __half2float(q[4])});
     }
-    __device__ static __forceinline__ v3 load32(const T *p, uint32_t cs, uint32_t j)
+    __device__ static __forceinline__ v3 load32(const T *p, uint32_t, uint32_t at, uint32_t j)
     {
-        return normalise_rsq(v3{__half2float(*elem<true>(p, j)), __half2float(*elem<true>(p, cs + j)),
-                                __half2float(*elem<true>(p, 2 * cs + j))});
+        const uint32_t q = at + 6 * (j >> 1) + (j & 1);
+        return normalise_rsq(v3{__half2float(*elem<true>(p, q)), __half2float(*elem<true>(p, q + 2)),
+                                __half2float(*elem<true>(p, q + 4))});
     }
-    __device__ static __forceinline__ void store(T *p, int64_t cs, int64_t j, v3 s)
+    __device__ static __forceinline__ void store(T *p, int64_t, int64_t j, v3 s)
     {
-        p[j] = __float2half_rn(s.x);
-        p[cs + j] = __float2half_rn(s.y);
-        p[2 * cs + j] = __float2half_rn(s.z);
+        T *q = p + 6 * (j >> 1) + (j & 1);
+        q[0] = __float2half_rn(s.x);
+        q[2] = __float2half_rn(s.y);
+        q[4] = __float2half_rn(s.z);
     }
     __device__ static __forceinline__ v3 stored_value(v3 s)
     {
         return normalise_rsq(v3{__half2float(__float2half_rn(s.x)), __half2float(__float2half_rn(s.y)),
                                 __half2float(__float2half_rn(s.z))});
     }
+    using R = hsg_u32x3;
+    __device__ static __forceinline__ __half2 h2(uint32_t w) { return __builtin_bit_cast(__half2, w); }
     template <bool B32 = false>
-    __device__ static __forceinline__ void load_pair(const T *p, uint32_t cs, uint32_t j0, v3 &a, v3 &b)
+    __device__ static __forceinline__ void load_raw_pair(const T *p, uint32_t, uint32_t j0, R &r)
     {
-        const __half2 x = *reinterpret_cast<const __half2 *>(elem<B32>(p, j0));
-        const __half2 y = *reinterpret_cast<const __half2 *>(elem<B32>(p, cs + j0));
-        const __half2 z = *reinterpret_cast<const __half2 *>(elem<B32>(p, 2 * cs + j0));
-        a = normalise_rsq(v3{__low2float(x), __low2float(y), __low2float(z)});
-        b = normalise_rsq(v3{__high2float(x), __high2float(y), __high2float(z)});
+        r = *reinterpret_cast<const hsg_u32x3 *>(elem<B32>(p, 3 * j0));
     }
-    struct R {
-        __half2 x, y, z;
-    };
-    template <bool B32 = false>
-    __device__ static __forceinline__ void load_raw_pair(const T *p, uint32_t cs, uint32_t j0, R &r)
+    // the components as stored (not renormalised)
+    __device__ static __forceinline__ void components(const R &r, v3 &a, v3 &b)
     {
-        r.x = *reinterpret_cast<const __half2 *>(elem<B32>(p, j0));
-        r.y = *reinterpret_cast<const __half2 *>(elem<B32>(p, cs + j0));
-        r.z = *reinterpret_cast<const __half2 *>(elem<B32>(p, 2 * cs + j0));
+        a = v3{__low2float(h2(r.x)), __low2float(h2(r.y)), __low2float(h2(r.z))};
+        b = v3{__high2float(h2(r.x)), __high2float(h2(r.y)), __high2float(h2(r.z))};
     }
     __device__ static __forceinline__ void decode_pair(const R &r, v3 &a, v3 &b)
     {
-        a = normalise_rsq(v3{__low2float(r.x), __low2float(r.y), __low2float(r.z)});
-        b = normalise_rsq(v3{__high2float(r.x), __high2float(r.y), __high2float(r.z)});
+        components(r, a, b);
+        a = normalise_rsq(a);
+        b = normalise_rsq(b);
     }
     // Each value by the scalar conversion: the compiler would otherwise pair
     // two of them into gfx950's packed conversion, which rounds results in
     // float16's subnormal range differently (the empty asm keeps them apart).
-    __device__ static __forceinline__ __half2 pack(float lo, float hi)
+    __device__ static __forceinline__ uint32_t pack(float lo, float hi)
     {
         __half l = __float2half_rn(lo);
         asm volatile("" : "+v"(l));
-        return __halves2half2(l, __float2half_rn(hi));
+        return __builtin_bit_cast(uint32_t, __halves2half2(l, __float2half_rn(hi)));
     }
     __device__ static __forceinline__ R encode_pair(v3 a, v3 b)
     {
         return R{pack(a.x, b.x), pack(a.y, b.y), pack(a.z, b.z)};
     }
     template <bool B32 = false>
-    __device__ static __forceinline__ void store_raw_pair(T *p, uint32_t cs, uint32_t j0, const R &r)
+    __device__ static __forceinline__ void store_raw_pair(T *p, uint32_t, uint32_t j0, const R &r)
     {
-        *reinterpret_cast<__half2 *>(elem<B32>(p, j0)) = r.x;
-        *reinterpret_cast<__half2 *>(elem<B32>(p, cs + j0)) = r.y;
-        *reinterpret_cast<__half2 *>(elem<B32>(p, 2 * cs + j0)) = r.z;
+        *reinterpret_cast<hsg_u32x3 *>(elem<B32>(p, 3 * j0)) = r;
+    }
+    template <bool B32 = false>
+    __device__ static __forceinline__ void load_pair(const T *p, uint32_t cs, uint32_t j0, v3 &a, v3 &b)
+    {
+        R r;
+        load_raw_pair<B32>(p, cs, j0, r);
+        decode_pair(r, a, b);
     }
     template <bool B32 = false>
     __device__ static __forceinline__ void store_pair(T *p, uint32_t cs, uint32_t j0, v3 a, v3 b)
@@ -539,20 +551,23 @@ template <>
 struct Codec<2> {  // bfloat16 components, renormalised on load
     using T = uint16_t;
     static constexpr int kPlanes = 3;
-    __device__ static __forceinline__ v3 load(const T *p, int64_t cs, int64_t j)
+    __device__ static __forceinline__ v3 load(const T *p, int64_t, int64_t j)
     {
-        return normalise_rsq(v3{bf16_to_f32(p[j]), bf16_to_f32(p[cs + j]), bf16_to_f32(p[2 * cs + j])});
+        const T *q = p + 6 * (j >> 1) + (j & 1);
+        return normalise_rsq(v3{bf16_to_f32(q[0]), bf16_to_f32(q[2]), bf16_to_f32(q[4])});
     }
-    __device__ static __forceinline__ v3 load32(const T *p, uint32_t cs, uint32_t j)
+    __device__ static __forceinline__ v3 load32(const T *p, uint32_t, uint32_t at, uint32_t j)
     {
-        return normalise_rsq(v3{bf16_to_f32(*elem<true>(p, j)), bf16_to_f32(*elem<true>(p, cs + j)),
-                                bf16_to_f32(*elem<true>(p, 2 * cs + j))});
+        const uint32_t q = at + 6 * (j >> 1) + (j & 1);
+        return normalise_rsq(v3{bf16_to_f32(*elem<true>(p, q)), bf16_to_f32(*elem<true>(p, q + 2)),
+                                bf16_to_f32(*elem<true>(p, q + 4))});
     }
-    __device__ static __forceinline__ void store(T *p, int64_t cs, int64_t j, v3 s)
+    __device__ static __forceinline__ void store(T *p, int64_t, int64_t j, v3 s)
     {
-        p[j] = f32_to_bf16_rne(s.x);
-        p[cs + j] = f32_to_bf16_rne(s.y);
-        p[2 * cs + j] = f32_to_bf16_rne(s.z);
+        T *q = p + 6 * (j >> 1) + (j & 1);
+        q[0] = f32_to_bf16_rne(s.x);
+        q[2] = f32_to_bf16_rne(s.y);
+        q[4] = f32_to_bf16_rne(s.z);
     }
     __device__ static __forceinline__ v3 stored_value(v3 s)
     {
@@ -560,42 +575,39 @@ struct Codec<2> {  // bfloat16 components, renormalised on load
         return normalise_rsq(v3{__uint_as_float(xy << 16), __uint_as_float(xy & 0xFFFF0000u),
                                 bf16_to_f32(f32_to_bf16_rne(s.z))});
     }
+    using R = hsg_u32x3;
     template <bool B32 = false>
-    __device__ static __forceinline__ void load_pair(const T *p, uint32_t cs, uint32_t j0, v3 &a, v3 &b)
+    __device__ static __forceinline__ void load_raw_pair(const T *p, uint32_t, uint32_t j0, R &r)
     {
-        const uint32_t x = *reinterpret_cast<const uint32_t *>(elem<B32>(p, j0));
-        const uint32_t y = *reinterpret_cast<const uint32_t *>(elem<B32>(p, cs + j0));
-        const uint32_t z = *reinterpret_cast<const uint32_t *>(elem<B32>(p, 2 * cs + j0));
-        a = normalise_rsq(v3{__uint_as_float(x << 16), __uint_as_float(y << 16), __uint_as_float(z << 16)});
-        b = normalise_rsq(v3{__uint_as_float(x & 0xFFFF0000u), __uint_as_float(y & 0xFFFF0000u),
-                             __uint_as_float(z & 0xFFFF0000u)});
+        r = *reinterpret_cast<const hsg_u32x3 *>(elem<B32>(p, 3 * j0));
     }
-    struct R {
-        uint32_t x, y, z;
-    };
-    template <bool B32 = false>
-    __device__ static __forceinline__ void load_raw_pair(const T *p, uint32_t cs, uint32_t j0, R &r)
+    __device__ static __forceinline__ void components(const R &r, v3 &a, v3 &b)
     {
-        r.x = *reinterpret_cast<const uint32_t *>(elem<B32>(p, j0));
-        r.y = *reinterpret_cast<const uint32_t *>(elem<B32>(p, cs + j0));
-        r.z = *reinterpret_cast<const uint32_t *>(elem<B32>(p, 2 * cs + j0));
+        a = v3{__uint_as_float(r.x << 16), __uint_as_float(r.y << 16), __uint_as_float(r.z << 16)};
+        b = v3{__uint_as_float(r.x & 0xFFFF0000u), __uint_as_float(r.y & 0xFFFF0000u),
+               __uint_as_float(r.z & 0xFFFF0000u)};
     }
     __device__ static __forceinline__ void decode_pair(const R &r, v3 &a, v3 &b)
     {
-        a = normalise_rsq(v3{__uint_as_float(r.x << 16), __uint_as_float(r.y << 16), __uint_as_float(r.z << 16)});
-        b = normalise_rsq(v3{__uint_as_float(r.x & 0xFFFF0000u), __uint_as_float(r.y & 0xFFFF0000u),
-                             __uint_as_float(r.z & 0xFFFF0000u)});
+        components(r, a, b);
+        a = normalise_rsq(a);
+        b = normalise_rsq(b);
     }
     __device__ static __forceinline__ R encode_pair(v3 a, v3 b)
     {
         return R{bf16x2_rne(a.x, b.x), bf16x2_rne(a.y, b.y), bf16x2_rne(a.z, b.z)};
     }
     template <bool B32 = false>
-    __device__ static __forceinline__ void store_raw_pair(T *p, uint32_t cs, uint32_t j0, const R &r)
+    __device__ static __forceinline__ void store_raw_pair(T *p, uint32_t, uint32_t j0, const R &r)
     {
-        *reinterpret_cast<uint32_t *>(elem<B32>(p, j0)) = r.x;
-        *reinterpret_cast<uint32_t *>(elem<B32>(p, cs + j0)) = r.y;
-        *reinterpret_cast<uint32_t *>(elem<B32>(p, 2 * cs + j0)) = r.z;
+        *reinterpret_cast<hsg_u32x3 *>(elem<B32>(p, 3 * j0)) = r;
+    }
+    template <bool B32 = false>
+    __device__ static __forceinline__ void load_pair(const T *p, uint32_t cs, uint32_t j0, v3 &a, v3 &b)
+    {
+        R r;
+        load_raw_pair<B32>(p, cs, j0, r);
+        decode_pair(r, a, b);
     }
     template <bool B32 = false>
     __device__ static __forceinline__ void store_pair(T *p, uint32_t cs, uint32_t j0, v3 a, v3 b)
@@ -649,7 +661,10 @@ struct Codec<3> {
     using T = uint32_t;
     static constexpr int kPlanes = 1;
     __device__ static __forceinline__ v3 load(const T *p, int64_t, int64_t j) { return oct_decode(p[j]); }
-    __device__ static __forceinline__ v3 load32(const T *p, uint32_t, uint32_t j) { return oct_decode(*elem<true>(p, j)); }
+    __device__ static __forceinline__ v3 load32(const T *p, uint32_t, uint32_t at, uint32_t j)
+    {
+        return oct_decode(*elem<true>(p, at + j));
+    }
     __device__ static __forceinline__ void store(T *p, int64_t, int64_t j, v3 s) { p[j] = oct_encode(s); }
     __device__ static __forceinline__ v3 stored_value(v3 s) { return oct_decode(oct_encode(s)); }
     template <bool B32 = false>

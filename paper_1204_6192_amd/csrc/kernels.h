@@ -9,9 +9,9 @@ namespace hsg {
 constexpr int kBlock = 256;  // work-group size of the sweep and reduction kernels (4 waves)
 
 // Internal layouts (per group; d = sample, r = replica in canonical order):
-//   spins  [r][parity][3][Nh]      storage type per codec, Nh = L^3 / 2,
-//                                  element j of parity p = canonical site i with
-//                                  parity(i) = p and i >> 1 = j
+//   spins  [r][parity][3 Nh]       storage type per codec, Nh = L^3 / 2, placed as the
+//                                  codec does (device.h); site j of parity p =
+//                                  canonical site i with parity(i) = p and i >> 1 = j
 //   J6     [d][parity][6 Nh]       float32, the six couplings of each site (neighbour
 //                                  order +x, -x, +y, -y, +z, -z) as coupling_at places
 //                                  them: three float4 per pair of sites

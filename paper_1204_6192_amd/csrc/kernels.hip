@@ -227,37 +227,83 @@ __device__ __forceinline__ int64_t index_of(int32_t x, int32_t y, int32_t z, int
     return (int64_t)x + (int64_t)L * ((int64_t)y + (int64_t)L * z);
 }
 
-template <int STORE>
+// Four consecutive canonical sites 4 b .. 4 b + 3 are the pair of half-indices
+// (2 b, 2 b + 1) of both parities; which site of a half-index is even changes with
+// the row (a pair may straddle rows where L % 4 = 2). One thread per four sites:
+// with aligned canonical arrays (WIDE) three 16-byte accesses there and one or two
+// per parity, instead of one per component and site.
+template <bool WIDE>
+__device__ __forceinline__ void canonical4(const float *p, float (&v)[4])
+{
+    if constexpr (WIDE) {
+        const float4 q = *reinterpret_cast<const float4 *>(p);
+        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = p[k];
+    }
+}
+
+template <bool WIDE>
+__device__ __forceinline__ void to_canonical4(float *p, const float (&v)[4])
+{
+    if constexpr (WIDE) {
+        *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) p[k] = v[k];
+    }
+}
+
+// 1 where the first site of half-index j is odd
+__device__ __forceinline__ int first_odd(int64_t j, int32_t L)
+{
+    const Site c = site_of(2 * j, L);
+    return (c.y + c.z) & 1;
+}
+
+template <int STORE, bool WIDE>
 __global__ __launch_bounds__(256) void k_pack_spins(PackArgs a)
 {
     using C = Codec<STORE>;
     const int64_t N = (int64_t)a.L * a.L * a.L, Nh = N / 2;
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= a.n_rep * N) return;
-    const int64_t rep = gid / N, i = gid - rep * N;
-    const Site c = site_of(i, a.L);
-    const int p = (c.x + c.y + c.z) & 1;
-    const float *src = a.spins_can + rep * 3 * N;
-    typename C::T *dst = (typename C::T *)a.spins_int + (rep * 2 + p) * C::kPlanes * Nh;
-    C::store(dst, Nh, i >> 1, v3{src[i], src[N + i], src[2 * N + i]});
+    if (gid >= a.n_rep * (N / 4)) return;
+    const int64_t rep = gid / (N / 4), b = gid - rep * (N / 4);
+    const float *src = a.spins_can + rep * 3 * N + 4 * b;
+    float x[4], y[4], z[4];
+    canonical4<WIDE>(src, x);
+    canonical4<WIDE>(src + N, y);
+    canonical4<WIDE>(src + 2 * N, z);
+    const int o0 = first_odd(2 * b, a.L), o1 = first_odd(2 * b + 1, a.L);
+    typename C::T *dst = (typename C::T *)a.spins_int + rep * 2 * C::kPlanes * Nh;
+    auto site = [&](int k, int other) {
+        return other ? v3{x[k + 1], y[k + 1], z[k + 1]} : v3{x[k], y[k], z[k]};
+    };
+    C::store_pair(dst, (uint32_t)Nh, (uint32_t)(2 * b), site(0, o0), site(2, o1));
+    C::store_pair(dst + C::kPlanes * Nh, (uint32_t)Nh, (uint32_t)(2 * b), site(0, 1 - o0), site(2, 1 - o1));
 }
 
-template <int STORE>
+template <int STORE, bool WIDE>
 __global__ __launch_bounds__(256) void k_unpack_spins(PackArgs a)
 {
     using C = Codec<STORE>;
     const int64_t N = (int64_t)a.L * a.L * a.L, Nh = N / 2;
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= a.n_rep * N) return;
-    const int64_t rep = gid / N, i = gid - rep * N;
-    const Site c = site_of(i, a.L);
-    const int p = (c.x + c.y + c.z) & 1;
-    const typename C::T *src = (const typename C::T *)a.spins_int + (rep * 2 + p) * C::kPlanes * Nh;
-    const v3 s = C::load(src, Nh, i >> 1);
-    float *dst = a.spins_can + rep * 3 * N;
-    dst[i] = s.x;
-    dst[N + i] = s.y;
-    dst[2 * N + i] = s.z;
+    if (gid >= a.n_rep * (N / 4)) return;
+    const int64_t rep = gid / (N / 4), b = gid - rep * (N / 4);
+    const typename C::T *src = (const typename C::T *)a.spins_int + rep * 2 * C::kPlanes * Nh;
+    v3 e0, e1, f0, f1;  // the pair on parity 0 and on parity 1
+    C::load_pair(src, (uint32_t)Nh, (uint32_t)(2 * b), e0, e1);
+    C::load_pair(src + C::kPlanes * Nh, (uint32_t)Nh, (uint32_t)(2 * b), f0, f1);
+    const int o0 = first_odd(2 * b, a.L), o1 = first_odd(2 * b + 1, a.L);
+    const v3 s[4] = {o0 ? f0 : e0, o0 ? e0 : f0, o1 ? f1 : e1, o1 ? e1 : f1};
+    float *dst = a.spins_can + rep * 3 * N + 4 * b;
+    const float x[4] = {s[0].x, s[1].x, s[2].x, s[3].x}, y[4] = {s[0].y, s[1].y, s[2].y, s[3].y},
+                z[4] = {s[0].z, s[1].z, s[2].z, s[3].z};
+    to_canonical4<WIDE>(dst, x);
+    to_canonical4<WIDE>(dst + N, y);
+    to_canonical4<WIDE>(dst + 2 * N, z);
 }
 
 __global__ __launch_bounds__(256) void k_pack_couplings(PackArgs a)
@@ -344,29 +390,43 @@ hipError_t launch_pack_jbits(const float *J_can, uint8_t *Jbits, int64_t D, int3
 
 hipError_t launch_pack_spins(const PackArgs &a, int storage, hipStream_t s)
 {
-    const int64_t n = a.n_rep * (int64_t)a.L * a.L * a.L;
+    const int64_t n = a.n_rep * ((int64_t)a.L * a.L * a.L / 4);
     if (n == 0) return hipSuccess;
+    const bool wide = (reinterpret_cast<uintptr_t>(a.spins_can) & 15) == 0;
+#define HSG_C(S)                                                                                    \
+    do {                                                                                            \
+        if (wide) hipLaunchKernelGGL((k_pack_spins<S, true>), dim3(blocks_for(n)), dim3(256), 0, s, a); \
+        else hipLaunchKernelGGL((k_pack_spins<S, false>), dim3(blocks_for(n)), dim3(256), 0, s, a);     \
+    } while (0)
     switch (storage) {
-    case 0: hipLaunchKernelGGL(k_pack_spins<0>, dim3(blocks_for(n)), dim3(256), 0, s, a); break;
-    case 1: hipLaunchKernelGGL(k_pack_spins<1>, dim3(blocks_for(n)), dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL(k_pack_spins<2>, dim3(blocks_for(n)), dim3(256), 0, s, a); break;
-    case 3: hipLaunchKernelGGL(k_pack_spins<3>, dim3(blocks_for(n)), dim3(256), 0, s, a); break;
+    case 0: HSG_C(0); break;
+    case 1: HSG_C(1); break;
+    case 2: HSG_C(2); break;
+    case 3: HSG_C(3); break;
     default: return hipErrorInvalidValue;
     }
+#undef HSG_C
     return hipGetLastError();
 }
 
 hipError_t launch_unpack_spins(const PackArgs &a, int storage, hipStream_t s)
 {
-    const int64_t n = a.n_rep * (int64_t)a.L * a.L * a.L;
+    const int64_t n = a.n_rep * ((int64_t)a.L * a.L * a.L / 4);
     if (n == 0) return hipSuccess;
+    const bool wide = (reinterpret_cast<uintptr_t>(a.spins_can) & 15) == 0;
+#define HSG_C(S)                                                                                      \
+    do {                                                                                              \
+        if (wide) hipLaunchKernelGGL((k_unpack_spins<S, true>), dim3(blocks_for(n)), dim3(256), 0, s, a); \
+        else hipLaunchKernelGGL((k_unpack_spins<S, false>), dim3(blocks_for(n)), dim3(256), 0, s, a);     \
+    } while (0)
     switch (storage) {
-    case 0: hipLaunchKernelGGL(k_unpack_spins<0>, dim3(blocks_for(n)), dim3(256), 0, s, a); break;
-    case 1: hipLaunchKernelGGL(k_unpack_spins<1>, dim3(blocks_for(n)), dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL(k_unpack_spins<2>, dim3(blocks_for(n)), dim3(256), 0, s, a); break;
-    case 3: hipLaunchKernelGGL(k_unpack_spins<3>, dim3(blocks_for(n)), dim3(256), 0, s, a); break;
+    case 0: HSG_C(0); break;
+    case 1: HSG_C(1); break;
+    case 2: HSG_C(2); break;
+    case 3: HSG_C(3); break;
     default: return hipErrorInvalidValue;
     }
+#undef HSG_C
     return hipGetLastError();
 }
 
@@ -801,7 +861,7 @@ __device__ __forceinline__ v3 load_site(const typename Codec<STORE>::T *rep, int
     const uint32_t p = (x + y + z) & 1u;
     const uint32_t j = (z * L + y) * (L >> 1) + (x >> 1);
     if constexpr (B32)
-        return Codec<STORE>::load32(rep, (uint32_t)Nh, (p ? (uint32_t)Codec<STORE>::kPlanes * (uint32_t)Nh : 0u) + j);
+        return Codec<STORE>::load32(rep, (uint32_t)Nh, p ? (uint32_t)Codec<STORE>::kPlanes * (uint32_t)Nh : 0u, j);
     else
         return Codec<STORE>::load(rep + (p ? (int64_t)Codec<STORE>::kPlanes * Nh : 0), Nh, (int64_t)j);
 }

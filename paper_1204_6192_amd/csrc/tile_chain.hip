@@ -59,18 +59,10 @@ template <int STORE>
 __device__ __forceinline__ void load_raw_pair(const typename Codec<STORE>::T *p, uint32_t cs, uint32_t j0, v3 &a,
                                               v3 &b)
 {
-    if constexpr (STORE == 1) {
-        const __half2 x = *reinterpret_cast<const __half2 *>(p + j0);
-        const __half2 y = *reinterpret_cast<const __half2 *>(p + cs + j0);
-        const __half2 z = *reinterpret_cast<const __half2 *>(p + 2 * cs + j0);
-        a = v3{__low2float(x), __low2float(y), __low2float(z)};
-        b = v3{__high2float(x), __high2float(y), __high2float(z)};
-    } else if constexpr (STORE == 2) {
-        const uint32_t x = *reinterpret_cast<const uint32_t *>(p + j0);
-        const uint32_t y = *reinterpret_cast<const uint32_t *>(p + cs + j0);
-        const uint32_t z = *reinterpret_cast<const uint32_t *>(p + 2 * cs + j0);
-        a = v3{__uint_as_float(x << 16), __uint_as_float(y << 16), __uint_as_float(z << 16)};
-        b = v3{__uint_as_float(x & 0xFFFF0000u), __uint_as_float(y & 0xFFFF0000u), __uint_as_float(z & 0xFFFF0000u)};
+    if constexpr (STORE == 1 || STORE == 2) {
+        typename Codec<STORE>::R r;
+        Codec<STORE>::load_raw_pair(p, cs, j0, r);
+        Codec<STORE>::components(r, a, b);
     } else {
         Codec<STORE>::load_pair(p, cs, j0, a, b);
     }
