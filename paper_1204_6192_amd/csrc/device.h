@@ -390,8 +390,9 @@ struct Codec<0> {  // float32: stored renormalised, read as is
     static constexpr int kPlanes = 3;  // elements per site and parity
     __device__ static __forceinline__ v3 load(const T *p, int64_t cs, int64_t j)
     {
-        const T *q = p + 4 * (j >> 1) + (j & 1);
-        return v3{q[0], q[2], p[2 * cs + j]};
+        // two loads, not three: a load's cost does not depend on its width
+        const float4 xy = *reinterpret_cast<const float4 *>(p + 4 * (j >> 1));
+        return (j & 1) ? v3{xy.y, xy.w, p[2 * cs + j]} : v3{xy.x, xy.z, p[2 * cs + j]};
     }
     // site j of the array at element `at` of the base, with 32-bit byte offsets from
     // that (uniform) base (everything within 4 GiB of it)
@@ -461,8 +462,9 @@ struct Codec<1> {  // float16 components (round to nearest even), renormalised o
     static constexpr int kPlanes = 3;
     __device__ static __forceinline__ v3 load(const T *p, int64_t, int64_t j)
     {
-        const T *q = p + 6 * (j >> 1) + (j & 1);
-        return normalise_rsq(v3{__half2float(q[0]), __half2float(q[2]), __half2float(q[4])});
+        v3 a, b;
+        components(*reinterpret_cast<const R *>(p + 6 * (j >> 1)), a, b);
+        return normalise_rsq((j & 1) ? b : a);
     }
     __device__ static __forceinline__ v3 load32(const T *p, uint32_t, uint32_t at, uint32_t j)
     {
@@ -553,8 +555,9 @@ struct Codec<2> {  // bfloat16 components, renormalised on load
     static constexpr int kPlanes = 3;
     __device__ static __forceinline__ v3 load(const T *p, int64_t, int64_t j)
     {
-        const T *q = p + 6 * (j >> 1) + (j & 1);
-        return normalise_rsq(v3{bf16_to_f32(q[0]), bf16_to_f32(q[2]), bf16_to_f32(q[4])});
+        v3 a, b;
+        components(*reinterpret_cast<const R *>(p + 6 * (j >> 1)), a, b);
+        return normalise_rsq((j & 1) ? b : a);
     }
     __device__ static __forceinline__ v3 load32(const T *p, uint32_t, uint32_t at, uint32_t j)
     {

@@ -42,6 +42,13 @@ __device__ __forceinline__ void neighbours(int64_t j, int32_t L, int32_t Lh, int
 // share Philox block q) and walks `chunk` replicas of one sample, keeping the
 // sample's couplings and field in registers. Grid: samples x replica chunks x
 // blocks of 256 site pairs, remapped so each XCD gets contiguous work.
+// Bound by the number of vector loads, not by their width: the pair's own spins,
+// the ones beside it at the same half-index (one of each site's two x neighbours)
+// and the planes above and below come as pairs, whatever L is (a plane holds an
+// even number of sites per parity), and only the other x neighbour and the two y
+// neighbours site by site. Against loads of single components: an over-relaxation
+// pair of 512 replicas of L = 30 in float32 273 -> 171 us, of 32 replicas 25 -> 17;
+// bfloat16 186 -> 116 and 19 -> 13.
 template <int STORE, int KIND, bool FIELD, bool ENERGY>
 __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
 {
@@ -59,7 +66,9 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
     const bool active = q < (Nh >> 1);
     const int p = (int)a.parity;
 
-    int64_t nb[2][6];
+    int64_t zp = 0, zm = 0;       // the pairs above and below
+    int64_t xo[2], yp[2], ym[2];  // per site: the x neighbour at another half-index, y neighbours
+    bool plus[2];                 // that x neighbour is the one at x + 1
     float Jc[2][6];
     v3 Hs[2] = {v3{0.f, 0.f, 0.f}, v3{0.f, 0.f, 0.f}};
     v3 He[2] = {v3{0.f, 0.f, 0.f}, v3{0.f, 0.f, 0.f}};
@@ -67,7 +76,16 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int64_t j = 2 * q + k;
-            neighbours(j, a.L, a.Lh, p, nb[k]);
+            int64_t nb[6];
+            neighbours(j, a.L, a.Lh, p, nb);
+            plus[k] = nb[0] != j;
+            xo[k] = plus[k] ? nb[0] : nb[1];
+            yp[k] = nb[2];
+            ym[k] = nb[3];
+            if (k == 0) {
+                zp = nb[4];
+                zm = nb[5];
+            }
             const float *Jb = a.J6 + ((int64_t)d * 2 + p) * 6 * Nh;
 #pragma unroll
             for (int n = 0; n < 6; ++n) Jc[k][n] = Jb[coupling_at(n, j, Nh)];
@@ -100,37 +118,41 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
                 const uint32_t c2 = (uint32_t)ts | ((uint32_t)o << 8) | (a.rep << 12) | ((uint32_t)p << 16);
                 r = philox4x32_10(u32x4{(uint32_t)q, tsweep, c2, a.uid_base + (uint32_t)d}, a.key0, a.key1);
             }
+            const uint32_t cs32 = (uint32_t)Nh, j0 = (uint32_t)(2 * q);
+            v3 same[2], up[2], dn[2], s1[2];
+            C::load_pair(oth, cs32, j0, same[0], same[1]);
+            C::load_pair(oth, cs32, (uint32_t)zp, up[0], up[1]);
+            C::load_pair(oth, cs32, (uint32_t)zm, dn[0], dn[1]);
+            if (KIND == 1) C::load_pair(own, cs32, j0, s1[0], s1[1]);
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-                const int64_t j = 2 * q + k;
+                const v3 x = C::load(oth, Nh, xo[k]);
+                const v3 sn[6] = {plus[k] ? x : same[k], plus[k] ? same[k] : x, C::load(oth, Nh, yp[k]),
+                                  C::load(oth, Nh, ym[k]), up[k], dn[k]};
                 v3 h = Hs[k];
                 double hx = Hs[k].x, hy = Hs[k].y, hz = Hs[k].z;
 #pragma unroll
                 for (int n = 0; n < 6; ++n) {
-                    const v3 sn = C::load(oth, Nh, nb[k][n]);
-                    acc3(h, Jc[k][n], sn);
+                    acc3(h, Jc[k][n], sn[n]);
                     if (ENERGY) {
-                        hx = fma((double)Jc[k][n], (double)sn.x, hx);
-                        hy = fma((double)Jc[k][n], (double)sn.y, hy);
-                        hz = fma((double)Jc[k][n], (double)sn.z, hz);
+                        hx = fma((double)Jc[k][n], (double)sn[n].x, hx);
+                        hy = fma((double)Jc[k][n], (double)sn[n].y, hy);
+                        hz = fma((double)Jc[k][n], (double)sn[n].z, hz);
                     }
                 }
-                v3 s1;
                 if (KIND != 1)
-                    s1 = heat_bath<KIND == 2, STORE == 0>(h, beta, k ? r.z : r.x, k ? r.w : r.y);
+                    s1[k] = heat_bath<KIND == 2, STORE == 0>(h, beta, k ? r.z : r.x, k ? r.w : r.y);
                 else
-                    s1 = over_relax<STORE == 0>(C::load(own, Nh, j), h);
-                C::store(own, Nh, j, s1);
+                    s1[k] = over_relax<STORE == 0>(s1[k], h);
                 if (ENERGY) {
                     // each bond has exactly one endpoint on this parity (the odd one)
-                    const v3 sv = C::stored_value(s1);
+                    const v3 sv = C::stored_value(s1[k]);
                     e -= (double)sv.x * hx + (double)sv.y * hy + (double)sv.z * hz;
-                    if (FIELD) {
-                        const v3 so = C::load(oth, Nh, j);
-                        e -= (double)He[k].x * so.x + (double)He[k].y * so.y + (double)He[k].z * so.z;
-                    }
+                    if (FIELD)
+                        e -= (double)He[k].x * same[k].x + (double)He[k].y * same[k].y + (double)He[k].z * same[k].z;
                 }
             }
+            C::store_pair(own, cs32, j0, s1[0], s1[1]);
         }
         if (ENERGY) {
             const double tot = block_sum(e, red);
