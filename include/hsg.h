@@ -287,14 +287,17 @@ hsg_status hsg_set_tuning(hsg_lattice *h, int32_t slots_per_item);
  * pair in one launch where the whole plane fits a work-group (L <= 32), else
  * as 2; 4 = as 3, and the over-relaxation pairs of a sweep two by two in one
  * launch (four half-sweeps per read and write of the spins) where eleven
- * staged planes fit the work-group's LDS; 5 = lattice sizes whose replica fits
+ * staged planes fit the work-group's LDS; from L = 24 on, where a replica's
+ * whole planes fit one work-group (L <= 64 for a pair, L <= 32 for two pairs, any
+ * even L) and there are replicas enough for the card, 4 takes them in one walk
+ * per replica; 5 = lattice sizes whose replica fits
  * a work-group's LDS (12 bytes per site: L <= 22 with 160 KiB; the paper's per-block shared-memory tiles, Sec. 3.1, taken to a whole
  * replica) run all half-sweeps and the energies of a sweep in one launch of
  * hsg_sweep, the spins staying in LDS; the other sizes, and the per-call entry
  * points, as 4; 0 = automatic (currently 5, with 3 in place of 4 for
  * quantised-angle storage, whose two-pair launch is slower than two fused
- * pairs). The energies computed by 5 equal the others' to rounding (another
- * summation order). */
+ * pairs, except in the walk by whole planes). The energies computed by 4 and 5
+ * equal the others' to rounding (another summation order). */
 hsg_status hsg_set_kernel(hsg_lattice *h, int32_t variant);
 
 /* Tuning (results do not depend on it): 1 = where every lattice size runs
@@ -383,7 +386,7 @@ hsg_status hsg_set_chain(hsg_lattice *h, int32_t chain, int32_t tile_x, int32_t 
  * runs single passes, one size after the other, the current geometry first
  * and replaced only by one at least 1 % faster (hsg_get_geometry reports the
  * result). Every variant computes the same spins and temperature maps bit
- * for bit (variant 5 the energies to rounding, another summation order), so
+ * for bit (variants 4 and 5 the energies to rounding, another summation order), so
  * the trial sweeps are ordinary sweeps of the chain: with
  * d_backup == NULL the chain advances by them (2 (n_sweeps + 10) per candidate);
  * with d_backup (device, state_bytes of hsg_query_sizes, 256-byte aligned,

@@ -539,6 +539,123 @@ hsg_status run_half_sweep(hsg_lattice *h, int kind, int parity, int rep, bool en
     return run_groups(h, kind, parity, rep, energy, 0, [](const Group &) { return true; }, s);
 }
 
+size_t plane_lds_bytes(const Group &g, int groups) { return (size_t)(groups == 1 ? 4 : 11) * 6 * g.L * g.L; }
+
+// One pair (groups = 1) or two over-relaxation pairs (groups = 2) in one walk of
+// whole planes (launch_plane_march), where a plane's site pairs fit the work-group
+// (1024 and 256 threads) and the staged planes its LDS, and where that is the faster
+// way for a launch of n replicas. A work-group walks one replica, so a launch of
+// fewer replicas than CUs takes as long as one of 256, and where a work-group has 9
+// to 16 waves a CU holds one: its time goes by rounds of 256. Measured in us, this
+// walk against the kernel that takes the work otherwise:
+//   L % 4 == 2, against gather passes (which split a replica over work-groups):
+//     two pairs L = 30: f32 32 replicas 48 : 33, 64 48 : 59, 256 54 : 176;
+//     bf16 64 49 : 38, 128 49 : 65. A pair L = 46: f32 64 87 : 79, 128 131 : 164;
+//     bf16 64 72 : 55, 128 73 : 91. Heat bath L = 30: 128 82 : 51, 256 85 : 89;
+//     L = 62: 256 410 : 757. With 256 + 44 replicas of L = 62 bf16 the second round
+//     is empty enough for 606 : 510.
+//   L <= 32, L % 4 == 0, against the fused marches, L = 32: heat bath 256 replicas
+//     84 : 109, 8192 1757 : 1804 (f32), 1451 : 1595 (bf16), but with a field
+//     2048 550 : 528. Two pairs f32 256 64 : 80, 1024 307 : 313, 8192 2373 : 2167
+//     (there the fused march keeps more bytes in flight); bf16 1024 226 : 260, 8192
+//     1724 : 1779; f16 with a field 2048 623 : 815. A pair 256 46 : 51, 2048
+//     507 : 486 (f32).
+//   L = 36 to 64, L % 4 == 0, against two single passes: a pair of L = 64 f32 96
+//     replicas 339 : 230, 192 379 : 495, 768 1489 : 1993; bf16 768 986 : 1258;
+//     L = 40 f32 192 89 : 114; with a field L = 64 f32 192 400 : 451, f16 574 : 547.
+//     Heat bath L = 64 f32 256 420 : 526, bf16 192 338 : 306, 768 1160 : 1198;
+//     L = 40 f32 768 350 : 424; L = 48 (9 waves, so 9 of a CU's 16) bf16 592 : 528.
+bool use_plane(const hsg_lattice *h, const Group &g, int kind, int groups, int64_t n)
+{
+    if ((h->kernel_variant != 0 && h->kernel_variant < 4) || g.L < 24) return false;
+    const int pp = (g.L / 2) * (g.L / 2), waves = (pp + 63) / 64;
+    if (pp > (groups == 1 ? 1024 : 256) || plane_lds_bytes(g, groups) + 256 > h->max_lds) return false;
+    const bool f32 = h->storage == HSG_STORE_F32;
+    const int64_t slots = 256 * ((n + 255) / 256);  // of whole rounds
+    if (!g.stream_ok) {
+        const int64_t least = kind == 0 ? 256 : f32 ? 96 : 128;
+        return n >= least && (waves <= 8 || n <= 256 || 4 * n >= 3 * slots);
+    }
+    if (g.L <= 32) {
+        if (groups == 2) return !f32 || n <= 1024;
+        return !g.field && (kind == 0 || n <= 512);
+    }
+    if (kind == 1) return (!g.field || f32) && (waves <= 8 ? n >= 192 : 4 * n >= 3 * slots);
+    return !g.field && (waves <= 8 || waves >= 13) && 20 * n >= 19 * slots;
+}
+
+// Replicas that choose the route of a pass over [r0, r1) (r1 < 0: all): the launch's,
+// but with energies the group's, so that batches and halves sum them in the same order
+// as the whole.
+int64_t route_count(const Group &g, bool energy, int64_t r0, int64_t r1)
+{
+    return energy || r1 < 0 ? g.n_rep : r1 - r0;
+}
+
+// groups = 1: a pair of half-sweeps of the given kind; 2: two over-relaxation pairs,
+// of the replicas [r0, r1) (r1 < 0: all) of the lattice sizes `pick` selects; with
+// energy into E.
+template <class Pick>
+hsg_status run_plane(hsg_lattice *h, int kind, int rep, int groups, bool energy, Pick pick, hipStream_t s, int64_t r0,
+                     int64_t r1)
+{
+    if (kind == 0 && h->hw_math) kind = 2;
+    hsg::MultiPlaneArgs m{};
+    int64_t blocks = 0;
+    unsigned threads = 0;
+    size_t lds = 0;
+    auto flush = [&]() -> hsg_status {
+        if (m.n_groups == 0) return HSG_OK;
+        m.block_start[m.n_groups] = (int32_t)blocks;
+        m.n_blocks = (int32_t)blocks;
+        const hipError_t e = hsg::launch_plane_march(m, h->storage, kind, groups, energy, threads, lds, s);
+        m = hsg::MultiPlaneArgs{};
+        blocks = 0;
+        threads = 0;
+        lds = 0;
+        if (e != hipSuccess) return hip_fail(e, "plane march launch");
+        return HSG_OK;
+    };
+    for (const Group &g : h->lay.g) {
+        if (!pick(g)) continue;
+        const int pp = (g.L / 2) * (g.L / 2), tpg = (pp + 63) / 64 * 64;
+        const int64_t nb = (r1 < 0 ? g.n_rep : r1) - r0;
+        if (nb > 0x7FFFFFFFll) return fail(HSG_E_SIZE, "grid too large");
+        // one launch per lattice size: the sizes differ in threads and LDS
+        if (m.n_groups == hsg::kMaxStreamGroups || (m.n_groups > 0 && (unsigned)(groups * tpg) != threads)) {
+            const hsg_status st = flush();
+            if (st != HSG_OK) return st;
+        }
+        hsg::PlaneArgs a{};
+        a.spins = h->state + g.o_spins;
+        a.J6 = reinterpret_cast<const float *>(h->coup + g.o_J6);
+        a.Jbits = g.ckind == 1 ? reinterpret_cast<const uint8_t *>(h->coup + g.o_Jbits) : nullptr;
+        a.Hp = g.field ? reinterpret_cast<const float *>(h->field + g.o_H) : nullptr;
+        a.temp_of_slot = reinterpret_cast<const int32_t *>(h->state + g.o_tos);
+        a.beta32 = reinterpret_cast<const float *>(h->coup + g.o_b32);
+        a.E = reinterpret_cast<double *>(h->state + g.o_E);
+        a.tptr = dev_counter(h);
+        a.Nh = g.Nh;
+        a.r_base = r0;
+        a.L = g.L;
+        a.Lh = g.L / 2;
+        a.pp = pp;
+        a.tpg = tpg;
+        a.slots_per_sample = g.O * g.T;
+        a.T = g.T;
+        a.rep = (uint32_t)rep;
+        a.key0 = (uint32_t)(h->seed & 0xFFFFFFFFu);
+        a.key1 = (uint32_t)(h->seed >> 32);
+        a.uid_base = g.uid_base;
+        m.block_start[m.n_groups] = (int32_t)blocks;
+        m.g[m.n_groups++] = a;
+        blocks += nb;
+        threads = std::max(threads, (unsigned)(groups * tpg));
+        lds = std::max(lds, plane_lds_bytes(g, groups));
+    }
+    return flush();
+}
+
 // A pair of half-sweeps (parity 0, then parity 1) of the groups `pick`
 // selects: fused where the group holds whole planes, as two single passes
 // otherwise. `energy`: the parity-1 pass computes the energies.
@@ -546,19 +663,25 @@ template <class Pick>
 hsg_status run_pair_of(hsg_lattice *h, int kind, int rep, bool energy, hipStream_t s, Pick pick, int64_t r0,
                        int64_t r1)
 {
-    bool any_pair = false, any_single = false;
+    bool any_pair = false, any_single = false, any_plane = false;
+    auto plane = [&](const Group &g) { return use_plane(h, g, kind, 1, route_count(g, energy, r0, r1)); };
     for (const Group &g : h->lay.g) {
         if (!pick(g)) continue;
-        any_pair = any_pair || use_pair(h, g);
-        any_single = any_single || !use_pair(h, g);
+        if (plane(g)) any_plane = true;
+        else if (use_pair(h, g)) any_pair = true;
+        else any_single = true;
+    }
+    if (any_plane) {
+        hsg_status st = run_plane(h, kind, rep, 1, energy, [&](const Group &g) { return pick(g) && plane(g); }, s, r0, r1);
+        if (st != HSG_OK) return st;
     }
     if (any_pair) {
-        auto fused = [h, &pick](const Group &g) { return pick(g) && use_pair(h, g); };
+        auto fused = [h, &pick, &plane](const Group &g) { return pick(g) && use_pair(h, g) && !plane(g); };
         hsg_status st = run_groups(h, kind, 0, rep, energy, 1, fused, s, r0, r1);
         if (st != HSG_OK) return st;
     }
     if (any_single) {
-        auto single = [h, &pick](const Group &g) { return pick(g) && !use_pair(h, g); };
+        auto single = [h, &pick, &plane](const Group &g) { return pick(g) && !use_pair(h, g) && !plane(g); };
         hsg_status st = run_groups(h, kind, 0, rep, false, 0, single, s, r0, r1);
         if (st == HSG_OK) st = run_groups(h, kind, 1, rep, energy, 0, single, s, r0, r1);
         if (st != HSG_OK) return st;
@@ -572,19 +695,25 @@ hsg_status run_pair_of(hsg_lattice *h, int kind, int rep, bool energy, hipStream
 template <class Pick>
 hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, Pick pick, int64_t r0, int64_t r1)
 {
-    bool any_quad = false, any_other = false;
+    bool any_quad = false, any_other = false, any_plane = false;
+    auto plane = [&](const Group &g) { return use_plane(h, g, 1, 2, route_count(g, energy, r0, r1)); };
     for (const Group &g : h->lay.g) {
         if (!pick(g)) continue;
-        any_quad = any_quad || use_quad(h, g);
-        any_other = any_other || !use_quad(h, g);
+        if (plane(g)) any_plane = true;
+        else if (use_quad(h, g)) any_quad = true;
+        else any_other = true;
+    }
+    if (any_plane) {
+        hsg_status st = run_plane(h, 1, 0, 2, energy, [&](const Group &g) { return pick(g) && plane(g); }, s, r0, r1);
+        if (st != HSG_OK) return st;
     }
     if (any_quad) {
-        auto quad = [h, &pick](const Group &g) { return pick(g) && use_quad(h, g); };
+        auto quad = [h, &pick, &plane](const Group &g) { return pick(g) && use_quad(h, g) && !plane(g); };
         hsg_status st = run_groups(h, 1, 0, 0, energy, 2, quad, s, r0, r1);
         if (st != HSG_OK) return st;
     }
     if (any_other) {
-        auto other = [h, &pick](const Group &g) { return pick(g) && !use_quad(h, g); };
+        auto other = [h, &pick, &plane](const Group &g) { return pick(g) && !use_quad(h, g) && !plane(g); };
         hsg_status st = run_pair_of(h, 1, 0, false, s, other, r0, r1);
         if (st == HSG_OK) st = run_pair_of(h, 1, 0, energy, s, other, r0, r1);
         if (st != HSG_OK) return st;
@@ -600,7 +729,7 @@ hsg_status run_or_rounds(hsg_lattice *h, int n_or, bool energy, hipStream_t s, P
 {
     bool any_quad = false;
     for (const Group &g : h->lay.g)
-        if (pick(g)) any_quad = any_quad || use_quad(h, g);
+        if (pick(g)) any_quad = any_quad || use_quad(h, g) || use_plane(h, g, 1, 2, route_count(g, false, r0, r1));
     int r = 0;
     hsg_status st = HSG_OK;
     while (r < n_or && st == HSG_OK) {
@@ -733,6 +862,8 @@ hsg_status run_replica(hsg_lattice *h, hipStream_t s)
 int energy_pb(const hsg_lattice *h, const Group &g)
 {
     if (h->chain == 1 || use_replica(h, g)) return 0;
+    const bool quad = h->n_or > 0 && h->n_or % 2 == 0 && (use_plane(h, g, 1, 2, g.n_rep) || use_quad(h, g));
+    if (use_plane(h, g, h->n_or > 0 ? 1 : 0, quad ? 2 : 1, g.n_rep)) return 0;
     return use_pair(h, g) ? 1 : use_stream(h, g) ? g.s_ytiles * g.s_zslabs : g.n_pb_sweep;
 }
 
@@ -1768,15 +1899,19 @@ hsg_status hsg_autotune(hsg_lattice *h, int32_t n_sweeps, void *d_backup, int32_
         h->kernel_variant = v0;
         if (replica) cands.push_back({5, 0, false});
     }
-    if (any_pair) {
+    {
         const int32_t v0 = h->kernel_variant;
         h->kernel_variant = 4;
-        bool any_quad = false;
-        for (const Group &g : h->lay.g) any_quad = any_quad || use_quad(h, g);
+        bool any = false;  // a launch that only variant 4 makes
+        for (const Group &g : h->lay.g) {
+            any = any || (h->n_hb > 0 && use_plane(h, g, 0, 1, g.n_rep));
+            any = any || (h->n_or > 0 && use_plane(h, g, 1, 1, g.n_rep));
+            any = any || (h->n_or >= 2 && (use_quad(h, g) || use_plane(h, g, 1, 2, g.n_rep)));
+        }
         h->kernel_variant = v0;
-        if (any_quad && h->n_or >= 2) add(4, any_gather);
-        add(3, any_gather);
+        if (any) add(4, any_gather);
     }
+    if (any_pair) add(3, any_gather);
     if (any_stream) add(2, any_gather);
     add(1, true);
     constexpr int kRounds = 2;  // every candidate is timed once per round; its best time counts

@@ -125,6 +125,32 @@ struct MultiReplicaArgs {
 hipError_t launch_replica(const MultiReplicaArgs &m, int storage, bool hw, unsigned threads, size_t lds,
                           hipStream_t s);
 
+// A pair of half-sweeps (groups = 1) or two over-relaxation pairs (groups = 2) in one
+// walk of whole planes, a replica per work-group (plane_march.h): tpg threads (whole
+// waves) per group for the pp = (L/2)^2 site pairs of a plane and parity. Launch with
+// groups * tpg threads and (4 or 11) * 6 L^2 bytes of LDS. The energies go to E.
+struct PlaneArgs {
+    void *spins;
+    const float *J6;
+    const uint8_t *Jbits;
+    const float *Hp;
+    const int32_t *temp_of_slot;
+    const float *beta32;
+    double *E;
+    const uint32_t *tptr;
+    int64_t Nh, r_base;  // r_base: first replica of the launch
+    int32_t L, Lh, pp, tpg;
+    int32_t slots_per_sample, T;
+    uint32_t rep, key0, key1, uid_base;
+};
+struct MultiPlaneArgs {
+    int32_t n_groups, n_blocks;
+    int32_t block_start[kMaxStreamGroups + 1];
+    PlaneArgs g[kMaxStreamGroups];
+};
+hipError_t launch_plane_march(const MultiPlaneArgs &m, int storage, int kind, int groups, bool energy,
+                              unsigned threads, size_t lds, hipStream_t s);
+
 // *flag = 1 if any of the n values is not exactly +1 or -1, else 0.
 hipError_t launch_check_pm1(const float *v, int64_t n, int32_t *flag, hipStream_t s);
 

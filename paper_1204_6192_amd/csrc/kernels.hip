@@ -47,8 +47,8 @@ __device__ __forceinline__ void neighbours(int64_t j, int32_t L, int32_t Lh, int
 // and the planes above and below come as pairs, whatever L is (a plane holds an
 // even number of sites per parity), and only the other x neighbour and the two y
 // neighbours site by site. Against loads of single components: an over-relaxation
-// pair of 512 replicas of L = 30 in float32 273 -> 171 us, of 32 replicas 25 -> 17;
-// bfloat16 186 -> 116 and 19 -> 13.
+// pair of 128 replicas of L = 30 in float32 83 -> 49 us, of 32 replicas 25 -> 17;
+// bfloat16 55 -> 34 and 19 -> 13.
 template <int STORE, int KIND, bool FIELD, bool ENERGY>
 __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
 {

@@ -1,5 +1,5 @@
 // lds_sites.h -- updates of site pairs whose spins, decoded, are held in LDS as
-// three consecutive floats per site (replica.hip).
+// three consecutive floats per site (replica.hip, plane_march.h).
 //
 // A pair of sites is three 8-byte LDS accesses from one address, and consecutive
 // lanes (24 bytes apart) fall into distinct banks. A plane holds (L/2)^2 pairs
@@ -66,6 +66,16 @@ __device__ __forceinline__ PairPos<PAIRED> pair_pos(int j, int L, int Lh)
     return q;
 }
 
+// Hides that the offsets never change, so that the compiler adds them to a plane's
+// base where they are used, and does not hold every sum across a loop.
+template <bool PAIRED>
+__device__ __forceinline__ void hide_pos(PairPos<PAIRED> &q)
+{
+    asm volatile("" : "+v"(q.c), "+v"(q.up0), "+v"(q.dn0));
+    asm volatile("" : "+v"(q.xp0[0]), "+v"(q.xm0[0]), "+v"(q.xp1[0]), "+v"(q.xp0[1]), "+v"(q.xm0[1]), "+v"(q.xp1[1]));
+    if constexpr (!PAIRED) asm volatile("" : "+v"(q.up1), "+v"(q.dn1), "+v"(q.xm1[0]), "+v"(q.xm1[1]));
+}
+
 // The in-plane neighbours (+x, -x, +y, -y) of a pair in the other parity's plane at
 // pl; t as above.
 struct PlaneNb {
@@ -126,6 +136,16 @@ __device__ __forceinline__ PairField<ENERGY> pair_field(const PlaneNb &n, v3 u0,
     return f;
 }
 
+// Makes the compiler form the fields here: it would otherwise move the sums into the
+// branch that uses them, and hold neighbours and couplings until then.
+template <bool ENERGY>
+__device__ __forceinline__ void pin_field(PairField<ENERGY> &f)
+{
+    asm volatile("" : "+v"(f.h0.x), "+v"(f.h0.y), "+v"(f.h0.z), "+v"(f.h1.x), "+v"(f.h1.y), "+v"(f.h1.z));
+    if constexpr (ENERGY)
+        asm volatile("" : "+v"(f.x0), "+v"(f.y0), "+v"(f.z0), "+v"(f.x1), "+v"(f.y1), "+v"(f.z1));
+}
+
 // The new spins of a pair from its fields and (over-relaxation) its old spins o0,
 // o1: their codes, and in s0, s1 what reading the codes back gives. With ENERGY the
 // bond energy of the two sites is added to e (each bond has one endpoint on a
@@ -135,13 +155,14 @@ __device__ __forceinline__ typename Codec<STORE>::R pair_update(const PairField<
                                                                 float beta, v3 &s0, v3 &s1, double &e)
 {
     using C = Codec<STORE>;
+    v3 n0, n1;
     if (KIND != 1) {
-        s0 = heat_bath<HW, STORE == 0>(f.h0, beta, rr.x, rr.y);
-        s1 = heat_bath<HW, STORE == 0>(f.h1, beta, rr.z, rr.w);
+        n0 = heat_bath<HW, STORE == 0>(f.h0, beta, rr.x, rr.y);
+        n1 = heat_bath<HW, STORE == 0>(f.h1, beta, rr.z, rr.w);
     } else {
-        over_relax_pair<STORE == 0>(o0, f.h0, o1, f.h1, s0, s1);
+        over_relax_pair<STORE == 0>(o0, f.h0, o1, f.h1, n0, n1);
     }
-    const typename C::R code = C::encode_pair(s0, s1);
+    const typename C::R code = C::encode_pair(n0, n1);
     C::decode_pair(code, s0, s1);
     if (ENERGY) {
         e -= (double)s0.x * f.x0 + (double)s0.y * f.y0 + (double)s0.z * f.z0;

@@ -1,0 +1,8 @@
+// Instantiation of the plane march for spin storage codec 3 (one translation unit per
+// codec so that the library builds in parallel).
+#include "plane_march.h"
+
+namespace hsg {
+template hipError_t launch_plane_s<3>(const MultiPlaneArgs &, int, int, bool, bool, bool, bool, unsigned, size_t,
+                                       hipStream_t);
+}  // namespace hsg

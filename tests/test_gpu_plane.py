@@ -1,0 +1,78 @@
+"""Pairs of half-sweeps, and two over-relaxation pairs, in one walk of whole planes
+against single half-sweep launches (kernel variant 1, the gather kernel): the same
+spins, temperature maps and acceptances bit for bit, the energies to rounding. Sums
+of at most 3 L^3 float64 terms of order 1 in two orders differ by less than
+3 L^3 2^-53 of their absolute sum, a few 1e-11 of |E| at L = 64 at worst."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1204_6192_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hsg():
+    from paper_1204_6192_amd import hsg as mod
+    return mod
+
+
+def _group(L, D, O, T, field, couplings, uid=0):
+    rng = np.random.Generator(np.random.Philox(inputs.INSTANCE_SEED_BASE + 97))
+    one = inputs.make_group(rng, L, D, 1, inputs.geometric_ladder(0.1, 0.6, 1), couplings=couplings, field=field)
+    return inputs.Group(L=L, n_samples=D, n_copies=O, temps=inputs.geometric_ladder(0.1, 0.6, T), J=one.J, H=one.H,
+                        spins0=np.broadcast_to(one.spins0, (D, O, T, 3, L ** 3)).copy(),
+                        coupling_kind=one.coupling_kind, sample_uid_base=uid)
+
+
+def _run(hsg, groups, variant, storage, n_hb, n_or, math, batch=None, overlap=False):
+    lat = hsg.Lattice(groups, storage=storage, n_hb=n_hb, n_or=n_or, seed=inputs.PHILOX_KEY_BASE + 97)
+    lat.set_kernel(variant)
+    lat.set_math(math)
+    if batch is not None:
+        lat.set_batch(batch)
+    if overlap:
+        lat.set_overlap(True)
+    lat.sweep(2)
+    out = [lat.get_spins(), lat.get_temp_map(), lat.get_pt_accepts(), lat.get_energies()]
+    E = lat.measure_energy()
+    torch.cuda.synchronize()
+    lat.close()
+    return out, E
+
+
+# (L, samples, copies, rungs): every plane size class -- idle lanes (26, 30, 34, 36, 46,
+# 62), whole waves (24, 32, 64), rows that a pair straddles (L % 4 = 2) -- at replica
+# counts on both sides of the lines that the choice of the walk draws
+@pytest.mark.parametrize("L,D,O,T", [(24, 1, 2, 3), (26, 1, 2, 48), (26, 2, 2, 64), (28, 1, 1, 1), (30, 1, 2, 128),
+                                     (32, 2, 2, 3), (32, 3, 2, 86), (32, 5, 2, 110), (34, 1, 2, 64), (36, 1, 2, 95),
+                                     (36, 1, 2, 96), (44, 2, 2, 64), (46, 2, 1, 128), (48, 1, 2, 96), (62, 1, 1, 97),
+                                     (62, 1, 2, 129), (64, 2, 1, 97), (64, 2, 1, 128)])
+@pytest.mark.parametrize("storage,field,couplings,n_hb,n_or,math",
+                         [("f32", None, "gaussian", 1, 4, 0), ("f32", ("gaussian", 0.2), "bimodal", 2, 1, 0),
+                          ("bf16", ("gaussian", 0.1), "gaussian", 1, 0, 1), ("f16", None, "bimodal", 1, 3, 0),
+                          ("qangle", None, "gaussian", 1, 2, 0), ("bf16", None, "gaussian", 1, 0, 0)])
+def test_plane_march_bit_identical(hsg, L, D, O, T, storage, field, couplings, n_hb, n_or, math):
+    g = _group(L, D, O, T, field, couplings)
+    a, E = _run(hsg, [g], 0, storage, n_hb, n_or, math)
+    b, _ = _run(hsg, [g], 1, storage, n_hb, n_or, math)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
+    assert torch.allclose(a[3], b[3], rtol=1e-10, atol=1e-9)
+    assert torch.allclose(a[3], E, rtol=1e-10, atol=1e-9)
+
+
+@pytest.mark.parametrize("storage,n_or", [("f32", 4), ("bf16", 3), ("f16", 0)])
+def test_plane_march_of_several_sizes(hsg, storage, n_or):
+    """Several sizes in one handle, in batches that leave a remainder and as two
+    halves on two streams: the same result, energies included."""
+    groups, uid = [], 0
+    for L, D, O, T in ((24, 2, 2, 7), (32, 2, 2, 5), (36, 2, 2, 64), (40, 2, 2, 48)):
+        groups.append(_group(L, D, O, T, None, "gaussian", uid))
+        uid += D
+    ref, _ = _run(hsg, groups, 0, storage, 1, n_or, 0)
+    for kw in ({"batch": 50}, {"batch": 200}, {"overlap": True}):
+        got, _ = _run(hsg, groups, 0, storage, 1, n_or, 0, **kw)
+        for x, y in zip(got, ref):
+            assert torch.equal(x, y)
