@@ -290,7 +290,8 @@ hsg_status hsg_set_tuning(hsg_lattice *h, int32_t slots_per_item);
  * staged planes fit the work-group's LDS; from L = 24 on, where a replica's
  * whole planes fit one work-group (L <= 64 for a pair, L <= 32 for two pairs, any
  * even L) and there are replicas enough for the card, 4 takes them in one walk
- * per replica; 5 = lattice sizes whose replica fits
+ * per replica, and where there are too few for any march it takes single
+ * half-sweeps by the gather kernel; 5 = lattice sizes whose replica fits
  * a work-group's LDS (12 bytes per site: L <= 22 with 160 KiB; the paper's per-block shared-memory tiles, Sec. 3.1, taken to a whole
  * replica) run all half-sweeps and the energies of a sweep in one launch of
  * hsg_sweep, the spins staying in LDS; the other sizes, and the per-call entry

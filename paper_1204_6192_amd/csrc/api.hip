@@ -376,16 +376,23 @@ void drop_graphs(hsg_lattice *h)
     h->graph = nullptr;
 }
 
+// Slots per work item of the gather kernel: set, or 8, which spares the couplings'
+// loads, but fewer where that leaves less than eight work-groups per CU.
 int chunk_for(const hsg_lattice *h, const Group &g)
 {
     const int spp = g.O * g.T;
     int c = h->slots_per_item > 0 ? h->slots_per_item : 8;
+    if (h->slots_per_item == 0)
+        while (c > 1 && (int64_t)g.D * ((spp + c - 1) / c) * g.n_pb_sweep < 2048) c /= 2;
     return c < spp ? c : spp;
 }
 
-hsg::SweepArgs sweep_args(const hsg_lattice *h, const Group &g, int parity, uint32_t rep)
+hsg::SweepArgs sweep_args(const hsg_lattice *h, const Group &g, int parity, uint32_t rep, int64_t r0 = 0,
+                          int64_t r1 = -1)
 {
     hsg::SweepArgs a{};
+    a.r_begin = r0;
+    a.r_end = r1 < 0 ? g.n_rep : r1;
     a.spins = h->state + g.o_spins;
     a.J6 = reinterpret_cast<const float *>(h->coup + g.o_J6);
     a.Hp = g.field ? reinterpret_cast<const float *>(h->field + g.o_H) : nullptr;
@@ -479,6 +486,37 @@ hsg::StreamArgs stream_args(const hsg_lattice *h, const Group &g, int parity, ui
     return a;
 }
 
+// Replicas that choose the route of a pass over [r0, r1) (r1 < 0: all): the launch's,
+// but with energies the group's, so that batches and halves sum them in the same order
+// as the whole.
+int64_t route_count(const Group &g, bool energy, int64_t r0, int64_t r1)
+{
+    return energy || r1 < 0 ? g.n_rep : r1 - r0;
+}
+
+// Single half-sweeps by the gather kernel, whose work-groups split a replica, where
+// the marches along z would leave CUs idle in a launch of n replicas: a march is a
+// chain of L steps however few replicas there are, a gather pass of some replicas
+// lasts 6 us. Measured in us, gather against the march that takes the work otherwise:
+//   L <= 32 (whole planes per work-group): two pairs L = 32 f32 8 replicas 24 : 41,
+//     32 33 : 42, 64 59 : 44; bf16 64 39 : 44, 96 53 : 45; heat bath 8 replicas
+//     15 : 83, 192 74 : 91 (f32), 58 : 88 (bf16); a whole sweep of 8 58 : 173.
+//   above (z-slabs), by sites: a pair L = 40 f32 32 replicas (2.0 M) 30 : 42, 64
+//     51 : 45, bf16 64 (4.1 M) 34 : 45, 128 54 : 55; heat bath f32 96 (6.1 M)
+//     76 : 86, bf16 128 (8.2 M) 71 : 91. Where rows make whole waves (L % 64 == 0)
+//     the march is faster: L = 64 f32 a pair 8 (2.1 M) 31 : 36, 16 53 : 39, heat
+//     bath 16 (4.2 M) 57 : 63, 32 101 : 78; bf16 a pair 16 34 : 36, 32 54 : 47.
+bool use_gather(const hsg_lattice *h, const Group &g, int kind, int64_t n)
+{
+    if (!use_stream(h, g)) return true;
+    if ((h->kernel_variant != 0 && h->kernel_variant < 4) || g.L < 24) return false;
+    const bool f32 = h->storage == HSG_STORE_F32, waves = g.L % 64 == 0;
+    if (g.L <= 32) return n <= (kind != 1 ? 192 : f32 ? 48 : 72);
+    const int64_t sites = n * g.L * g.L * g.L;
+    if (kind == 1) return sites <= (f32 ? (waves ? 2400000 : 3200000) : (waves ? 4200000 : 6000000));
+    return sites <= (f32 ? (waves ? 4500000 : 6000000) : (waves ? 6000000 : 8000000));
+}
+
 // Launches one half-sweep of parity `parity` (fuse = 0), one fused pair
 // (fuse = 1) or two fused over-relaxation pairs (fuse = 2) for the groups
 // `pick` selects, over replicas [r0, r1) of each (r1 < 0: all). The z-march
@@ -508,7 +546,7 @@ hsg_status run_groups(hsg_lattice *h, int kind, int parity, int rep, bool energy
     };
     for (const Group &g : h->lay.g) {
         if (!pick(g)) continue;
-        if (fuse || use_stream(h, g)) {
+        if (fuse || (use_stream(h, g) && !use_gather(h, g, kind, route_count(g, energy, r0, r1)))) {
             if (m.n_groups == hsg::kMaxStreamGroups) {
                 hsg_status st = flush();
                 if (st != HSG_OK) return st;
@@ -524,8 +562,7 @@ hsg_status run_groups(hsg_lattice *h, int kind, int parity, int rep, bool energy
             const size_t l = fused_lds_bytes(g, fuse);
             lds = l > lds ? l : lds;
         } else {
-            if (r0 != 0 || (r1 >= 0 && r1 != g.n_rep)) return fail(HSG_E_STATE, "replica ranges need the z-march");
-            const hsg::SweepArgs a = sweep_args(h, g, parity, (uint32_t)rep);
+            const hsg::SweepArgs a = sweep_args(h, g, parity, (uint32_t)rep, r0, r1);
             if ((int64_t)g.D * a.n_chunks * a.n_pb > 0x7FFFFFFFll) return fail(HSG_E_SIZE, "grid too large");
             const hipError_t e = hsg::launch_half_sweep(a, h->storage, kind, g.field, energy, s);
             if (e != hipSuccess) return hip_fail(e, "half-sweep launch");
@@ -576,20 +613,13 @@ bool use_plane(const hsg_lattice *h, const Group &g, int kind, int groups, int64
         const int64_t least = kind == 0 ? 256 : f32 ? 96 : 128;
         return n >= least && (waves <= 8 || n <= 256 || 4 * n >= 3 * slots);
     }
+    if (use_gather(h, g, kind, n)) return false;
     if (g.L <= 32) {
         if (groups == 2) return !f32 || n <= 1024;
         return !g.field && (kind == 0 || n <= 512);
     }
     if (kind == 1) return (!g.field || f32) && (waves <= 8 ? n >= 192 : 4 * n >= 3 * slots);
     return !g.field && (waves <= 8 || waves >= 13) && 20 * n >= 19 * slots;
-}
-
-// Replicas that choose the route of a pass over [r0, r1) (r1 < 0: all): the launch's,
-// but with energies the group's, so that batches and halves sum them in the same order
-// as the whole.
-int64_t route_count(const Group &g, bool energy, int64_t r0, int64_t r1)
-{
-    return energy || r1 < 0 ? g.n_rep : r1 - r0;
 }
 
 // groups = 1: a pair of half-sweeps of the given kind; 2: two over-relaxation pairs,
@@ -665,10 +695,11 @@ hsg_status run_pair_of(hsg_lattice *h, int kind, int rep, bool energy, hipStream
 {
     bool any_pair = false, any_single = false, any_plane = false;
     auto plane = [&](const Group &g) { return use_plane(h, g, kind, 1, route_count(g, energy, r0, r1)); };
+    auto pair = [&](const Group &g) { return use_pair(h, g) && !use_gather(h, g, kind, route_count(g, energy, r0, r1)); };
     for (const Group &g : h->lay.g) {
         if (!pick(g)) continue;
         if (plane(g)) any_plane = true;
-        else if (use_pair(h, g)) any_pair = true;
+        else if (pair(g)) any_pair = true;
         else any_single = true;
     }
     if (any_plane) {
@@ -676,12 +707,12 @@ hsg_status run_pair_of(hsg_lattice *h, int kind, int rep, bool energy, hipStream
         if (st != HSG_OK) return st;
     }
     if (any_pair) {
-        auto fused = [h, &pick, &plane](const Group &g) { return pick(g) && use_pair(h, g) && !plane(g); };
+        auto fused = [&](const Group &g) { return pick(g) && pair(g) && !plane(g); };
         hsg_status st = run_groups(h, kind, 0, rep, energy, 1, fused, s, r0, r1);
         if (st != HSG_OK) return st;
     }
     if (any_single) {
-        auto single = [h, &pick, &plane](const Group &g) { return pick(g) && !use_pair(h, g) && !plane(g); };
+        auto single = [&](const Group &g) { return pick(g) && !pair(g) && !plane(g); };
         hsg_status st = run_groups(h, kind, 0, rep, false, 0, single, s, r0, r1);
         if (st == HSG_OK) st = run_groups(h, kind, 1, rep, energy, 0, single, s, r0, r1);
         if (st != HSG_OK) return st;
@@ -697,10 +728,11 @@ hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, Pick pick, in
 {
     bool any_quad = false, any_other = false, any_plane = false;
     auto plane = [&](const Group &g) { return use_plane(h, g, 1, 2, route_count(g, energy, r0, r1)); };
+    auto quads = [&](const Group &g) { return use_quad(h, g) && !use_gather(h, g, 1, route_count(g, energy, r0, r1)); };
     for (const Group &g : h->lay.g) {
         if (!pick(g)) continue;
         if (plane(g)) any_plane = true;
-        else if (use_quad(h, g)) any_quad = true;
+        else if (quads(g)) any_quad = true;
         else any_other = true;
     }
     if (any_plane) {
@@ -708,12 +740,12 @@ hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, Pick pick, in
         if (st != HSG_OK) return st;
     }
     if (any_quad) {
-        auto quad = [h, &pick, &plane](const Group &g) { return pick(g) && use_quad(h, g) && !plane(g); };
+        auto quad = [&](const Group &g) { return pick(g) && quads(g) && !plane(g); };
         hsg_status st = run_groups(h, 1, 0, 0, energy, 2, quad, s, r0, r1);
         if (st != HSG_OK) return st;
     }
     if (any_other) {
-        auto other = [h, &pick, &plane](const Group &g) { return pick(g) && !use_quad(h, g) && !plane(g); };
+        auto other = [&](const Group &g) { return pick(g) && !quads(g) && !plane(g); };
         hsg_status st = run_pair_of(h, 1, 0, false, s, other, r0, r1);
         if (st == HSG_OK) st = run_pair_of(h, 1, 0, energy, s, other, r0, r1);
         if (st != HSG_OK) return st;
@@ -862,9 +894,12 @@ hsg_status run_replica(hsg_lattice *h, hipStream_t s)
 int energy_pb(const hsg_lattice *h, const Group &g)
 {
     if (h->chain == 1 || use_replica(h, g)) return 0;
-    const bool quad = h->n_or > 0 && h->n_or % 2 == 0 && (use_plane(h, g, 1, 2, g.n_rep) || use_quad(h, g));
-    if (use_plane(h, g, h->n_or > 0 ? 1 : 0, quad ? 2 : 1, g.n_rep)) return 0;
-    return use_pair(h, g) ? 1 : use_stream(h, g) ? g.s_ytiles * g.s_zslabs : g.n_pb_sweep;
+    const int kind = h->n_or > 0 ? 1 : 0;  // of the last pass
+    const bool gather = use_gather(h, g, kind, g.n_rep);
+    const bool quad = h->n_or > 0 && h->n_or % 2 == 0 && (use_plane(h, g, 1, 2, g.n_rep) || (use_quad(h, g) && !gather));
+    if (use_plane(h, g, kind, quad ? 2 : 1, g.n_rep)) return 0;
+    if (gather) return g.n_pb_sweep;
+    return use_pair(h, g) ? 1 : g.s_ytiles * g.s_zslabs;
 }
 
 // Samples [d0, d1) of half c of group g (c < 0: all).
@@ -1904,8 +1939,8 @@ hsg_status hsg_autotune(hsg_lattice *h, int32_t n_sweeps, void *d_backup, int32_
         h->kernel_variant = 4;
         bool any = false;  // a launch that only variant 4 makes
         for (const Group &g : h->lay.g) {
-            any = any || (h->n_hb > 0 && use_plane(h, g, 0, 1, g.n_rep));
-            any = any || (h->n_or > 0 && use_plane(h, g, 1, 1, g.n_rep));
+            any = any || (h->n_hb > 0 && (use_plane(h, g, 0, 1, g.n_rep) || (g.stream_ok && use_gather(h, g, 0, g.n_rep))));
+            any = any || (h->n_or > 0 && (use_plane(h, g, 1, 1, g.n_rep) || (g.stream_ok && use_gather(h, g, 1, g.n_rep))));
             any = any || (h->n_or >= 2 && (use_quad(h, g) || use_plane(h, g, 1, 2, g.n_rep)));
         }
         h->kernel_variant = v0;

@@ -23,6 +23,7 @@ struct SweepArgs {
     const int32_t *temp_of_slot; // [D][O][T] rung of each slot
     const float *beta32;         // [T]
     double *e_partials;          // [replica][n_pb] when the pass computes energies
+    int64_t r_begin, r_end;      // replicas of the launch
     int64_t Nh;
     int32_t L, Lh;
     int32_t slots_per_sample;    // O * T

@@ -106,6 +106,7 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
         const int sis = ch * a.chunk + cs;  // replica index inside the sample: o * T + slot
         if (sis >= a.slots_per_sample) break;
         const int64_t rep = (int64_t)d * a.slots_per_sample + sis;
+        if (rep < a.r_begin || rep >= a.r_end) continue;
         double e = 0.0;
         if (active) {
             const float beta = a.beta32[a.temp_of_slot[rep]];

@@ -46,7 +46,7 @@ def _run(hsg, groups, variant, storage, n_hb, n_or, math, batch=None, overlap=Fa
 # (L, samples, copies, rungs): every plane size class -- idle lanes (26, 30, 34, 36, 46,
 # 62), whole waves (24, 32, 64), rows that a pair straddles (L % 4 = 2) -- at replica
 # counts on both sides of the lines that the choice of the walk draws
-@pytest.mark.parametrize("L,D,O,T", [(24, 1, 2, 3), (26, 1, 2, 48), (26, 2, 2, 64), (28, 1, 1, 1), (30, 1, 2, 128),
+@pytest.mark.parametrize("L,D,O,T", [(24, 1, 2, 3), (24, 2, 1, 100), (28, 1, 2, 97), (26, 1, 2, 48), (26, 2, 2, 64), (28, 1, 1, 1), (30, 1, 2, 128),
                                      (32, 2, 2, 3), (32, 3, 2, 86), (32, 5, 2, 110), (34, 1, 2, 64), (36, 1, 2, 95),
                                      (36, 1, 2, 96), (44, 2, 2, 64), (46, 2, 1, 128), (48, 1, 2, 96), (62, 1, 1, 97),
                                      (62, 1, 2, 129), (64, 2, 1, 97), (64, 2, 1, 128)])
@@ -75,4 +75,24 @@ def test_plane_march_of_several_sizes(hsg, storage, n_or):
     for kw in ({"batch": 50}, {"batch": 200}, {"overlap": True}):
         got, _ = _run(hsg, groups, 0, storage, 1, n_or, 0, **kw)
         for x, y in zip(got, ref):
+            assert torch.equal(x, y)
+
+
+# few replicas: gather passes, with one and several slots per work item, and with one
+# kind of pass on each side of its line (24 of 100, 32 of 60, 40 of 60 replicas)
+@pytest.mark.parametrize("L,D,O,T", [(24, 1, 1, 1), (24, 2, 2, 25), (28, 1, 2, 12), (32, 2, 2, 15), (36, 2, 2, 3),
+                                     (40, 3, 2, 10), (64, 1, 2, 2), (64, 2, 1, 8), (128, 1, 1, 2)])
+@pytest.mark.parametrize("storage,field,couplings,n_hb,n_or,math",
+                         [("f32", None, "gaussian", 1, 4, 0), ("f32", ("gaussian", 0.2), "bimodal", 2, 1, 0),
+                          ("bf16", None, "gaussian", 1, 3, 1), ("qangle", None, "bimodal", 1, 0, 0)])
+def test_few_replicas_bit_identical(hsg, L, D, O, T, storage, field, couplings, n_hb, n_or, math):
+    g = _group(L, D, O, T, field, couplings)
+    a, E = _run(hsg, [g], 0, storage, n_hb, n_or, math)
+    b, _ = _run(hsg, [g], 2, storage, n_hb, n_or, math)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
+    assert torch.allclose(a[3], b[3], rtol=1e-10, atol=1e-9)
+    assert torch.allclose(a[3], E, rtol=1e-10, atol=1e-9)
+    for kw in ({"batch": 3}, {"overlap": True}):
+        c, _ = _run(hsg, [g], 0, storage, n_hb, n_or, math, **kw)
+        for x, y in zip(c, a):
             assert torch.equal(x, y)
