@@ -111,7 +111,7 @@ struct Group {
     int32_t s_TY, s_RB, s_rows, s_ytiles, s_zslabs;
     int32_t s_max_pb;  // most energy partials per replica any allowed geometry makes (scratch sizing)
     // tile-local chain geometry, see hsg::TileArgs (set by hsg_set_chain)
-    int32_t t_TX, t_TY, t_TZ, t_BX, t_BY, t_BZ, t_hx, t_hy, t_hz, t_RXh, t_RY, t_RZ, t_P, t_RB, t_chunks, t_threads;
+    int32_t t_TX, t_TY, t_TZ, t_BX, t_BY, t_BZ, t_hx, t_hy, t_hz, t_RXh, t_RY, t_RZ, t_ps, t_P, t_RB, t_chunks, t_threads;
     size_t t_lds;
 };
 
@@ -1077,6 +1077,35 @@ int32_t tiles_in_phase(const Group &g, int phase)
     return phase == 0 ? 1 : 0;
 }
 
+// Floats per staged plane of a tile: the rows, and as much more as it takes for the
+// 8-byte reads of half a wave (32 site pairs, in the order x, y, z, replica) to meet
+// the fewest bank conflicts on 64 banks. 8^3 tiles: 84 for 80 floats, so that the
+// odd planes use the banks that the rows' halo columns leave free.
+int32_t tile_plane_stride(const Group &g)
+{
+    const int32_t rows = g.t_RY * g.t_RXh, txq = g.t_TX / 4;
+    int32_t best = rows;
+    int least = 1 << 30;
+    for (int32_t ps = rows; ps < rows + 64; ps += 2) {
+        int cost = 0;
+        for (int half = 0; half < 4; ++half) {
+            int uses[64] = {};
+            for (int l = 0; l < 32; ++l) {
+                const int i = half * 32 + l, rb = i / g.t_P, q = i % g.t_P;
+                const int at = rb * 6 * g.t_RZ * ps + q / (txq * g.t_TY) * ps + q / txq % g.t_TY * g.t_RXh + 2 * (q % txq);
+                ++uses[at % 64];
+                ++uses[(at + 1) % 64];
+            }
+            cost += *std::max_element(uses, uses + 64);
+        }
+        if (cost < least) {
+            least = cost;
+            best = ps;
+        }
+    }
+    return best;
+}
+
 // One sweep of the tile-local chain: the tiles of coarse parity 0, then 1.
 hsg_status run_tile_sweep(hsg_lattice *h, hipStream_t s)
 {
@@ -1107,6 +1136,7 @@ hsg_status run_tile_sweep(hsg_lattice *h, hipStream_t s)
             a.RXh = g.t_RXh;
             a.RY = g.t_RY;
             a.RZ = g.t_RZ;
+            a.ps = g.t_ps;
             a.P = g.t_P;
             a.RB = g.t_RB;
             a.n_chunks = g.t_chunks;
@@ -2120,7 +2150,12 @@ hsg_status hsg_set_chain(hsg_lattice *h, int32_t chain, int32_t tile_x, int32_t 
         g.t_RB = rb;
         g.t_chunks = (g.O * g.T + rb - 1) / rb;
         g.t_threads = (g.t_P * rb + 63) / 64 * 64;
-        g.t_lds = per_rep * rb;
+        g.t_ps = tile_plane_stride(g);
+        g.t_lds = (size_t)2 * 3 * g.t_RZ * g.t_ps * sizeof(float) * rb;
+        if (g.t_lds > 64 * 1024) {
+            g.t_ps = g.t_RY * g.t_RXh;
+            g.t_lds = per_rep * rb;
+        }
     }
     h->lay.g = gs;
     h->chain = 1;

@@ -76,7 +76,7 @@ struct TileArgs {
     const float *beta32;
     const uint32_t *tptr;
     int64_t Nh;
-    int32_t L, Lh, TX, TY, TZ, BX, BY, BZ, hx, hy, hz, RXh, RY, RZ, P, RB, n_chunks;
+    int32_t L, Lh, TX, TY, TZ, BX, BY, BZ, hx, hy, hz, RXh, RY, RZ, ps, P, RB, n_chunks;
     int32_t phase, n_tiles_phase, n_blocks;
     int32_t n_or, n_hb, n_hit;
     int32_t slots_per_sample, T;

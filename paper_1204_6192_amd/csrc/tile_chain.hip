@@ -14,8 +14,16 @@
 // loaded once per visit). The halo belongs to tiles of the other coarse parity,
 // which no work-group of this launch changes. Finally the tile's own sites are
 // written back. A thread owns one pair of neighbouring sites (x/2 = 2m, 2m + 1)
-// of each parity in one replica and keeps their couplings (and field) in
-// registers for the whole visit.
+// of each parity in one replica and keeps their spins, couplings (and field) in
+// registers for the whole visit: of a site's neighbours LDS gives the four pairs
+// beside it in y and z and the one x neighbour of another thread, and it takes the
+// pair's new spins for the others.
+//
+// Bound by LDS, then VALU. With every neighbour and the old spins read component by
+// component the LDS pipe was busy for 86 % of a visit, two thirds of that in bank
+// conflicts; pairs in 8-byte reads, a third fewer of them, and planes padded against
+// conflicts (tile_plane_stride) brought a visit of 8^3 tiles of 256 float32 replicas of
+// L = 32 (10 over-relaxation rounds and a heat-bath round) from 231 to 113 us.
 //
 // What LDS holds: every spin as a load returns it (decoded and renormalised).
 // The final store must write exactly the code of each site's last update:
@@ -117,7 +125,7 @@ __device__ __forceinline__ void pair_update(const v3 (&nb0)[6], const v3 (&nb1)[
 template <int STORE, bool FIELD, bool JB, bool HW>
 __global__ __launch_bounds__(1024) void k_tile_visit(TileArgs a)
 {
-    extern __shared__ float lds[];  // [RB][parity][3][RZ][RY][Lh]
+    extern __shared__ __align__(16) float lds[];  // [RB][parity][3][RZ][ps], ps >= RY RXh
     using C = Codec<STORE>;
     using R = TileRep<STORE>;
     using T = typename C::T;
@@ -132,7 +140,7 @@ __global__ __launch_bounds__(1024) void k_tile_visit(TileArgs a)
     const int L = a.L, Lh = a.Lh, RXh = a.RXh, RY = a.RY, RZ = a.RZ;
     const int xs = a.hx ? (X * a.TX / 2 - 2 + Lh) % Lh : 0;  // half-index of LDS column 0
     const uint32_t Nh = (uint32_t)a.Nh;
-    const int cs = RZ * RY * RXh;  // floats per component of one parity of one replica
+    const int ps = a.ps, cs = RZ * ps;  // floats per plane, and per component of one parity of one replica
     const int tid = threadIdx.x;
     const int P = a.P;  // site pairs per parity of the tile
     const int rb = tid / P;
@@ -165,7 +173,7 @@ __global__ __launch_bounds__(1024) void k_tile_visit(TileArgs a)
         xh = xh >= Lh ? xh - Lh : xh;
         v3 s0, s1;
         C::load_pair(src, Nh, (uint32_t)((z * L + y) * Lh + xh), s0, s1);
-        lds_put_pair(lds, ((rr * 2 + par) * 3 * RZ + lz) * RY * RXh + ly * RXh + 2 * xp, cs, s0, s1);
+        lds_put_pair(lds, ((rr * 2 + par) * 3 * RZ + lz) * ps + ly * RXh + 2 * xp, cs, s0, s1);
     }
 
     // my pair, its couplings and field (both parities)
@@ -210,7 +218,13 @@ __global__ __launch_bounds__(1024) void k_tile_visit(TileArgs a)
     const uint32_t tsweep = *a.tptr;
     __syncthreads();
 
-    auto at = [&](int par, int pz, int py, int lx) { return ((rb * 2 + par) * 3 * RZ + pz) * RY * RXh + py * RXh + lx; };
+    auto at = [&](int par, int pz, int py, int lx) { return ((rb * 2 + par) * 3 * RZ + pz) * ps + py * RXh + lx; };
+    // my sites as LDS holds them: only the neighbours at other half-indices are read there
+    v3 own[2][2];
+    if (active) {
+#pragma unroll
+        for (int par = 0; par < 2; ++par) lds_get_pair(lds, at(par, lz, ly, lx0), cs, own[par][0], own[par][1]);
+    }
     auto rd = [&](int w) { return v3{lds[w], lds[w + cs], lds[w + 2 * cs]}; };
     auto half_round = [&](int kind, int p, uint32_t rep) {
         if (active) {
@@ -219,11 +233,12 @@ __global__ __launch_bounds__(1024) void k_tile_visit(TileArgs a)
             // the x-neighbour that is not one of my two positions (periodic only
             // when the row is whole; with a halo it lies inside the staged row)
             const int xe = o ? (lx0 + 2 == RXh ? 0 : lx0 + 2) : (lx0 == 0 ? RXh - 1 : lx0 - 1);
-            const v3 c0 = rd(at(qo, lz, ly, lx0)), c1 = rd(at(qo, lz, ly, lx0 + 1)), ex = rd(at(qo, lz, ly, xe));
-            const v3 ym0 = rd(at(qo, lz, lym, lx0)), ym1 = rd(at(qo, lz, lym, lx0 + 1));
-            const v3 yp0 = rd(at(qo, lz, lyp, lx0)), yp1 = rd(at(qo, lz, lyp, lx0 + 1));
-            const v3 zm0 = rd(at(qo, lzm, ly, lx0)), zm1 = rd(at(qo, lzm, ly, lx0 + 1));
-            const v3 zp0 = rd(at(qo, lzp, ly, lx0)), zp1 = rd(at(qo, lzp, ly, lx0 + 1));
+            const v3 c0 = own[qo][0], c1 = own[qo][1], ex = rd(at(qo, lz, ly, xe));
+            v3 ym0, ym1, yp0, yp1, zm0, zm1, zp0, zp1;
+            lds_get_pair(lds, at(qo, lz, lyp, lx0), cs, yp0, yp1);
+            lds_get_pair(lds, at(qo, lz, lym, lx0), cs, ym0, ym1);
+            lds_get_pair(lds, at(qo, lzp, ly, lx0), cs, zp0, zp1);
+            lds_get_pair(lds, at(qo, lzm, ly, lx0), cs, zm0, zm1);
             v3 nb0[6], nb1[6];  // neighbours in the order +x, -x, +y, -y, +z, -z
             if (o) {
                 nb0[0] = c1; nb0[1] = c0;
@@ -239,8 +254,7 @@ __global__ __launch_bounds__(1024) void k_tile_visit(TileArgs a)
             const int w = at(p, lz, ly, lx0);
             v3 s0, s1;
             if (kind == 1) {
-                const v3 old0 = rd(w), old1 = rd(w + 1);
-                pair_update<STORE, 1>(nb0, nb1, jc[p], hs[p][0], hs[p][1], old0, old1, u32x4{0u, 0u, 0u, 0u}, beta,
+                pair_update<STORE, 1>(nb0, nb1, jc[p], hs[p][0], hs[p][1], own[p][0], own[p][1], u32x4{0u, 0u, 0u, 0u}, beta,
                                       false, s0, s1);
             } else {
                 const u32x4 rr = philox4x32_10(u32x4{j0 >> 1, tsweep, c2 | (rep << 12) | ((uint32_t)p << 16), uid},
@@ -252,7 +266,9 @@ __global__ __launch_bounds__(1024) void k_tile_visit(TileArgs a)
                 own_raw[p][0] = r0;
                 own_raw[p][1] = r1;
             }
-            lds_put_pair(lds, w, cs, R::shared(r0), R::shared(r1));
+            own[p][0] = R::shared(r0);
+            own[p][1] = R::shared(r1);
+            lds_put_pair(lds, w, cs, own[p][0], own[p][1]);
         }
         __syncthreads();
     };
@@ -273,14 +289,8 @@ __global__ __launch_bounds__(1024) void k_tile_visit(TileArgs a)
     if (active) {
 #pragma unroll
         for (int par = 0; par < 2; ++par) {
-            v3 s0, s1;
-            if (R::kRaw) {
-                s0 = own_raw[par][0];
-                s1 = own_raw[par][1];
-            } else {
-                lds_get_pair(lds, at(par, lz, ly, lx0), cs, s0, s1);
-            }
-            C::store_pair(base + (int64_t)par * C::kPlanes * Nh, Nh, j0, s0, s1);
+            const auto &s = R::kRaw ? own_raw[par] : own[par];
+            C::store_pair(base + (int64_t)par * C::kPlanes * Nh, Nh, j0, s[0], s[1]);
         }
     }
 }
