@@ -16,11 +16,20 @@
 // work-groups on the same XCD. The arithmetic per site is the one of the
 // generic kernel (same neighbour order, same functions), so both produce the
 // same bits.
+//
+// Single passes are bound by HBM with float32 spins (a pass of 96 replicas of L = 64
+// with a field, 472 MB, in 113 us: 4.2 TB/s) and by VALU with quantised angles (issued
+// in every cycle) and in the heat bath. So the index arithmetic of a step is kept
+// small: planes as uniform offsets, LDS sites as three consecutive floats (one address
+// per pair) and rolling offsets instead of selects, which took an over-relaxation pair
+// of 32 replicas of L = 128 with quantised angles from 243 to 229 us, of 96 replicas of
+// L = 64 in float16 with a field from 123 to 114 us.
 #pragma once
 #include <type_traits>
 
 #include "device.h"
 #include "kernels.h"
+#include "lds_sites.h"
 
 namespace hsg {
 
@@ -52,13 +61,19 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int lb, f
     const int p = (int)a.parity;
     const bool full = a.TY == L;
     const int y = ytile * a.TY + ty;
-    const int lrow = full ? ty : ty + 1;                         // my row in the LDS plane
-    const int lrm = full ? (ty == 0 ? L - 1 : ty - 1) : ty;      // row y - 1
-    const int lrp = full ? (ty == L - 1 ? 0 : ty + 1) : ty + 2;  // row y + 1
-    const int cstride = a.rows * Lh;                             // floats per component plane
     const int xh0 = 2 * m;
+    // LDS: two planes of [RB][rows][Lh] sites of three floats (lds_sites.h). My sites,
+    // the rows y - 1 and y + 1, the halo row that I stage, in floats from the start of a
+    // replica's plane.
+    const int lrow = full ? ty : ty + 1;
+    const int lrm = full ? (ty == 0 ? L - 1 : ty - 1) : ty;
+    const int lrp = full ? (ty == L - 1 ? 0 : ty + 1) : ty + 2;
+    const int pc = 3 * (lrow * Lh + xh0), pm = 3 * (lrm * Lh + xh0), pq = 3 * (lrp * Lh + xh0);
+    const int ph = 3 * ((ty == 0 ? 0 : a.TY + 1) * Lh + xh0);
     const int rbc = active ? rb : 0;
-    const int lbuf[2] = {rbc * 3 * cstride, (a.RB + rbc) * 3 * cstride};
+    const int lsz = 3 * a.rows * Lh;
+    int lo = rbc * lsz;                        // plane z; the two planes take turns
+    const int losum = (a.RB + 2 * rbc) * lsz;
 
     // Idle lanes read the group's first replica (valid memory) and discard it, so
     // that every global load is issued on every path: the hardware counts
@@ -95,42 +110,46 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int lb, f
     // (a cache hit), so the load is issued by every lane.
     const bool halo = !full && (ty == 0 || ty == a.TY - 1);
     const int hy = !halo ? y : (ty == 0) ? (y == 0 ? L - 1 : y - 1) : (y + 1 == L ? 0 : y + 1);
-    const int hw_row = (ty == 0) ? 0 : a.TY + 1;
-    auto wrapz = [L](int v) { return v >= L ? v - L : v; };
+    // x = 2 x/2 + o on my row of plane z; the x neighbour that is not one of my own two
+    // positions stands to the right for o = 1, to the left for o = 0
+    bool o = (y + z0 + p) & 1;
+    const int pr = 3 * (lrow * Lh + (xh0 + 2 == Lh ? 0 : xh0 + 2)), pl = 3 * (lrow * Lh + (xh0 == 0 ? Lh : xh0) - 1);
+    int pe = o ? pr : pl;
+    const int pesum = pr + pl;
+    const uint32_t cst = (uint32_t)(L * Lh);  // sites of a parity per plane
+    const uint32_t c = (uint32_t)(y * Lh + xh0), ch = (uint32_t)(hy * Lh + xh0);
+    auto plane = [&](int v) { return (uint32_t)(v >= L ? v - L : v) * cst; };
 
-    // Other parity at my two positions: planes z - 1, z, z + 1 decoded and
-    // rolling; plane z + 2, the halo row of plane z + 1 and (over-relaxation)
-    // my own old spins of plane z + 1 are loaded one step ahead, raw.
-    v3 prv0{}, prv1{}, cur0{}, cur1{}, nxt0{}, nxt1{};
+    // Other parity at my two positions: planes z - 1, z, z + 1 decoded and rolling
+    // (three steps at a time without the moves took 10 registers more, and a wave less
+    // per SIMD); plane z + 2, the halo row of plane z + 1 and (over-relaxation) my own
+    // old spins of plane z + 1 are loaded one step ahead, raw.
+    v3 prv[2], cur[2], nxt[2];
     typename C::R nraw, graw, oraw;
     {
-        C::template load_pair<UNI>(oth, Nh, (uint32_t)((((z0 == 0 ? L : z0) - 1) * L + y) * Lh + xh0), prv0, prv1);
-        C::template load_pair<UNI>(oth, Nh, (uint32_t)((z0 * L + y) * Lh + xh0), cur0, cur1);
-        C::template load_raw_pair<UNI>(oth, Nh, (uint32_t)((wrapz(z0 + 1) * L + y) * Lh + xh0), nraw);
-        C::template load_raw_pair<UNI>(oth, Nh, (uint32_t)((z0 * L + hy) * Lh + xh0), graw);
-        C::template load_raw_pair<UNI>(own, Nh, (uint32_t)((z0 * L + y) * Lh + xh0), oraw);
+        C::template load_pair<UNI>(oth, Nh, plane(z0 == 0 ? L - 1 : z0 - 1) + c, prv[0], prv[1]);
+        C::template load_pair<UNI>(oth, Nh, plane(z0) + c, cur[0], cur[1]);
+        C::template load_raw_pair<UNI>(oth, Nh, plane(z0 + 1) + c, nraw);
+        C::template load_raw_pair<UNI>(oth, Nh, plane(z0) + ch, graw);
+        C::template load_raw_pair<UNI>(own, Nh, plane(z0) + c, oraw);
     }
     double e = 0.0;
+    uint32_t j0 = plane(z0) + c;  // my first site, half-index
 
     for (int z = z0; z < z1; ++z) {
-        const int lo = lbuf[z & 1];
-        const uint32_t j0 = (uint32_t)((z * L + y) * Lh + xh0);  // my first site, half-index
+        // (not known to the compiler, so that it adds the offsets where they are used
+        // and does not hold every sum across the loop)
+        asm volatile("" : "+v"(lo), "+v"(pe), "+v"(j0));
         // values that arrived during the last step
-        C::decode_pair(nraw, nxt0, nxt1);
+        C::decode_pair(nraw, nxt[0], nxt[1]);
         v3 old0{}, old1{};
         if (KIND == 1) C::decode_pair(oraw, old0, old1);
         if (active) {  // stage plane z (my two positions, and the halo rows) in LDS
-            const int w = lo + lrow * Lh + xh0;
-            *reinterpret_cast<float2 *>(&lds[w]) = make_float2(cur0.x, cur1.x);
-            *reinterpret_cast<float2 *>(&lds[w + cstride]) = make_float2(cur0.y, cur1.y);
-            *reinterpret_cast<float2 *>(&lds[w + 2 * cstride]) = make_float2(cur0.z, cur1.z);
+            pair_put(lds + lo + pc, cur[0], cur[1]);
             if (halo) {  // whole rows: a wave without halo rows skips the decoding
                 v3 g0, g1;
                 C::decode_pair(graw, g0, g1);
-                const int hw = lo + hw_row * Lh + xh0;
-                *reinterpret_cast<float2 *>(&lds[hw]) = make_float2(g0.x, g1.x);
-                *reinterpret_cast<float2 *>(&lds[hw + cstride]) = make_float2(g0.y, g1.y);
-                *reinterpret_cast<float2 *>(&lds[hw + 2 * cstride]) = make_float2(g0.z, g1.z);
+                pair_put(lds + lo + ph, g0, g1);
             }
         }
         float2 jc[6];
@@ -142,42 +161,28 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int lb, f
         // planes already read (their values are never used).
         __builtin_amdgcn_sched_barrier(0);
         {
-            const int zn = z + 1 < z1 ? z + 1 : z;
-            C::template load_raw_pair<UNI>(oth, Nh, (uint32_t)((wrapz(z + 2 <= z1 ? z + 2 : z1) * L + y) * Lh + xh0), nraw);
-            C::template load_raw_pair<UNI>(oth, Nh, (uint32_t)((zn * L + hy) * Lh + xh0), graw);
-            C::template load_raw_pair<UNI>(own, Nh, (uint32_t)((zn * L + y) * Lh + xh0), oraw);
+            const uint32_t zn = plane(z + 1 < z1 ? z + 1 : z);
+            C::template load_raw_pair<UNI>(oth, Nh, plane(z + 2 <= z1 ? z + 2 : z1) + c, nraw);
+            C::template load_raw_pair<UNI>(oth, Nh, zn + ch, graw);
+            C::template load_raw_pair<UNI>(own, Nh, zn + c, oraw);
         }
         u32x4 rr{0u, 0u, 0u, 0u};
         if (KIND != 1 && active) rr = philox4x32_10(u32x4{j0 >> 1, tsweep, c2, uid}, a.key0, a.key1);
         __syncthreads();
         if (active) {
-            const int o = (y + z + p) & 1;  // x = 2 x/2 + o on this row
-            // the x-neighbour that is not one of my own two positions
-            const int xe = o ? (xh0 + 2 == Lh ? 0 : xh0 + 2) : (xh0 == 0 ? Lh - 1 : xh0 - 1);
-            const int we = lo + lrow * Lh + xe;
-            const v3 ex{lds[we], lds[we + cstride], lds[we + 2 * cstride]};
-            const int wm = lo + lrm * Lh + xh0, wp = lo + lrp * Lh + xh0;
-            const float2 ym0 = *reinterpret_cast<const float2 *>(&lds[wm]);
-            const float2 ym1 = *reinterpret_cast<const float2 *>(&lds[wm + cstride]);
-            const float2 ym2 = *reinterpret_cast<const float2 *>(&lds[wm + 2 * cstride]);
-            const float2 yp0 = *reinterpret_cast<const float2 *>(&lds[wp]);
-            const float2 yp1 = *reinterpret_cast<const float2 *>(&lds[wp + cstride]);
-            const float2 yp2 = *reinterpret_cast<const float2 *>(&lds[wp + 2 * cstride]);
+            const v3 ex = site_get(lds + lo + pe);
             // neighbours in the order +x, -x, +y, -y, +z, -z
             v3 nb0[6], nb1[6];
-            if (o) {  // site k at x = 2(xh0 + k) + 1: +x -> xh0 + k + 1, -x -> xh0 + k
-                nb0[0] = cur1; nb0[1] = cur0;
-                nb1[0] = ex;   nb1[1] = cur1;
-            } else {  // x = 2(xh0 + k): +x -> xh0 + k, -x -> xh0 + k - 1
-                nb0[0] = cur0; nb0[1] = ex;
-                nb1[0] = cur1; nb1[1] = cur0;
-            }
-            nb0[2] = v3{yp0.x, yp1.x, yp2.x};
-            nb1[2] = v3{yp0.y, yp1.y, yp2.y};
-            nb0[3] = v3{ym0.x, ym1.x, ym2.x};
-            nb1[3] = v3{ym0.y, ym1.y, ym2.y};
-            nb0[4] = nxt0; nb1[4] = nxt1;
-            nb0[5] = prv0; nb1[5] = prv1;
+            pair_get(lds + lo + pq, nb0[2], nb1[2]);
+            pair_get(lds + lo + pm, nb0[3], nb1[3]);
+            // o: site k at x = 2(xh0 + k) + 1, +x -> xh0 + k + 1, -x -> xh0 + k; else
+            // x = 2(xh0 + k), +x -> xh0 + k, -x -> xh0 + k - 1
+            nb0[0] = o ? cur[1] : cur[0];
+            nb0[1] = o ? cur[0] : ex;
+            nb1[0] = o ? ex : cur[1];
+            nb1[1] = nb0[0];
+            nb0[4] = nxt[0]; nb1[4] = nxt[1];
+            nb0[5] = prv[0]; nb1[5] = prv[1];
             v3 h0 = hs0, h1 = hs1;
             double hx0 = hs0.x, hy0 = hs0.y, hz0 = hs0.z, hx1 = hs1.x, hy1 = hs1.y, hz1 = hs1.z;
 #pragma unroll
@@ -198,8 +203,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int lb, f
                 s0 = heat_bath<KIND == 2, STORE == 0>(h0, beta, rr.x, rr.y);
                 s1 = heat_bath<KIND == 2, STORE == 0>(h1, beta, rr.z, rr.w);
             } else {
-                s0 = over_relax<STORE == 0>(old0, h0);
-                s1 = over_relax<STORE == 0>(old1, h1);
+                over_relax_pair<STORE == 0>(old0, h0, old1, h1, s0, s1);
             }
             const typename C::R code = C::encode_pair(s0, s1);
             C::template store_raw_pair<UNI>(own, Nh, j0, code);
@@ -210,12 +214,16 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int lb, f
                 e -= (double)v0.x * hx0 + (double)v0.y * hy0 + (double)v0.z * hz0;
                 e -= (double)v1.x * hx1 + (double)v1.y * hy1 + (double)v1.z * hz1;
                 if (field) {  // field term of the even sites at my two half-indices
-                    field_energy<UNI>(cur0, cur1, Ho, Nh, j0, e);
+                    field_energy<UNI>(cur[0], cur[1], Ho, Nh, j0, e);
                 }
             }
         }
-        prv0 = cur0; prv1 = cur1;
-        cur0 = nxt0; cur1 = nxt1;
+        prv[0] = cur[0]; prv[1] = cur[1];
+        cur[0] = nxt[0]; cur[1] = nxt[1];
+        lo = losum - lo;
+        pe = pesum - pe;
+        o = !o;
+        j0 += cst;
     }
 
     if (ENERGY) {
