@@ -593,16 +593,18 @@ size_t plane_lds_bytes(const Group &g, int groups) { return (size_t)(groups == 1
 //     is empty enough for 606 : 510.
 //   L <= 32, L % 4 == 0, against the fused marches, L = 32: heat bath 256 replicas
 //     84 : 109, 8192 1757 : 1804 (f32), 1451 : 1595 (bf16), but with a field
-//     2048 550 : 528. Two pairs f32 256 64 : 80, 1024 307 : 313, 8192 2373 : 2167
-//     (there the fused march keeps more bytes in flight); bf16 1024 226 : 260, 8192
-//     1724 : 1779; f16 with a field 2048 623 : 815. A pair 256 46 : 51, 2048
+//     2048 550 : 528. Two pairs f32 256 64 : 80, 1024 306 : 311, 8192 2377 : 2170
+//     (there the fused march keeps more bytes in flight), with energies, whose sums
+//     cost this walk's 128 registers more, 256 75 : 79, 1024 324 : 294; with a field
+//     1024 401 : 435, 8192 3069 : 3320, its sweep 8475 : 9322; bf16 1024 226 : 260,
+//     8192 1724 : 1779; f16 with a field 2048 623 : 815. A pair 256 46 : 51, 2048
 //     507 : 486 (f32).
 //   L = 36 to 64, L % 4 == 0, against two single passes: a pair of L = 64 f32 96
 //     replicas 339 : 230, 192 379 : 495, 768 1489 : 1993; bf16 768 986 : 1258;
 //     L = 40 f32 192 89 : 114; with a field L = 64 f32 192 400 : 451, f16 574 : 547.
 //     Heat bath L = 64 f32 256 420 : 526, bf16 192 338 : 306, 768 1160 : 1198;
 //     L = 40 f32 768 350 : 424; L = 48 (9 waves, so 9 of a CU's 16) bf16 592 : 528.
-bool use_plane(const hsg_lattice *h, const Group &g, int kind, int groups, int64_t n)
+bool use_plane(const hsg_lattice *h, const Group &g, int kind, int groups, bool energy, int64_t n)
 {
     if ((h->kernel_variant != 0 && h->kernel_variant < 4) || g.L < 24) return false;
     const int pp = (g.L / 2) * (g.L / 2), waves = (pp + 63) / 64;
@@ -615,7 +617,7 @@ bool use_plane(const hsg_lattice *h, const Group &g, int kind, int groups, int64
     }
     if (use_gather(h, g, kind, n)) return false;
     if (g.L <= 32) {
-        if (groups == 2) return !f32 || n <= 1024;
+        if (groups == 2) return !f32 || g.field || n <= (energy ? 512 : 1024);
         return !g.field && (kind == 0 || n <= 512);
     }
     if (kind == 1) return (!g.field || f32) && (waves <= 8 ? n >= 192 : 4 * n >= 3 * slots);
@@ -694,7 +696,7 @@ hsg_status run_pair_of(hsg_lattice *h, int kind, int rep, bool energy, hipStream
                        int64_t r1)
 {
     bool any_pair = false, any_single = false, any_plane = false;
-    auto plane = [&](const Group &g) { return use_plane(h, g, kind, 1, route_count(g, energy, r0, r1)); };
+    auto plane = [&](const Group &g) { return use_plane(h, g, kind, 1, energy, route_count(g, energy, r0, r1)); };
     auto pair = [&](const Group &g) { return use_pair(h, g) && !use_gather(h, g, kind, route_count(g, energy, r0, r1)); };
     for (const Group &g : h->lay.g) {
         if (!pick(g)) continue;
@@ -727,7 +729,7 @@ template <class Pick>
 hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, Pick pick, int64_t r0, int64_t r1)
 {
     bool any_quad = false, any_other = false, any_plane = false;
-    auto plane = [&](const Group &g) { return use_plane(h, g, 1, 2, route_count(g, energy, r0, r1)); };
+    auto plane = [&](const Group &g) { return use_plane(h, g, 1, 2, energy, route_count(g, energy, r0, r1)); };
     auto quads = [&](const Group &g) { return use_quad(h, g) && !use_gather(h, g, 1, route_count(g, energy, r0, r1)); };
     for (const Group &g : h->lay.g) {
         if (!pick(g)) continue;
@@ -761,7 +763,7 @@ hsg_status run_or_rounds(hsg_lattice *h, int n_or, bool energy, hipStream_t s, P
 {
     bool any_quad = false;
     for (const Group &g : h->lay.g)
-        if (pick(g)) any_quad = any_quad || use_quad(h, g) || use_plane(h, g, 1, 2, route_count(g, false, r0, r1));
+        if (pick(g)) any_quad = any_quad || use_quad(h, g) || use_plane(h, g, 1, 2, false, route_count(g, false, r0, r1));
     int r = 0;
     hsg_status st = HSG_OK;
     while (r < n_or && st == HSG_OK) {
@@ -896,8 +898,8 @@ int energy_pb(const hsg_lattice *h, const Group &g)
     if (h->chain == 1 || use_replica(h, g)) return 0;
     const int kind = h->n_or > 0 ? 1 : 0;  // of the last pass
     const bool gather = use_gather(h, g, kind, g.n_rep);
-    const bool quad = h->n_or > 0 && h->n_or % 2 == 0 && (use_plane(h, g, 1, 2, g.n_rep) || (use_quad(h, g) && !gather));
-    if (use_plane(h, g, kind, quad ? 2 : 1, g.n_rep)) return 0;
+    const bool quad = h->n_or > 0 && h->n_or % 2 == 0 && (use_plane(h, g, 1, 2, true, g.n_rep) || (use_quad(h, g) && !gather));
+    if (use_plane(h, g, kind, quad ? 2 : 1, true, g.n_rep)) return 0;
     if (gather) return g.n_pb_sweep;
     return use_pair(h, g) ? 1 : g.s_ytiles * g.s_zslabs;
 }
@@ -1969,9 +1971,9 @@ hsg_status hsg_autotune(hsg_lattice *h, int32_t n_sweeps, void *d_backup, int32_
         h->kernel_variant = 4;
         bool any = false;  // a launch that only variant 4 makes
         for (const Group &g : h->lay.g) {
-            any = any || (h->n_hb > 0 && (use_plane(h, g, 0, 1, g.n_rep) || (g.stream_ok && use_gather(h, g, 0, g.n_rep))));
-            any = any || (h->n_or > 0 && (use_plane(h, g, 1, 1, g.n_rep) || (g.stream_ok && use_gather(h, g, 1, g.n_rep))));
-            any = any || (h->n_or >= 2 && (use_quad(h, g) || use_plane(h, g, 1, 2, g.n_rep)));
+            any = any || (h->n_hb > 0 && (use_plane(h, g, 0, 1, false, g.n_rep) || (g.stream_ok && use_gather(h, g, 0, g.n_rep))));
+            any = any || (h->n_or > 0 && (use_plane(h, g, 1, 1, false, g.n_rep) || (g.stream_ok && use_gather(h, g, 1, g.n_rep))));
+            any = any || (h->n_or >= 2 && (use_quad(h, g) || use_plane(h, g, 1, 2, false, g.n_rep)));
         }
         h->kernel_variant = v0;
         if (any) add(4, any_gather);
