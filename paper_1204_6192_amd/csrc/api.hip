@@ -688,6 +688,46 @@ hsg_status run_plane(hsg_lattice *h, int kind, int rep, int groups, bool energy,
     return flush();
 }
 
+// How a lattice size runs a pair of half-sweeps, or two over-relaxation pairs: in a
+// walk of whole planes, fused in a z-march, or (a pair) as two single passes.
+enum class Way { none, plane, fused, march, gather };
+
+// pairs = 1: a pair of the given kind; 2: two over-relaxation pairs, none where they
+// do not go in one launch. n replicas, see route_count.
+Way way_of(const hsg_lattice *h, const Group &g, int kind, int pairs, bool energy, int64_t n)
+{
+    if (use_plane(h, g, kind, pairs, energy, n)) return Way::plane;
+    const bool gather = use_gather(h, g, kind, n);
+    if (pairs == 2) return use_quad(h, g) && !gather ? Way::fused : Way::none;
+    return gather ? Way::gather : use_pair(h, g) ? Way::fused : Way::march;
+}
+
+// The launch of a sweep that computes the energies of group g, and what it leaves:
+// n_pb partial sums per replica in the scratch buffer, or with n_pb = 0 the energies in
+// E. Decided here alone, by the group, for whoever makes the launch (whatever part of
+// the replicas it is for) and for the end of the sweep, which reads the energies.
+struct LastPass {
+    int pairs;
+    Way way;
+    int n_pb;
+};
+
+LastPass last_pass(const hsg_lattice *h, const Group &g)
+{
+    const int kind = h->n_or > 0 ? 1 : 0;
+    LastPass l{1, Way::none, 0};
+    if (h->n_or > 0 && h->n_or % 2 == 0) l.way = way_of(h, g, 1, 2, true, g.n_rep);
+    if (l.way != Way::none) l.pairs = 2;
+    else l.way = way_of(h, g, kind, 1, true, g.n_rep);
+    switch (l.way) {
+    case Way::plane: l.n_pb = 0; break;
+    case Way::fused: l.n_pb = 1; break;
+    case Way::gather: l.n_pb = g.n_pb_sweep; break;
+    default: l.n_pb = g.s_ytiles * g.s_zslabs;
+    }
+    return l;
+}
+
 // A pair of half-sweeps (parity 0, then parity 1) of the groups `pick`
 // selects: fused where the group holds whole planes, as two single passes
 // otherwise. `energy`: the parity-1 pass computes the energies.
@@ -695,26 +735,29 @@ template <class Pick>
 hsg_status run_pair_of(hsg_lattice *h, int kind, int rep, bool energy, hipStream_t s, Pick pick, int64_t r0,
                        int64_t r1)
 {
+    auto way = [&](const Group &g) {
+        return energy ? last_pass(h, g).way : way_of(h, g, kind, 1, false, route_count(g, false, r0, r1));
+    };
     bool any_pair = false, any_single = false, any_plane = false;
-    auto plane = [&](const Group &g) { return use_plane(h, g, kind, 1, energy, route_count(g, energy, r0, r1)); };
-    auto pair = [&](const Group &g) { return use_pair(h, g) && !use_gather(h, g, kind, route_count(g, energy, r0, r1)); };
     for (const Group &g : h->lay.g) {
         if (!pick(g)) continue;
-        if (plane(g)) any_plane = true;
-        else if (pair(g)) any_pair = true;
+        const Way w = way(g);
+        if (w == Way::plane) any_plane = true;
+        else if (w == Way::fused) any_pair = true;
         else any_single = true;
     }
     if (any_plane) {
-        hsg_status st = run_plane(h, kind, rep, 1, energy, [&](const Group &g) { return pick(g) && plane(g); }, s, r0, r1);
+        auto plane = [&](const Group &g) { return pick(g) && way(g) == Way::plane; };
+        hsg_status st = run_plane(h, kind, rep, 1, energy, plane, s, r0, r1);
         if (st != HSG_OK) return st;
     }
     if (any_pair) {
-        auto fused = [&](const Group &g) { return pick(g) && pair(g) && !plane(g); };
+        auto fused = [&](const Group &g) { return pick(g) && way(g) == Way::fused; };
         hsg_status st = run_groups(h, kind, 0, rep, energy, 1, fused, s, r0, r1);
         if (st != HSG_OK) return st;
     }
     if (any_single) {
-        auto single = [&](const Group &g) { return pick(g) && !pair(g) && !plane(g); };
+        auto single = [&](const Group &g) { return pick(g) && way(g) != Way::plane && way(g) != Way::fused; };
         hsg_status st = run_groups(h, kind, 0, rep, false, 0, single, s, r0, r1);
         if (st == HSG_OK) st = run_groups(h, kind, 1, rep, energy, 0, single, s, r0, r1);
         if (st != HSG_OK) return st;
@@ -722,32 +765,36 @@ hsg_status run_pair_of(hsg_lattice *h, int kind, int rep, bool energy, hipStream
     return HSG_OK;
 }
 
-// Two over-relaxation pairs of the groups `pick` selects: one z-march where
-// use_quad allows it, two pairs elsewhere. `energy`: the last pass computes the
-// energies.
+// Two over-relaxation pairs of the groups `pick` selects: one launch where way_of
+// allows it, two pairs elsewhere. `energy`: the last pass computes the energies.
 template <class Pick>
 hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, Pick pick, int64_t r0, int64_t r1)
 {
+    auto way = [&](const Group &g) {
+        if (!energy) return way_of(h, g, 1, 2, false, route_count(g, false, r0, r1));
+        const LastPass l = last_pass(h, g);
+        return l.pairs == 2 ? l.way : Way::none;
+    };
     bool any_quad = false, any_other = false, any_plane = false;
-    auto plane = [&](const Group &g) { return use_plane(h, g, 1, 2, energy, route_count(g, energy, r0, r1)); };
-    auto quads = [&](const Group &g) { return use_quad(h, g) && !use_gather(h, g, 1, route_count(g, energy, r0, r1)); };
     for (const Group &g : h->lay.g) {
         if (!pick(g)) continue;
-        if (plane(g)) any_plane = true;
-        else if (quads(g)) any_quad = true;
+        const Way w = way(g);
+        if (w == Way::plane) any_plane = true;
+        else if (w == Way::fused) any_quad = true;
         else any_other = true;
     }
     if (any_plane) {
-        hsg_status st = run_plane(h, 1, 0, 2, energy, [&](const Group &g) { return pick(g) && plane(g); }, s, r0, r1);
+        auto plane = [&](const Group &g) { return pick(g) && way(g) == Way::plane; };
+        hsg_status st = run_plane(h, 1, 0, 2, energy, plane, s, r0, r1);
         if (st != HSG_OK) return st;
     }
     if (any_quad) {
-        auto quad = [&](const Group &g) { return pick(g) && quads(g) && !plane(g); };
+        auto quad = [&](const Group &g) { return pick(g) && way(g) == Way::fused; };
         hsg_status st = run_groups(h, 1, 0, 0, energy, 2, quad, s, r0, r1);
         if (st != HSG_OK) return st;
     }
     if (any_other) {
-        auto other = [&](const Group &g) { return pick(g) && !quads(g) && !plane(g); };
+        auto other = [&](const Group &g) { return pick(g) && way(g) == Way::none; };
         hsg_status st = run_pair_of(h, 1, 0, false, s, other, r0, r1);
         if (st == HSG_OK) st = run_pair_of(h, 1, 0, energy, s, other, r0, r1);
         if (st != HSG_OK) return st;
@@ -755,27 +802,34 @@ hsg_status run_or_quad(hsg_lattice *h, bool energy, hipStream_t s, Pick pick, in
     return HSG_OK;
 }
 
-// n_or over-relaxation pairs of the groups `pick` selects, two by two where
-// possible; the last pass computes the energies when `energy` is set.
+// n_or over-relaxation pairs of the groups `pick` selects, two by two where some
+// size takes them so. `energy`: n_or is the sweep's, and the last pass computes the
+// energies, so that the last launch is the one that last_pass says.
 template <class Pick>
 hsg_status run_or_rounds(hsg_lattice *h, int n_or, bool energy, hipStream_t s, Pick pick, int64_t r0 = 0,
                          int64_t r1 = -1)
 {
-    bool any_quad = false;
-    for (const Group &g : h->lay.g)
-        if (pick(g)) any_quad = any_quad || use_quad(h, g) || use_plane(h, g, 1, 2, false, route_count(g, false, r0, r1));
+    if (n_or == 0) return HSG_OK;
+    bool two = false;
+    int tail = energy ? 1 : 0;  // pairs of the last launch, with the energies
+    for (const Group &g : h->lay.g) {
+        if (!pick(g)) continue;
+        two = two || way_of(h, g, 1, 2, false, route_count(g, false, r0, r1)) != Way::none;
+        if (energy) tail = std::max(tail, last_pass(h, g).pairs);
+    }
     int r = 0;
     hsg_status st = HSG_OK;
-    while (r < n_or && st == HSG_OK) {
-        if (any_quad && r + 1 < n_or) {
-            st = run_or_quad(h, energy && r + 2 == n_or, s, pick, r0, r1);
+    while (r < n_or - tail && st == HSG_OK) {
+        if (two && r + 1 < n_or - tail) {
+            st = run_or_quad(h, false, s, pick, r0, r1);
             r += 2;
         } else {
-            st = run_pair_of(h, 1, 0, energy && r + 1 == n_or, s, pick, r0, r1);
+            st = run_pair_of(h, 1, 0, false, s, pick, r0, r1);
             r += 1;
         }
     }
-    return st;
+    if (st != HSG_OK || !energy) return st;
+    return tail == 2 ? run_or_quad(h, true, s, pick, r0, r1) : run_pair_of(h, 1, 0, true, s, pick, r0, r1);
 }
 
 // Threads per replica of the replica launch, at most cap: whole waves for
@@ -891,17 +945,11 @@ hsg_status run_replica(hsg_lattice *h, hipStream_t s)
     return HSG_OK;
 }
 
-// Energy partial sums per replica that the last half-sweep of a sweep leaves for
-// group g: 0 where the energies themselves are written.
+// Energy partial sums per replica that a sweep's updates leave for group g: 0 where the
+// energies themselves are written.
 int energy_pb(const hsg_lattice *h, const Group &g)
 {
-    if (h->chain == 1 || use_replica(h, g)) return 0;
-    const int kind = h->n_or > 0 ? 1 : 0;  // of the last pass
-    const bool gather = use_gather(h, g, kind, g.n_rep);
-    const bool quad = h->n_or > 0 && h->n_or % 2 == 0 && (use_plane(h, g, 1, 2, true, g.n_rep) || (use_quad(h, g) && !gather));
-    if (use_plane(h, g, kind, quad ? 2 : 1, true, g.n_rep)) return 0;
-    if (gather) return g.n_pb_sweep;
-    return use_pair(h, g) ? 1 : g.s_ytiles * g.s_zslabs;
+    return h->chain == 1 || use_replica(h, g) ? 0 : last_pass(h, g).n_pb;
 }
 
 // Samples [d0, d1) of half c of group g (c < 0: all).

@@ -96,3 +96,22 @@ def test_few_replicas_bit_identical(hsg, L, D, O, T, storage, field, couplings, 
         c, _ = _run(hsg, [g], 0, storage, n_hb, n_or, math, **kw)
         for x, y in zip(c, a):
             assert torch.equal(x, y)
+
+
+# quantised angles, where two pairs go in one launch only in the walk of whole planes:
+# batches, a remainder and halves of so few replicas that their passes take another
+# route than the group's, which decides where the energies are left
+@pytest.mark.parametrize("L,D,O,T,field,kw",
+                         [(32, 8, 1, 65, None, {"batch": 64}), (32, 5, 1, 107, None, {"batch": 500}),
+                          (24, 8, 2, 33, None, {"batch": 50}), (28, 3, 2, 64, ("gaussian", 0.1), {"batch": 72}),
+                          (32, 2, 2, 32, ("gaussian", 0.1), {"overlap": True}),
+                          (24, 3, 1, 66, ("gaussian", 0.1), {"overlap": True})])
+@pytest.mark.parametrize("n_or", [2, 4])
+def test_energies_of_parts_of_a_size(hsg, L, D, O, T, field, kw, n_or):
+    g = _group(L, D, O, T, field, "gaussian")
+    a, E = _run(hsg, [g], 0, "qangle", 1, n_or, 0, **kw)
+    b, _ = _run(hsg, [g], 1, "qangle", 1, n_or, 0)
+    whole, _ = _run(hsg, [g], 0, "qangle", 1, n_or, 0)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
+    assert torch.allclose(a[3], E, rtol=1e-10, atol=1e-9)
+    assert torch.equal(a[3], whole[3])
