@@ -960,6 +960,16 @@ void sample_range(const Group &g, int c, int64_t &d0, int64_t &d1)
     d1 = c == 0 ? half : g.D;
 }
 
+// Lines of the end of a sweep, in us per sweep of L = 4 in float32. A work-group takes
+// one ladder up to 512 ladders and then as many as keep to 512 work-groups (as many as
+// its threads allow): 65536 ladders of one rung 2044 with a work-group each, 223 so;
+// 256, 1024 and 2048 work-groups measured the same. And up to 128 work-groups the last
+// one steps the sweep counter, beyond that a launch of its own does, since the
+// work-groups take their tickets at one address one after the other, about 15 ns each:
+// 16 ladders of 8 rungs 16.1 : 17.0 by its own launch, 128 of 32 rungs 26.9 : 27.2, 256
+// 42.1 : 41.0, 512 of one rung 20.8 : 15.9.
+constexpr int64_t kLadderBlocks = 512, kTickets = 128;
+
 // After the updates of a sweep (purpose 1: counter read from the device), or a
 // standalone tempering pass (purpose 2, counter ctr1): reduces the energy partials
 // when `reduce`, tempers when `pt`, accumulates the statistics when `stats` and
@@ -981,9 +991,11 @@ hsg_status run_sweep_end(hsg_lattice *h, bool reduce, bool pt, bool stats, bool 
         if (m.n_groups == 0) return HSG_OK;
         m.block_start[m.n_groups] = (int32_t)blocks;
         m.n_blocks = (int32_t)blocks;
-        m.advance = last && advance ? dev_counter(h) : nullptr;
+        const bool own_step = last && advance && blocks > kTickets;
+        m.advance = last && advance && !own_step ? dev_counter(h) : nullptr;
         m.ticket = dev_counter(h) + 2;
-        const hipError_t e = hsg::launch_sweep_end(m, s);
+        hipError_t e = hsg::launch_sweep_end(m, s);
+        if (e == hipSuccess && own_step) e = hsg::launch_advance(dev_counter(h), s);
         m.n_groups = 0;
         blocks = 0;
         if (e != hipSuccess) return hip_fail(e, "end of sweep launch");
@@ -1008,8 +1020,14 @@ hsg_status run_sweep_end(hsg_lattice *h, bool reduce, bool pt, bool stats, bool 
         a.O = g.O;
         a.T = g.T;
         a.uid_base = g.uid_base + (uint32_t)d0;
-        const int64_t nb = (d1 - d0) * g.O;
-        if (nb == 0) continue;
+        a.n_lad = (d1 - d0) * g.O;
+        if (a.n_lad == 0) continue;
+        a.seg_log2 = 8;
+        if (g.T <= 64)
+            for (a.seg_log2 = 0; 1 << a.seg_log2 < g.T;) ++a.seg_log2;
+        const int64_t share = (a.n_lad + kLadderBlocks - 1) / kLadderBlocks;
+        a.per_block = (int32_t)std::min<int64_t>(share, 256 >> a.seg_log2);
+        const int64_t nb = (a.n_lad + a.per_block - 1) / a.per_block;
         if (m.n_groups == hsg::kMaxStreamGroups || blocks + nb > 0x7FFFFFFFll) {
             const hsg_status st = flush(false);
             if (st != HSG_OK) return st;

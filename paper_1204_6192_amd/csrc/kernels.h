@@ -162,12 +162,12 @@ hipError_t launch_pack_jbits(const float *J_can, uint8_t *Jbits, int64_t D, int3
 hipError_t launch_reduce_partials(const double *partials, int n_pb, int64_t n_rep, double *E,
                                   hipStream_t s);
 
-// After the updates of a sweep, one work-group per (sample, copy) ladder of up to
-// kMaxStreamGroups groups (ladder.hip): E from n_pb partial sums per replica (0: E
-// is there already), with pt one tempering walk (draws at counter word *tptr, or
-// ctr1 where tptr is null, for the given purpose), with stats the run statistics,
-// and where advance is not null *advance = *tptr + 1, written by the last
-// work-group to finish; the ticket must be zero and is left so.
+// After the updates of a sweep, per_block (sample, copy) ladders per work-group, each
+// by 2^seg_log2 threads, of up to kMaxStreamGroups groups (ladder.hip): E from n_pb
+// partial sums per replica (0: E is there already), with pt one tempering walk (draws
+// at counter word *tptr, or ctr1 where tptr is null, for the given purpose), with
+// stats the run statistics, and where advance is not null *advance = *tptr + 1,
+// written by the last work-group to finish; the ticket must be zero and is left so.
 struct LadderArgs {
     int32_t *slot_at_temp;       // [D][O][T]
     int32_t *temp_of_slot;       // [D][O][T]
@@ -178,7 +178,9 @@ struct LadderArgs {
     double *stat_sum;            // [D][O][T][2] (E, E^2 by rung)
     int32_t *stat_flag;          // [D][O][T] by slot
     uint32_t *stat_trips;
+    int64_t n_lad;               // ladders, [D][O]
     int32_t O, T, n_pb;
+    int32_t seg_log2, per_block; // 2^seg_log2 >= T: at most 64 up to 64 rungs, else 256
     uint32_t uid_base;
 };
 struct MultiLadderArgs {

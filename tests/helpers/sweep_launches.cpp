@@ -130,7 +130,11 @@ hipError_t launch_sweep_end(const MultiLadderArgs &m, hipStream_t)
         while (k < g_h->lay.g.size() &&
                !(a.E >= energies(k) && a.E < energies(k) + g_h->lay.g[k].n_rep))
             ++k;
-        const int64_t r0 = a.E - energies(k), n = (int64_t)(m.block_start[i + 1] - m.block_start[i]) * a.T;
+        const int64_t r0 = a.E - energies(k), n = a.n_lad * a.T;
+        const int64_t blocks = m.block_start[i + 1] - m.block_start[i];
+        if (blocks * a.per_block < a.n_lad || (blocks - 1) * a.per_block >= a.n_lad || (a.per_block << a.seg_log2) > 256 ||
+            a.T > 1 << a.seg_log2)
+            bad("the ladders do not fit their work-groups");
         for (int64_t j = 0; j < n; ++j) {
             if (a.n_pb > 0) {
                 double e = 0.0;

@@ -111,3 +111,42 @@ def test_end_of_sweep(hsg, variant, L, rungs, t_max):
     for k, (x, g) in enumerate(zip(split(lat.get_temp_map(), lambda g: g.n_temps), groups)):
         assert np.array_equal(x, _walk(hsg, g, E[k], sat[k], 0, 2, seed)[0])
     lat.close()
+
+
+# More ladders than work-groups: several per work-group, of 1 to 64 rungs by as many
+# lanes as the next power of two, with a remainder; the same ladders in handles of at
+# most 512 ladders, a work-group each, must end with the same bits.
+@pytest.mark.parametrize("variant,L", [(0, 4), (4, 8), (1, 12)])
+@pytest.mark.parametrize("D,O,T,t_max", [(1031, 1, 1, 0.3), (700, 2, 2, 3.0), (520, 2, 5, 3.0), (1100, 1, 16, 3.0),
+                                         (600, 1, 33, 3.0), (520, 1, 64, 3.0), (520, 1, 65, 3.0), (700, 2, 2, 0.31),
+                                         (1040, 1, 5, 0.34)])
+def test_many_ladders(hsg, variant, L, D, O, T, t_max):
+    rng = np.random.Generator(np.random.Philox(inputs.INSTANCE_SEED_BASE + 93))
+    temps = inputs.geometric_ladder(0.3, t_max, T)
+    one = inputs.make_group(rng, L, D, 1, temps[:1])
+    seed = inputs.PHILOX_KEY_BASE + 93
+
+    def run(d0, d1):
+        g = inputs.Group(L=L, n_samples=d1 - d0, n_copies=O, temps=temps, J=one.J[d0:d1], H=None,
+                         spins0=np.broadcast_to(one.spins0[d0:d1], (d1 - d0, O, T, 3, L ** 3)).copy(), coupling_kind=0,
+                         sample_uid_base=d0)
+        lat = hsg.Lattice([g], n_hb=1, n_or=1, seed=seed)
+        lat.set_kernel(variant)
+        lat.set_stats(True)
+        lat.sweep(3)
+        sums, trips, _ = lat.get_stats()
+        out = [t.cpu().numpy().reshape(-1) for t in (lat.get_energies(), lat.get_temp_map(), lat.get_pt_accepts(), sums,
+                                                     trips)]
+        lat.pt_exchange()
+        out.append(lat.get_temp_map().cpu().numpy().reshape(-1))
+        assert lat.get_state()[0] == 3
+        lat.close()
+        return out
+
+    whole = run(0, D)
+    step = 512 // O
+    parts = [run(d, min(d + step, D)) for d in range(0, D, step)]
+    for k, x in enumerate(whole):
+        assert np.array_equal(x, np.concatenate([p[k] for p in parts])), k
+    if T >= 16 or 0.3 < t_max < 0.4:  # close rungs: swaps there must have been
+        assert whole[2].sum() > 0
