@@ -376,23 +376,40 @@ void drop_graphs(hsg_lattice *h)
     h->graph = nullptr;
 }
 
-// Slots per work item of the gather kernel: set, or 8, which spares the couplings'
-// loads, but fewer where that leaves less than eight work-groups per CU.
-int chunk_for(const hsg_lattice *h, const Group &g)
+// The work item of the gather kernel that replica r of a group belongs to: `chunk`
+// slots of one sample each, in the order of the replicas.
+int64_t gather_item(const Group &g, int64_t r, int chunk)
 {
-    const int spp = g.O * g.T;
-    int c = h->slots_per_item > 0 ? h->slots_per_item : 8;
-    if (h->slots_per_item == 0)
-        while (c > 1 && (int64_t)g.D * ((spp + c - 1) / c) * g.n_pb_sweep < 2048) c /= 2;
-    return c < spp ? c : spp;
+    const int64_t spp = (int64_t)g.O * g.T, d = r / spp;
+    return d * ((spp + chunk - 1) / chunk) + (r - d * spp) / chunk;
 }
 
+int64_t gather_items(const Group &g, int64_t r0, int64_t r1, int chunk)
+{
+    return gather_item(g, r1 - 1, chunk) - gather_item(g, r0, chunk) + 1;
+}
+
+// Slots per work item of the gather kernel: set, or 8, which spares the couplings'
+// loads, but fewer where that leaves the launch less than eight work-groups per CU.
+int chunk_for(const hsg_lattice *h, const Group &g, int64_t r0, int64_t r1)
+{
+    const int spp = g.O * g.T;
+    if (h->slots_per_item > 0) return std::min(h->slots_per_item, spp);
+    int c = 8;
+    while (c > 1 && gather_items(g, r0, r1, std::min(c, spp)) * g.n_pb_sweep < 2048) c /= 2;
+    return std::min(c, spp);
+}
+
+// The work items that hold replicas of [r0, r1) (r1 < 0: all): a batch or a half launches
+// no others, whose couplings it would load for nothing (256 replicas of L = 40 in
+// float32 in batches of 32 took 5758 us per sweep with the whole grid each).
 hsg::SweepArgs sweep_args(const hsg_lattice *h, const Group &g, int parity, uint32_t rep, int64_t r0 = 0,
                           int64_t r1 = -1)
 {
+    if (r1 < 0) r1 = g.n_rep;
     hsg::SweepArgs a{};
     a.r_begin = r0;
-    a.r_end = r1 < 0 ? g.n_rep : r1;
+    a.r_end = r1;
     a.spins = h->state + g.o_spins;
     a.J6 = reinterpret_cast<const float *>(h->coup + g.o_J6);
     a.Hp = g.field ? reinterpret_cast<const float *>(h->field + g.o_H) : nullptr;
@@ -404,10 +421,12 @@ hsg::SweepArgs sweep_args(const hsg_lattice *h, const Group &g, int parity, uint
     a.Lh = g.L / 2;
     a.slots_per_sample = g.O * g.T;
     a.T = g.T;
-    a.chunk = chunk_for(h, g);
+    a.chunk = chunk_for(h, g, r0, r1);
     a.n_chunks = (a.slots_per_sample + a.chunk - 1) / a.chunk;
     a.n_pb = g.n_pb_sweep;
-    a.n_blocks = g.D * a.n_chunks * a.n_pb;
+    a.item0 = gather_item(g, r0, a.chunk);
+    const int64_t nb = gather_items(g, r0, r1, a.chunk) * a.n_pb;
+    a.n_blocks = nb > 0x7FFFFFFFll ? -1 : (int32_t)nb;
     a.tptr = dev_counter(h);
     a.rep = rep;
     a.parity = (uint32_t)parity;
@@ -563,7 +582,7 @@ hsg_status run_groups(hsg_lattice *h, int kind, int parity, int rep, bool energy
             lds = l > lds ? l : lds;
         } else {
             const hsg::SweepArgs a = sweep_args(h, g, parity, (uint32_t)rep, r0, r1);
-            if ((int64_t)g.D * a.n_chunks * a.n_pb > 0x7FFFFFFFll) return fail(HSG_E_SIZE, "grid too large");
+            if (a.n_blocks < 0) return fail(HSG_E_SIZE, "grid too large");
             const hipError_t e = hsg::launch_half_sweep(a, h->storage, kind, g.field, energy, s);
             if (e != hipSuccess) return hip_fail(e, "half-sweep launch");
         }

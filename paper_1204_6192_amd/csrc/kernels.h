@@ -24,6 +24,7 @@ struct SweepArgs {
     const float *beta32;         // [T]
     double *e_partials;          // [replica][n_pb] when the pass computes energies
     int64_t r_begin, r_end;      // replicas of the launch
+    int64_t item0;               // first (sample, chunk) item of the launch, d n_chunks + chunk
     int64_t Nh;
     int32_t L, Lh;
     int32_t slots_per_sample;    // O * T

@@ -58,9 +58,9 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
 
     const int lb = xcd_remap((int)blockIdx.x, a.n_blocks);
     const int pb = lb % a.n_pb;
-    const int rest = lb / a.n_pb;
-    const int ch = rest % a.n_chunks;
-    const int d = rest / a.n_chunks;
+    const int64_t rest = a.item0 + lb / a.n_pb;
+    const int d = (int)(rest / a.n_chunks);
+    const int ch = (int)(rest - (int64_t)d * a.n_chunks);
     const int64_t Nh = a.Nh;
     const int64_t q = (int64_t)pb * kBlock + threadIdx.x;
     const bool active = q < (Nh >> 1);

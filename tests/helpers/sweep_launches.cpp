@@ -70,9 +70,18 @@ namespace hsg {
 hipError_t launch_half_sweep(const SweepArgs &a, int, int kind, bool, bool energy, hipStream_t)
 {
     const size_t k = group_of(a.spins);
-    for (int64_t r = a.r_begin; r < a.r_end; ++r) {
-        half_sweep(k, r, kind, a.rep, (int)a.parity, a.tptr);
-        if (energy) leave_partials(a.e_partials, k, r, a.n_pb);
+    if (a.n_blocks < 1 || a.n_blocks % a.n_pb != 0) bad("a gather pass with part of an item");
+    for (int64_t i = a.item0; i < a.item0 + a.n_blocks / a.n_pb; ++i) {
+        const int64_t d = i / a.n_chunks, ch = i - d * a.n_chunks;
+        bool any = false;
+        for (int64_t s = ch * a.chunk; s < std::min((ch + 1) * a.chunk, (int64_t)a.slots_per_sample); ++s) {
+            const int64_t r = d * a.slots_per_sample + s;
+            if (r < a.r_begin || r >= a.r_end) continue;
+            any = true;
+            half_sweep(k, r, kind, a.rep, (int)a.parity, a.tptr);
+            if (energy) leave_partials(a.e_partials, k, r, a.n_pb);
+        }
+        if (!any) bad("a gather pass with an item of no replica");
     }
     return hipSuccess;
 }
