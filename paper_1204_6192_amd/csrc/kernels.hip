@@ -48,7 +48,9 @@ __device__ __forceinline__ void neighbours(int64_t j, int32_t L, int32_t Lh, int
 // even number of sites per parity), and only the other x neighbour and the two y
 // neighbours site by site. Against loads of single components: an over-relaxation
 // pair of 128 replicas of L = 30 in float32 83 -> 49 us, of 32 replicas 25 -> 17;
-// bfloat16 55 -> 34 and 19 -> 13.
+// bfloat16 55 -> 34 and 19 -> 13. Couplings and field in 16-byte loads as they stand,
+// against single elements of them: a sweep of 88 replicas of L = 34 in float32 with a
+// field 322 -> 232 us.
 template <int STORE, int KIND, bool FIELD, bool ENERGY>
 __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
 {
@@ -69,7 +71,7 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
     int64_t zp = 0, zm = 0;       // the pairs above and below
     int64_t xo[2], yp[2], ym[2];  // per site: the x neighbour at another half-index, y neighbours
     bool plus[2];                 // that x neighbour is the one at x + 1
-    float Jc[2][6];
+    float2 Jc[6] = {};
     v3 Hs[2] = {v3{0.f, 0.f, 0.f}, v3{0.f, 0.f, 0.f}};
     v3 He[2] = {v3{0.f, 0.f, 0.f}, v3{0.f, 0.f, 0.f}};
     if (active) {
@@ -86,18 +88,13 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
                 zp = nb[4];
                 zm = nb[5];
             }
-            const float *Jb = a.J6 + ((int64_t)d * 2 + p) * 6 * Nh;
-#pragma unroll
-            for (int n = 0; n < 6; ++n) Jc[k][n] = Jb[coupling_at(n, j, Nh)];
-            if (FIELD) {
-                const float *Hb = a.Hp + ((int64_t)d * 2 + p) * 3 * Nh;
-                Hs[k] = v3{Hb[field_at(0, j, Nh)], Hb[field_at(1, j, Nh)], Hb[field_at(2, j, Nh)]};
-                if (ENERGY) {  // the field on the other parity at the same half-index
-                    const float *Ho = a.Hp + ((int64_t)d * 2 + (1 - p)) * 3 * Nh;
-                    He[k] = v3{Ho[field_at(0, j, Nh)], Ho[field_at(1, j, Nh)], Ho[field_at(2, j, Nh)]};
-                }
-            }
         }
+        const uint32_t cs32 = (uint32_t)Nh, j0 = (uint32_t)(2 * q);
+        const float *Hd = FIELD ? a.Hp + (int64_t)d * 6 * Nh : nullptr;
+        load_couplings<false, FIELD>(a.J6 + ((int64_t)d * 2 + p) * 6 * Nh, nullptr, FIELD ? Hd + p * 3 * Nh : nullptr,
+                                     false, true, cs32, j0, Jc, Hs[0], Hs[1]);
+        // the field on the other parity at the same half-indices
+        if (FIELD && ENERGY) load_field_pair<false>(Hd + (1 - p) * 3 * Nh, cs32, j0, He[0], He[1]);
     }
 
     T *spins = (T *)a.spins;
@@ -134,11 +131,12 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
                 double hx = Hs[k].x, hy = Hs[k].y, hz = Hs[k].z;
 #pragma unroll
                 for (int n = 0; n < 6; ++n) {
-                    acc3(h, Jc[k][n], sn[n]);
+                    const float J = k ? Jc[n].y : Jc[n].x;
+                    acc3(h, J, sn[n]);
                     if (ENERGY) {
-                        hx = fma((double)Jc[k][n], (double)sn[n].x, hx);
-                        hy = fma((double)Jc[k][n], (double)sn[n].y, hy);
-                        hz = fma((double)Jc[k][n], (double)sn[n].z, hz);
+                        hx = fma((double)J, (double)sn[n].x, hx);
+                        hy = fma((double)J, (double)sn[n].y, hy);
+                        hz = fma((double)J, (double)sn[n].z, hz);
                     }
                 }
                 if (KIND != 1)
