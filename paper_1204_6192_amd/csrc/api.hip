@@ -513,27 +513,45 @@ int64_t route_count(const Group &g, bool energy, int64_t r0, int64_t r1)
     return energy || r1 < 0 ? g.n_rep : r1 - r0;
 }
 
-// Single half-sweeps by the gather kernel, whose work-groups split a replica, where
-// the marches along z would leave CUs idle in a launch of n replicas: a march is a
-// chain of L steps however few replicas there are, a gather pass of some replicas
-// lasts 6 us. Measured in us, gather against the march that takes the work otherwise:
-//   L <= 32 (whole planes per work-group): two pairs L = 32 f32 8 replicas 24 : 41,
-//     32 33 : 42, 64 59 : 44; bf16 64 39 : 44, 96 53 : 45; heat bath 8 replicas
-//     15 : 83, 192 74 : 91 (f32), 58 : 88 (bf16); a whole sweep of 8 58 : 173.
-//   above (z-slabs), by sites: a pair L = 40 f32 32 replicas (2.0 M) 30 : 42, 64
-//     51 : 45, bf16 64 (4.1 M) 34 : 45, 128 54 : 55; heat bath f32 96 (6.1 M)
-//     76 : 86, bf16 128 (8.2 M) 71 : 91. Where rows make whole waves (L % 64 == 0)
-//     the march is faster: L = 64 f32 a pair 8 (2.1 M) 31 : 36, 16 53 : 39, heat
-//     bath 16 (4.2 M) 57 : 63, 32 101 : 78; bf16 a pair 16 34 : 36, 32 54 : 47.
-bool use_gather(const hsg_lattice *h, const Group &g, int kind, int64_t n)
+// Rows of the tables of lines below: float32, 16-bit spins, quantised angles.
+int store_class(const hsg_lattice *h)
+{
+    return h->storage == HSG_STORE_F32 ? 0 : h->storage == HSG_STORE_QANGLE ? 2 : 1;
+}
+
+// Half-sweeps by the gather kernel, whose work-groups split a replica, where the
+// marches along z would leave CUs idle in a launch of n replicas: a march is a chain of
+// L steps however few replicas there are, a gather pass of some replicas lasts 6 us.
+// The lines are where the two took the same time, both measured for 28 sizes from L = 24
+// to 128, 2 to 4096 replicas (4638 points: float32, bfloat16, quantised angles, with and
+// without a field, 2 and 32 replicas to a sample). By these lines and use_plane's a
+// launch takes on average 0 to 2 % longer than by the best way at each point (a pair of
+// compressed spins with a field 3 to 6 %). In us, gather against the best other way:
+//   L <= 32, over-relaxation by replicas: two pairs L = 32 f32 32 replicas 33 : 42, 64
+//     55 : 41; a pair L = 24 bf16 96 18 : 24, 256 31 : 25; the heat bath by sites: f32
+//     L = 24 256 replicas (3.5 M) 50 : 64, L = 32 256 (8.4 M) 84 : 84, 384 (12.6 M)
+//     134 : 106.
+//   above, by sites: a pair f32 L = 48 32 replicas (3.5 M) 45 : 46, bf16 L = 72 16 (6.0 M)
+//     39 : 42, L = 36 256 (11.9 M) 67 : 46; the heat bath f32 L = 44 96 (8.2 M) 88 : 89,
+//     bf16 L = 40 224 (14.3 M) 115 : 124, L = 48 160 (17.7 M) 149 : 130. Where rows make
+//     whole waves (L % 64 == 0) the march is faster: L = 64, a pair f32 12 (3.1 M)
+//     41 : 37, bf16 24 (6.3 M) 41 : 42, 32 51 : 45, the heat bath f32 24 74 : 70, bf16 32
+//     (8.4 M) 80 : 71.
+bool use_gather(const hsg_lattice *h, const Group &g, int kind, int pairs, int64_t n)
 {
     if (!use_stream(h, g)) return true;
     if ((h->kernel_variant != 0 && h->kernel_variant < 4) || g.L < 24) return false;
-    const bool f32 = h->storage == HSG_STORE_F32, waves = g.L % 64 == 0;
-    if (g.L <= 32) return n <= (kind != 1 ? 192 : f32 ? 48 : 72);
-    const int64_t sites = n * g.L * g.L * g.L;
-    if (kind == 1) return sites <= (f32 ? (waves ? 2400000 : 3200000) : (waves ? 4200000 : 6000000));
-    return sites <= (f32 ? (waves ? 4500000 : 6000000) : (waves ? 6000000 : 8000000));
+    const int c = store_class(h);
+    const int64_t sites = n * g.N;
+    const bool waves = g.L % 64 == 0;
+    if (g.L <= 32) {
+        static constexpr int64_t or_line[2][2][3] = {{{64, 128, 192}, {160, 320, 384}},  // a pair: no field, field
+                                                     {{48, 64, 96}, {64, 128, 160}}};    // two pairs
+        if (kind == 1) return n <= or_line[pairs - 1][g.field ? 1 : 0][c];
+        return sites <= (c == 0 ? 9000000 : 15000000);
+    }
+    if (kind == 1) return sites <= (c == 0 ? (waves ? 2800000 : 3400000) : (waves ? 6500000 : 9000000));
+    return sites <= (c == 0 ? (waves ? 5500000 : 9000000) : (waves ? 7000000 : 13000000));
 }
 
 // Launches one half-sweep of parity `parity` (fuse = 0), one fused pair
@@ -565,7 +583,7 @@ hsg_status run_groups(hsg_lattice *h, int kind, int parity, int rep, bool energy
     };
     for (const Group &g : h->lay.g) {
         if (!pick(g)) continue;
-        if (fuse || (use_stream(h, g) && !use_gather(h, g, kind, route_count(g, energy, r0, r1)))) {
+        if (fuse || (use_stream(h, g) && !use_gather(h, g, kind, 1, route_count(g, energy, r0, r1)))) {
             if (m.n_groups == hsg::kMaxStreamGroups) {
                 hsg_status st = flush();
                 if (st != HSG_OK) return st;
@@ -602,45 +620,64 @@ size_t plane_lds_bytes(const Group &g, int groups) { return (size_t)(groups == 1
 // (1024 and 256 threads) and the staged planes its LDS, and where that is the faster
 // way for a launch of n replicas. A work-group walks one replica, so a launch of
 // fewer replicas than CUs takes as long as one of 256, and where a work-group has 9
-// to 16 waves a CU holds one: its time goes by rounds of 256. Measured in us, this
-// walk against the kernel that takes the work otherwise:
-//   L % 4 == 2, against gather passes (which split a replica over work-groups):
-//     two pairs L = 30: f32 32 replicas 48 : 33, 64 48 : 59, 256 54 : 176;
-//     bf16 64 49 : 38, 128 49 : 65. A pair L = 46: f32 64 87 : 79, 128 131 : 164;
-//     bf16 64 72 : 55, 128 73 : 91. Heat bath L = 30: 128 82 : 51, 256 85 : 89;
-//     L = 62: 256 410 : 757. With 256 + 44 replicas of L = 62 bf16 the second round
-//     is empty enough for 606 : 510.
-//   L <= 32, L % 4 == 0, against the fused marches, L = 32: heat bath 256 replicas
-//     84 : 109, 8192 1757 : 1804 (f32), 1451 : 1595 (bf16), but with a field
-//     2048 550 : 528. Two pairs f32 256 64 : 80, 1024 306 : 311, 8192 2377 : 2170
-//     (there the fused march keeps more bytes in flight), with energies, whose sums
-//     cost this walk's 128 registers more, 256 75 : 79, 1024 324 : 294; with a field
-//     1024 401 : 435, 8192 3069 : 3320, its sweep 8475 : 9322; bf16 1024 226 : 260,
-//     8192 1724 : 1779; f16 with a field 2048 623 : 815. A pair 256 46 : 51, 2048
-//     507 : 486 (f32).
-//   L = 36 to 64, L % 4 == 0, against two single passes: a pair of L = 64 f32 96
-//     replicas 339 : 230, 192 379 : 495, 768 1489 : 1993; bf16 768 986 : 1258;
-//     L = 40 f32 192 89 : 114; with a field L = 64 f32 192 400 : 451, f16 574 : 547.
-//     Heat bath L = 64 f32 256 420 : 526, bf16 192 338 : 306, 768 1160 : 1198;
-//     L = 40 f32 768 350 : 424; L = 48 (9 waves, so 9 of a CU's 16) bf16 592 : 528.
+// to 16 waves a CU holds one: its time goes by rounds of 256. The lines are drawn as
+// use_gather's are. In us, this walk against the best of the other ways:
+//   L % 4 == 2, against gather passes: two pairs L = 30 f32 96 replicas 49 : 67, with a
+//     field 79 : 69, 160 83 : 103; a pair f32 L = 46 96 89 : 94, 320 (of 512 slots)
+//     308 : 384, with a field 192 242 : 245, 256 264 : 322. The heat bath f32 L = 50 160
+//     224 : 234, L = 34 448 152 : 194; compressed spins gain from 512 on, but not in
+//     work-groups of 5 and 6 waves (L = 34, 38); with a field nothing does (f32 L = 34
+//     1024 661 : 462).
+//   L <= 32, L % 4 == 0: two pairs f32 L = 32 256 replicas 64 : 80, 1024 309 : 293, 8192
+//     2377 : 2170 (there the fused march keeps more bytes in flight), with energies,
+//     whose sums cost this walk's 128 registers more, 1024 324 : 294; with a field 8192
+//     3069 : 3320; quantised angles L = 24 768 86 : 116, with a field 1024 and above 1 to
+//     1.3 of the fused march's time, but less with the energies, which cost that march
+//     more. A pair f32 256 46 : 51, 2048 507 : 486; bf16 L = 28 1024 113 : 135. With a
+//     field a pair and the heat bath are the march's (f32 2048 550 : 528).
+//   L = 36 to 64, L % 4 == 0, against single passes: a pair f32 L = 44 160 replicas
+//     114 : 128, with a field L = 36 224 105 : 113, L = 64 256 486 : 673; bf16 L = 40 192
+//     49 : 61; compressed with a field 0.8 to 1.3 of their time, not by any simple line;
+//     quantised angles L = 48 (9 waves) 384 185 : 149, 512 259 : 304.
+//     The heat bath f32 L = 40 768 350 : 424, L = 36 (6 waves) 384 178 : 151; bf16 L = 64
+//     256 362 : 389, L = 48 (9 waves, so 9 of a CU's 16) 592 : 528; quantised angles
+//     L = 36 384 199 : 152, L = 64 256 404 : 390.
 bool use_plane(const hsg_lattice *h, const Group &g, int kind, int groups, bool energy, int64_t n)
 {
     if ((h->kernel_variant != 0 && h->kernel_variant < 4) || g.L < 24) return false;
     const int pp = (g.L / 2) * (g.L / 2), waves = (pp + 63) / 64;
     if (pp > (groups == 1 ? 1024 : 256) || plane_lds_bytes(g, groups) + 256 > h->max_lds) return false;
-    const bool f32 = h->storage == HSG_STORE_F32;
+    const int c = store_class(h);
+    const bool several = waves <= 8;  // a CU holds more than one work-group
     const int64_t slots = 256 * ((n + 255) / 256);  // of whole rounds
+    const bool full = 20 * n >= 19 * slots;
     if (!g.stream_ok) {
-        const int64_t least = kind == 0 ? 256 : f32 ? 96 : 128;
-        return n >= least && (waves <= 8 || n <= 256 || 4 * n >= 3 * slots);
+        if (kind == 0) {
+            if (g.field) return false;
+            if (several) return c == 0 ? n >= 384 : n >= 512 && waves != 5 && waves != 6;
+            return c == 0 ? n >= 144 && (n <= 256 || 4 * n >= 3 * slots) : waves >= 13 && n >= 208 && (n <= 256 || full);
+        }
+        static constexpr int64_t least[3][2][3] = {{{96, 112, 144}, {112, 144, 176}},   // two pairs: no field, field
+                                                   {{96, 192, 192}, {256, 384, 384}},   // a pair, several per CU
+                                                   {{96, 144, 144}, {176, 208, 208}}};  // a pair, one per CU
+        if (n < least[groups == 2 ? 0 : several ? 1 : 2][g.field ? 1 : 0][c]) return false;
+        if (groups == 2 || several || n <= 256) return true;
+        return c == 0 && !g.field ? true : c == 0 || !g.field ? 4 * n >= 3 * slots : full;
     }
-    if (use_gather(h, g, kind, n)) return false;
+    if (use_gather(h, g, kind, groups, n)) return false;
     if (g.L <= 32) {
-        if (groups == 2) return !f32 || g.field || n <= (energy ? 512 : 1024);
-        return !g.field && (kind == 0 || n <= 512);
+        if (groups == 2 && c == 0) return g.field || n <= (energy ? 512 : 1024);
+        if (groups == 2) return c == 1 || !g.field || g.L >= 28 || energy || n <= 768;
+        return !g.field && (kind == 0 || c != 0 || n <= 512);
     }
-    if (kind == 1) return (!g.field || f32) && (waves <= 8 ? n >= 192 : 4 * n >= 3 * slots);
-    return !g.field && (waves <= 8 || waves >= 13) && 20 * n >= 19 * slots;
+    if (kind == 1) {
+        if (g.field && c != 0) return false;
+        if (several) return n >= (g.field ? 224 : 160);
+        return c == 2 && waves < 13 ? full : 4 * n >= 3 * slots;
+    }
+    if (g.field || c == 2) return false;
+    if (several) return c == 0 && waves != 6 && (n >= 384 || full);
+    return waves >= 13 && full;
 }
 
 // groups = 1: a pair of half-sweeps of the given kind; 2: two over-relaxation pairs,
@@ -716,7 +753,7 @@ enum class Way { none, plane, fused, march, gather };
 Way way_of(const hsg_lattice *h, const Group &g, int kind, int pairs, bool energy, int64_t n)
 {
     if (use_plane(h, g, kind, pairs, energy, n)) return Way::plane;
-    const bool gather = use_gather(h, g, kind, n);
+    const bool gather = use_gather(h, g, kind, pairs, n);
     if (pairs == 2) return use_quad(h, g) && !gather ? Way::fused : Way::none;
     return gather ? Way::gather : use_pair(h, g) ? Way::fused : Way::march;
 }
@@ -2056,8 +2093,8 @@ hsg_status hsg_autotune(hsg_lattice *h, int32_t n_sweeps, void *d_backup, int32_
         h->kernel_variant = 4;
         bool any = false;  // a launch that only variant 4 makes
         for (const Group &g : h->lay.g) {
-            any = any || (h->n_hb > 0 && (use_plane(h, g, 0, 1, false, g.n_rep) || (g.stream_ok && use_gather(h, g, 0, g.n_rep))));
-            any = any || (h->n_or > 0 && (use_plane(h, g, 1, 1, false, g.n_rep) || (g.stream_ok && use_gather(h, g, 1, g.n_rep))));
+            any = any || (h->n_hb > 0 && (use_plane(h, g, 0, 1, false, g.n_rep) || (g.stream_ok && use_gather(h, g, 0, 1, g.n_rep))));
+            any = any || (h->n_or > 0 && (use_plane(h, g, 1, 1, false, g.n_rep) || (g.stream_ok && use_gather(h, g, 1, 1, g.n_rep))));
             any = any || (h->n_or >= 2 && (use_quad(h, g) || use_plane(h, g, 1, 2, false, g.n_rep)));
         }
         h->kernel_variant = v0;
