@@ -468,9 +468,9 @@ struct Codec<1> {  // float16 components (round to nearest even), renormalised o
     }
     __device__ static __forceinline__ v3 load32(const T *p, uint32_t, uint32_t at, uint32_t j)
     {
-        const uint32_t q = at + 6 * (j >> 1) + (j & 1);
-        return normalise_rsq(v3{__half2float(*elem<true>(p, q)), __half2float(*elem<true>(p, q + 2)),
-                                __half2float(*elem<true>(p, q + 4))});
+        v3 a, b;
+        components(*reinterpret_cast<const R *>(elem<true>(p, at + 6 * (j >> 1))), a, b);
+        return normalise_rsq((j & 1) ? b : a);
     }
     __device__ static __forceinline__ void store(T *p, int64_t, int64_t j, v3 s)
     {
@@ -561,9 +561,9 @@ struct Codec<2> {  // bfloat16 components, renormalised on load
     }
     __device__ static __forceinline__ v3 load32(const T *p, uint32_t, uint32_t at, uint32_t j)
     {
-        const uint32_t q = at + 6 * (j >> 1) + (j & 1);
-        return normalise_rsq(v3{bf16_to_f32(*elem<true>(p, q)), bf16_to_f32(*elem<true>(p, q + 2)),
-                                bf16_to_f32(*elem<true>(p, q + 4))});
+        v3 a, b;
+        components(*reinterpret_cast<const R *>(elem<true>(p, at + 6 * (j >> 1))), a, b);
+        return normalise_rsq((j & 1) ? b : a);
     }
     __device__ static __forceinline__ void store(T *p, int64_t, int64_t j, v3 s)
     {

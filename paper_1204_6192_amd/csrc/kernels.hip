@@ -16,37 +16,73 @@ struct Site {
     int32_t x, y, z;
 };
 
-// Neighbours (in the other parity's half-index space) of the parity-p site
-// with half-index j, in the order +x, -x, +y, -y, +z, -z.
-__device__ __forceinline__ void neighbours(int64_t j, int32_t L, int32_t Lh, int p, int64_t nb[6])
+// Where the neighbours of the pair (2q, 2q + 1) of a parity stand. The ones beside it at
+// the same half-index (one of each site's two x neighbours) and the planes above and
+// below come as pairs, whatever L is (a plane holds an even number of sites per parity);
+// only the other x neighbour and the two y neighbours are read site by site.
+struct GatherPos {
+    uint32_t zp, zm;               // the pairs above and below
+    uint32_t xo[2], yp[2], ym[2];  // per site: the x neighbour at another half-index, y neighbours
+    bool plus[2];                  // that x neighbour is the one at x + 1
+};
+
+// One division for the pair: Nh <= 2^29, and both sites are in one plane.
+__device__ __forceinline__ GatherPos gather_pos(uint32_t q, int32_t L, int32_t Lh, int p)
 {
-    const int32_t r = (int32_t)(j / Lh);
-    const int32_t xh = (int32_t)(j - (int64_t)r * Lh);
-    const int32_t y = r % L, z = r / L;
-    const int o = (y + z + p) & 1;  // x = 2 xh + o
-    const int32_t xp = o ? (xh + 1 == Lh ? 0 : xh + 1) : xh;
-    const int32_t xm = o ? xh : (xh == 0 ? Lh - 1 : xh - 1);
-    const int32_t yp = (y + 1 == L) ? 0 : y + 1, ym = (y == 0) ? L - 1 : y - 1;
-    const int32_t zp = (z + 1 == L) ? 0 : z + 1, zm = (z == 0) ? L - 1 : z - 1;
-    const int64_t row = (int64_t)r * Lh;
-    nb[0] = row + xp;
-    nb[1] = row + xm;
-    nb[2] = ((int64_t)z * L + yp) * Lh + xh;
-    nb[3] = ((int64_t)z * L + ym) * Lh + xh;
-    nb[4] = ((int64_t)zp * L + y) * Lh + xh;
-    nb[5] = ((int64_t)zm * L + y) * Lh + xh;
+    GatherPos g;
+    const uint32_t Lu = (uint32_t)L, Lhu = (uint32_t)Lh, cst = Lu * Lhu, j = 2 * q, r = j / Lhu, z = r / Lu;
+    uint32_t y = r - z * Lu, xh = j - r * Lhu;
+    g.zp = z + 1 == Lu ? j + cst - Lu * cst : j + cst;
+    g.zm = z == 0 ? j - cst + Lu * cst : j - cst;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const uint32_t at = j + (uint32_t)k;
+        const bool o = (y + z + (uint32_t)p) & 1u;  // x = 2 xh + o
+        g.plus[k] = o;
+        g.xo[k] = o ? (xh + 1 == Lhu ? at + 1 - Lhu : at + 1) : (xh == 0 ? at + Lhu - 1 : at - 1);
+        g.yp[k] = y + 1 == Lu ? at + Lhu - cst : at + Lhu;
+        g.ym[k] = y == 0 ? at + cst - Lhu : at - Lhu;
+        if (xh + 1 == Lhu) {
+            xh = 0;
+            ++y;
+        } else {
+            ++xh;
+        }
+    }
+    return g;
 }
+
+// The spins of the other parity beside the pair (same) and in the planes above and below.
+template <int STORE>
+struct GatherPairs {
+    v3 same[2], up[2], dn[2];
+    __device__ __forceinline__ void load(const typename Codec<STORE>::T *oth, uint32_t Nh, uint32_t j0, const GatherPos &g)
+    {
+        Codec<STORE>::load_pair(oth, Nh, j0, same[0], same[1]);
+        Codec<STORE>::load_pair(oth, Nh, g.zp, up[0], up[1]);
+        Codec<STORE>::load_pair(oth, Nh, g.zm, dn[0], dn[1]);
+    }
+    // the six neighbours of site k, in the order +x, -x, +y, -y, +z, -z
+    __device__ __forceinline__ void site(const typename Codec<STORE>::T *oth, int64_t Nh, const GatherPos &g, int k,
+                                         v3 (&sn)[6]) const
+    {
+        const v3 x = Codec<STORE>::load(oth, Nh, g.xo[k]);
+        sn[0] = g.plus[k] ? x : same[k];
+        sn[1] = g.plus[k] ? same[k] : x;
+        sn[2] = Codec<STORE>::load(oth, Nh, g.yp[k]);
+        sn[3] = Codec<STORE>::load(oth, Nh, g.ym[k]);
+        sn[4] = up[k];
+        sn[5] = dn[k];
+    }
+};
 
 // ---------------------------------------------------------------- half-sweep
 // One thread owns the two parity-p sites with half-indices 2q and 2q + 1 (they
 // share Philox block q) and walks `chunk` replicas of one sample, keeping the
 // sample's couplings and field in registers. Grid: samples x replica chunks x
 // blocks of 256 site pairs, remapped so each XCD gets contiguous work.
-// Bound by the number of vector loads, not by their width: the pair's own spins,
-// the ones beside it at the same half-index (one of each site's two x neighbours)
-// and the planes above and below come as pairs, whatever L is (a plane holds an
-// even number of sites per parity), and only the other x neighbour and the two y
-// neighbours site by site. Against loads of single components: an over-relaxation
+// Bound by the number of vector loads, not by their width: what stands together comes
+// in pairs (GatherPos). Against loads of single components: an over-relaxation
 // pair of 128 replicas of L = 30 in float32 83 -> 49 us, of 32 replicas 25 -> 17;
 // bfloat16 55 -> 34 and 19 -> 13. Couplings and field in 16-byte loads as they stand,
 // against single elements of them: a sweep of 88 replicas of L = 34 in float32 with a
@@ -68,27 +104,12 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
     const bool active = q < (Nh >> 1);
     const int p = (int)a.parity;
 
-    int64_t zp = 0, zm = 0;       // the pairs above and below
-    int64_t xo[2], yp[2], ym[2];  // per site: the x neighbour at another half-index, y neighbours
-    bool plus[2];                 // that x neighbour is the one at x + 1
+    GatherPos pos{};
     float2 Jc[6] = {};
     v3 Hs[2] = {v3{0.f, 0.f, 0.f}, v3{0.f, 0.f, 0.f}};
     v3 He[2] = {v3{0.f, 0.f, 0.f}, v3{0.f, 0.f, 0.f}};
     if (active) {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int64_t j = 2 * q + k;
-            int64_t nb[6];
-            neighbours(j, a.L, a.Lh, p, nb);
-            plus[k] = nb[0] != j;
-            xo[k] = plus[k] ? nb[0] : nb[1];
-            yp[k] = nb[2];
-            ym[k] = nb[3];
-            if (k == 0) {
-                zp = nb[4];
-                zm = nb[5];
-            }
-        }
+        pos = gather_pos((uint32_t)q, a.L, a.Lh, p);
         const uint32_t cs32 = (uint32_t)Nh, j0 = (uint32_t)(2 * q);
         const float *Hd = FIELD ? a.Hp + (int64_t)d * 6 * Nh : nullptr;
         load_couplings<false, FIELD>(a.J6 + ((int64_t)d * 2 + p) * 6 * Nh, nullptr, FIELD ? Hd + p * 3 * Nh : nullptr,
@@ -117,16 +138,14 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
                 r = philox4x32_10(u32x4{(uint32_t)q, tsweep, c2, a.uid_base + (uint32_t)d}, a.key0, a.key1);
             }
             const uint32_t cs32 = (uint32_t)Nh, j0 = (uint32_t)(2 * q);
-            v3 same[2], up[2], dn[2], s1[2];
-            C::load_pair(oth, cs32, j0, same[0], same[1]);
-            C::load_pair(oth, cs32, (uint32_t)zp, up[0], up[1]);
-            C::load_pair(oth, cs32, (uint32_t)zm, dn[0], dn[1]);
+            v3 s1[2];
+            GatherPairs<STORE> gp;
+            gp.load(oth, cs32, j0, pos);
             if (KIND == 1) C::load_pair(own, cs32, j0, s1[0], s1[1]);
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-                const v3 x = C::load(oth, Nh, xo[k]);
-                const v3 sn[6] = {plus[k] ? x : same[k], plus[k] ? same[k] : x, C::load(oth, Nh, yp[k]),
-                                  C::load(oth, Nh, ym[k]), up[k], dn[k]};
+                v3 sn[6];
+                gp.site(oth, Nh, pos, k, sn);
                 v3 h = Hs[k];
                 double hx = Hs[k].x, hy = Hs[k].y, hz = Hs[k].z;
 #pragma unroll
@@ -148,7 +167,8 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep(SweepArgs a)
                     const v3 sv = C::stored_value(s1[k]);
                     e -= (double)sv.x * hx + (double)sv.y * hy + (double)sv.z * hz;
                     if (FIELD)
-                        e -= (double)He[k].x * same[k].x + (double)He[k].y * same[k].y + (double)He[k].z * same[k].z;
+                        e -= (double)He[k].x * gp.same[k].x + (double)He[k].y * gp.same[k].y +
+                             (double)He[k].z * gp.same[k].z;
                 }
             }
             C::store_pair(own, cs32, j0, s1[0], s1[1]);
@@ -468,42 +488,56 @@ hipError_t launch_pack_field(const PackArgs &a, hipStream_t s)
 // ---------------------------------------------------------------- energy
 // Exact float64 energy of Eq. (1): every bond has one even endpoint, so the sum
 // over even sites of s_i . sum_n J_n s_n counts each bond once; the field term
-// runs over both parities at the same half-index.
+// runs over both parities at the same half-index. A thread takes a pair of even sites
+// and a work-group of 128 threads the 256 sites of a partial sum, neighbouring work-groups
+// on one XCD. Bound by the vector loads, which pairs halve against a site per thread:
+// 1024 replicas of L = 30 with a field in float32 232 -> 140 us, bfloat16 168 -> 102, 256
+// of L = 18 without 17 -> 13.
 template <int STORE>
-__global__ __launch_bounds__(kBlock) void k_energy(EnergyArgs a)
+__global__ __launch_bounds__(kBlock / 2) void k_energy(EnergyArgs a)
 {
     using C = Codec<STORE>;
     using T = typename C::T;
-    __shared__ double red[4];
-    const int64_t rep = blockIdx.x / a.n_pb;
-    const int pb = (int)(blockIdx.x - rep * a.n_pb);
+    __shared__ double red[2];
+    const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
+    const int64_t rep = b / a.n_pb;
+    const int pb = (int)(b - rep * a.n_pb);
     const int64_t Nh = a.Nh;
-    const int64_t j = (int64_t)pb * kBlock + threadIdx.x;
+    const int64_t q = (int64_t)pb * (kBlock / 2) + threadIdx.x;
     const int64_t d = rep / a.slots_per_sample;
     double e = 0.0;
-    if (j < Nh) {
-        const T *base = (const T *)a.spins + rep * 2 * C::kPlanes * Nh;
-        int64_t nb[6];
-        neighbours(j, a.L, a.Lh, 0, nb);
-        const v3 s0 = C::load(base, Nh, j);
-        const float *J6 = a.J6 + (d * 2 + 0) * 6 * Nh;
-        for (int n = 0; n < 6; ++n) {
-            const v3 sn = C::load(base + C::kPlanes * Nh, Nh, nb[n]);
-            const double sd = (double)s0.x * sn.x + (double)s0.y * sn.y + (double)s0.z * sn.z;
-            e -= (double)J6[coupling_at(n, j, Nh)] * sd;
-        }
+    if (q < (Nh >> 1)) {
+        const T *even = (const T *)a.spins + rep * 2 * C::kPlanes * Nh, *odd = even + C::kPlanes * Nh;
+        const uint32_t cs32 = (uint32_t)Nh, j0 = (uint32_t)(2 * q);
+        const GatherPos pos = gather_pos((uint32_t)q, a.L, a.Lh, 0);
+        float2 J[6];
+        v3 h0, h1;  // (zero: the field is read below)
+        load_couplings<false, false>(a.J6 + d * 12 * Nh, nullptr, nullptr, false, false, cs32, j0, J, h0, h1);
+        v3 s[2];
+        GatherPairs<STORE> gp;
+        gp.load(odd, cs32, j0, pos);
+        C::load_pair(even, cs32, j0, s[0], s[1]);
+        v3 sn[2][6];
+        gp.site(odd, Nh, pos, 0, sn[0]);
+        gp.site(odd, Nh, pos, 1, sn[1]);
+        __builtin_amdgcn_sched_barrier(0);  // every load goes out before the first is waited for
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int n = 0; n < 6; ++n) {
+                const double sd =
+                    (double)s[k].x * sn[k][n].x + (double)s[k].y * sn[k][n].y + (double)s[k].z * sn[k][n].z;
+                e -= (double)(k ? J[n].y : J[n].x) * sd;
+            }
         if (a.Hp != nullptr) {
-            const v3 s1 = C::load(base + C::kPlanes * Nh, Nh, j);
-            const float *H0 = a.Hp + (d * 2 + 0) * 3 * Nh;
-            const float *H1 = a.Hp + (d * 2 + 1) * 3 * Nh;
-            e -= (double)H0[field_at(0, j, Nh)] * s0.x + (double)H0[field_at(1, j, Nh)] * s0.y +
-                 (double)H0[field_at(2, j, Nh)] * s0.z;
-            e -= (double)H1[field_at(0, j, Nh)] * s1.x + (double)H1[field_at(1, j, Nh)] * s1.y +
-                 (double)H1[field_at(2, j, Nh)] * s1.z;
+            field_energy<false>(s[0], s[1], a.Hp + d * 6 * Nh, cs32, j0, e);
+            field_energy<false>(gp.same[0], gp.same[1], a.Hp + (d * 2 + 1) * 3 * Nh, cs32, j0, e);
         }
     }
-    const double tot = block_sum(e, red);
-    if (threadIdx.x == 0) a.partials[rep * a.n_pb + pb] = tot;
+    e = wave_sum(e);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
+    __syncthreads();
+    if (threadIdx.x == 0) a.partials[rep * a.n_pb + pb] = red[0] + red[1];
 }
 
 // The same energies as a z-march where kmode_rows(L) > 0: one work-group per
@@ -673,10 +707,10 @@ hipError_t launch_energy(const EnergyArgs &a, int storage, hipStream_t s)
     const int64_t blocks = a.n_rep * a.n_pb;
     if (blocks == 0) return hipSuccess;
     switch (storage) {
-    case 0: hipLaunchKernelGGL(k_energy<0>, dim3((unsigned)blocks), dim3(kBlock), 0, s, a); break;
-    case 1: hipLaunchKernelGGL(k_energy<1>, dim3((unsigned)blocks), dim3(kBlock), 0, s, a); break;
-    case 2: hipLaunchKernelGGL(k_energy<2>, dim3((unsigned)blocks), dim3(kBlock), 0, s, a); break;
-    case 3: hipLaunchKernelGGL(k_energy<3>, dim3((unsigned)blocks), dim3(kBlock), 0, s, a); break;
+    case 0: hipLaunchKernelGGL(k_energy<0>, dim3((unsigned)blocks), dim3(kBlock / 2), 0, s, a); break;
+    case 1: hipLaunchKernelGGL(k_energy<1>, dim3((unsigned)blocks), dim3(kBlock / 2), 0, s, a); break;
+    case 2: hipLaunchKernelGGL(k_energy<2>, dim3((unsigned)blocks), dim3(kBlock / 2), 0, s, a); break;
+    case 3: hipLaunchKernelGGL(k_energy<3>, dim3((unsigned)blocks), dim3(kBlock / 2), 0, s, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -702,15 +736,20 @@ __global__ __launch_bounds__(kBlock) void k_overlap(OverlapArgs a)
     const T *B = (const T *)a.spins + (((int64_t)d * a.O + 1) * a.T + sb) * 2 * C::kPlanes * Nh;
     double acc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     const int64_t j_end = ((int64_t)(pb + 1) * a.chunk < Nh) ? (int64_t)(pb + 1) * a.chunk : Nh;
-    // unrolled so that the loads of several iterations are in flight together
-    // (the sums keep their order)
+    // A pair of sites of one parity per thread: two waves take 256 half-indices of the
+    // even sites, two those of the odd ones. Unrolled so that the loads of several
+    // iterations are in flight together.
+    const int p = threadIdx.x >> 7;
+    A += (int64_t)p * C::kPlanes * Nh;
+    B += (int64_t)p * C::kPlanes * Nh;
 #pragma unroll 4
-    for (int64_t j = (int64_t)pb * a.chunk + threadIdx.x; j < j_end; j += kBlock) {
+    for (int64_t j = (int64_t)pb * a.chunk + 2 * (threadIdx.x & 127); j < j_end; j += kBlock) {
+        v3 x[2], y[2];
+        C::load_pair(A, (uint32_t)Nh, (uint32_t)j, x[0], x[1]);
+        C::load_pair(B, (uint32_t)Nh, (uint32_t)j, y[0], y[1]);
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const v3 x = C::load(A + (int64_t)p * C::kPlanes * Nh, Nh, j);
-            const v3 y = C::load(B + (int64_t)p * C::kPlanes * Nh, Nh, j);
-            const double xa[3] = {x.x, x.y, x.z}, ya[3] = {y.x, y.y, y.z};
+        for (int u = 0; u < 2; ++u) {
+            const double xa[3] = {x[u].x, x[u].y, x[u].z}, ya[3] = {y[u].x, y[u].y, y[u].z};
             for (int m = 0; m < 3; ++m)
                 for (int n = 0; n < 3; ++n) acc[3 * m + n] += xa[m] * ya[n];
         }
@@ -1488,19 +1527,34 @@ __global__ __launch_bounds__(kBlock) void k_pair_overlaps(PairOvArgs a)
 #pragma unroll
     for (int m = 0; m < 28; ++m) acc[m] = 0.0;
     const int64_t i_end = ((int64_t)(pb + 1) * a.chunk < N) ? (int64_t)(pb + 1) * a.chunk : N;
-    for (int64_t i = (int64_t)pb * a.chunk + threadIdx.x; i < i_end; i += kBlock) {
-        const int x = (int)(i % L), y = (int)((i / L) % L), z = (int)(i / ((int64_t)L * L));
-        const int p = (x + y + z) & 1;
-        const int64_t j = ((int64_t)z * L + y) * (L / 2) + (x >> 1);
-        const double ph[7] = {1.0, cph[x], sph[x], cph[y], sph[y], cph[z], sph[z]};
+    // Four consecutive sites hold a pair of either parity; a thread takes one pair, the
+    // first and third wave the even ones.
+    const int p = (threadIdx.x >> 6) & 1, Lh = L / 2;
+    for (int64_t i = (int64_t)pb * a.chunk + 4 * ((threadIdx.x >> 7) * 64 + (threadIdx.x & 63)); i < i_end;
+         i += 2 * kBlock) {
+        const uint32_t j0 = (uint32_t)(i >> 1);
+        double ph[2][7];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t r = (j0 + u) / (uint32_t)Lh, xh = j0 + u - r * (uint32_t)Lh;
+            const int y = (int)(r % (uint32_t)L), z = (int)(r / (uint32_t)L), x = 2 * (int)xh + ((y + z + p) & 1);
+            ph[u][0] = 1.0;
+            ph[u][1] = cph[x]; ph[u][2] = sph[x];
+            ph[u][3] = cph[y]; ph[u][4] = sph[y];
+            ph[u][5] = cph[z]; ph[u][6] = sph[z];
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             if (q < np) {
-                const v3 u = C::load(U[q] + (int64_t)p * C::kPlanes * Nh, Nh, j);
-                const v3 v = C::load(V[q] + (int64_t)p * C::kPlanes * Nh, Nh, j);
-                const double f = (double)u.x * v.x + (double)u.y * v.y + (double)u.z * v.z;
+                v3 v[2], w[2];
+                C::load_pair(U[q] + (int64_t)p * C::kPlanes * Nh, (uint32_t)Nh, j0, v[0], v[1]);
+                C::load_pair(V[q] + (int64_t)p * C::kPlanes * Nh, (uint32_t)Nh, j0, w[0], w[1]);
 #pragma unroll
-                for (int m = 0; m < 7; ++m) acc[7 * q + m] += f * ph[m];
+                for (int u = 0; u < 2; ++u) {
+                    const double f = (double)v[u].x * w[u].x + (double)v[u].y * w[u].y + (double)v[u].z * w[u].z;
+#pragma unroll
+                    for (int m = 0; m < 7; ++m) acc[7 * q + m] += f * ph[u][m];
+                }
             }
         }
     }
