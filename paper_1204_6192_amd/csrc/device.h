@@ -390,8 +390,10 @@ struct Codec<0> {  // float32: stored renormalised, read as is
     static constexpr int kPlanes = 3;  // elements per site and parity
     __device__ static __forceinline__ v3 load(const T *p, int64_t cs, int64_t j)
     {
-        // two loads, not three: a load's cost does not depend on its width
-        const float4 xy = *reinterpret_cast<const float4 *>(p + 4 * (j >> 1));
+        // two loads, not three: a load's cost does not depend on its width (the empty asm
+        // keeps the compiler from taking single components)
+        float4 xy = *reinterpret_cast<const float4 *>(p + 4 * (j >> 1));
+        asm("" : "+v"(xy.x), "+v"(xy.y), "+v"(xy.z), "+v"(xy.w));
         return (j & 1) ? v3{xy.y, xy.w, p[2 * cs + j]} : v3{xy.x, xy.z, p[2 * cs + j]};
     }
     // site j of the array at element `at` of the base, with 32-bit byte offsets from
