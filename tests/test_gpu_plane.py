@@ -115,3 +115,19 @@ def test_energies_of_parts_of_a_size(hsg, L, D, O, T, field, kw, n_or):
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
     assert torch.allclose(a[3], E, rtol=1e-10, atol=1e-9)
     assert torch.equal(a[3], whole[3])
+
+
+# many sites of L >= 128: bands of two rows by default, several replicas per work-group
+# (L = 144: three, of 216 threads)
+@pytest.mark.parametrize("L,D,T,storage,field", [(128, 3, 4, "f32", None), (128, 1, 12, "f16", ("gaussian", 0.1)),
+                                                 (144, 2, 4, "qangle", None), (144, 1, 10, "bf16", None)])
+def test_flat_bands_bit_identical(hsg, L, D, T, storage, field):
+    g = _group(L, D, 1, T, field, "gaussian")
+    lat = hsg.Lattice([g], storage=storage)
+    assert lat.get_geometry(0)[0] == 2
+    lat.close()
+    a, E = _run(hsg, [g], 2, storage, 1, 1, 0)
+    b, _ = _run(hsg, [g], 1, storage, 1, 1, 0)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
+    assert torch.allclose(a[3], b[3], rtol=1e-10, atol=1e-9)
+    assert torch.allclose(a[3], E, rtol=1e-10, atol=1e-9)
