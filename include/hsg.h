@@ -302,9 +302,9 @@ hsg_status hsg_set_tuning(hsg_lattice *h, int32_t slots_per_item);
 hsg_status hsg_set_kernel(hsg_lattice *h, int32_t variant);
 
 /* Tuning (results do not depend on it): 1 = where every lattice size runs
- * the z-march (none the LDS launch of variant 5), has at least two samples and
- * no replica batches, and the full-lattice chain is selected, hsg_sweep runs the two halves of every
- * group's samples on two streams (the caller's and one of the library's,
+ * the z-march or the LDS launch of variant 5 (at least one the z-march), has at
+ * least two samples and no replica batches, and the full-lattice chain is
+ * selected, hsg_sweep runs the two halves of every group's samples on two streams (the caller's and one of the library's,
  * joined before it returns), each half with its own device sweep counter
  * (the second copied from the first at the start of every call); one half's
  * heat-bath pairs then run beside the other half's over-relaxation pairs.

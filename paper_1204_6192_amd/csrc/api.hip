@@ -944,8 +944,27 @@ int64_t batch_of(const hsg_lattice *h, const Group &g)
     return b < g.n_rep ? b : 0;
 }
 
-// The half-sweeps and energies of one sweep of every group use_replica selects.
-hsg_status run_replica(hsg_lattice *h, hipStream_t s)
+// Samples [d0, d1) of half c of group g (c < 0: all).
+void sample_range(const Group &g, int c, int64_t &d0, int64_t &d1)
+{
+    const int64_t half = g.D / 2;
+    d0 = c == 1 ? half : 0;
+    d1 = c == 0 ? half : g.D;
+}
+
+// Replica range [r0, r1) of half c of group g (c < 0: all).
+void half_range(const Group &g, int c, int64_t &r0, int64_t &r1)
+{
+    int64_t d0, d1;
+    sample_range(g, c, d0, d1);
+    r0 = d0 * g.O * g.T;
+    r1 = d1 * g.O * g.T;
+}
+
+// The half-sweeps and energies of one sweep of every group use_replica selects, for the
+// samples of half c. Threads per replica, and so the order of the energies' sums, go by
+// all replicas.
+hsg_status run_replica(hsg_lattice *h, int c, hipStream_t s)
 {
     std::vector<const Group *> gs;
     for (const Group &g : h->lay.g)
@@ -982,7 +1001,7 @@ hsg_status run_replica(hsg_lattice *h, hipStream_t s)
             a.E = reinterpret_cast<double *>(h->state + g.o_E);
             a.tptr = dev_counter(h);
             a.Nh = g.Nh;
-            a.n_rep = g.n_rep;
+            half_range(g, c, a.r_base, a.r_end);
             a.L = g.L;
             a.Lh = g.L / 2;
             a.pp = (g.L / 2) * (g.L / 2);
@@ -995,7 +1014,7 @@ hsg_status run_replica(hsg_lattice *h, hipStream_t s)
             a.key0 = (uint32_t)(h->seed & 0xFFFFFFFFu);
             a.key1 = (uint32_t)(h->seed >> 32);
             a.uid_base = g.uid_base;
-            const int64_t nb = (g.n_rep + a.RB - 1) / a.RB;
+            const int64_t nb = (a.r_end - a.r_base + a.RB - 1) / a.RB;
             if (blocks + nb > 0x7FFFFFFFll) return fail(HSG_E_SIZE, "grid too large");
             a.n_blocks = (int32_t)nb;
             m.block_start[m.n_groups] = (int32_t)blocks;
@@ -1015,14 +1034,6 @@ hsg_status run_replica(hsg_lattice *h, hipStream_t s)
 int energy_pb(const hsg_lattice *h, const Group &g)
 {
     return h->chain == 1 || use_replica(h, g) ? 0 : last_pass(h, g).n_pb;
-}
-
-// Samples [d0, d1) of half c of group g (c < 0: all).
-void sample_range(const Group &g, int c, int64_t &d0, int64_t &d1)
-{
-    const int64_t half = g.D / 2;
-    d0 = c == 1 ? half : 0;
-    d1 = c == 0 ? half : g.D;
 }
 
 // Lines of the end of a sweep, in us per sweep of L = 4 in float32. A work-group takes
@@ -1319,7 +1330,7 @@ hsg_status enqueue_sweep(hsg_lattice *h, bool pt, hipStream_t s)
     bool batched = false;
     for (const Group &g : h->lay.g) batched = batched || batch_of(h, g) > 0;
     if (any_replica(h)) {
-        hsg_status st = run_replica(h, s);
+        hsg_status st = run_replica(h, -1, s);
         if (st != HSG_OK) return st;
     }
     if (!batched) {
@@ -1526,23 +1537,20 @@ hsg_status hsg_init_lattice(const hsg_desc *desc, const float *d_spins0, const f
 // the first half's next heat-bath pairs for the second half's, so that each
 // half's heat bath (bound by instruction issue) runs beside the other half's
 // over-relaxation (bound by latency). Every replica gets the same updates with
-// the same counters as in one stream, so the results are the same bits.
+// the same counters as in one stream, so the results are the same bits. Sizes with the
+// spins in LDS have one launch per half and sweep; a handle of such sizes alone has
+// nothing to overlap.
 bool overlap_ok(const hsg_lattice *h)
 {
-    if (!h->overlap || h->chain != 0 || h->series != nullptr || any_replica(h)) return false;
+    if (!h->overlap || h->chain != 0 || h->series != nullptr) return false;
+    bool any = false;
     for (const Group &g : h->lay.g) {
-        if (!use_stream(h, g) || g.D < 2 || batch_of(h, g) > 0) return false;
+        if (g.D < 2) return false;
+        if (use_replica(h, g)) continue;
+        if (!use_stream(h, g) || batch_of(h, g) > 0) return false;
+        any = true;
     }
-    return true;
-}
-
-// Replica range [r0, r1) of half c of group g.
-void half_range(const Group &g, int c, int64_t &r0, int64_t &r1)
-{
-    int64_t d0, d1;
-    sample_range(g, c, d0, d1);
-    r0 = d0 * g.O * g.T;
-    r1 = d1 * g.O * g.T;
+    return any;
 }
 
 // One sweep of half c (heat-bath pairs, then the rest), on stream s; `hb_done`
@@ -1553,6 +1561,7 @@ hsg_status enqueue_half_sweep(hsg_lattice *h, int c, bool pt, hipStream_t s, hip
     const int last_kind = h->n_or > 0 ? 1 : 0;
     hsg_status st = HSG_OK;
     for (const Group &g : h->lay.g) {
+        if (use_replica(h, g)) continue;
         int64_t r0, r1;
         half_range(g, c, r0, r1);
         auto only = [&g](const Group &x) { return &x == &g; };
@@ -1561,8 +1570,10 @@ hsg_status enqueue_half_sweep(hsg_lattice *h, int c, bool pt, hipStream_t s, hip
     }
     hipError_t e = st == HSG_OK ? hipEventRecord(hb_done, s) : hipSuccess;
     if (e != hipSuccess) st = hip_fail(e, "event record");
+    if (st == HSG_OK && any_replica(h)) st = run_replica(h, c, s);
     for (const Group &g : h->lay.g) {
         if (st != HSG_OK) break;
+        if (use_replica(h, g)) continue;
         int64_t r0, r1;
         half_range(g, c, r0, r1);
         auto only = [&g](const Group &x) { return &x == &g; };
@@ -2096,6 +2107,7 @@ hsg_status hsg_autotune(hsg_lattice *h, int32_t n_sweeps, void *d_backup, int32_
         const bool replica = any_replica(h);
         h->kernel_variant = v0;
         if (replica) cands.push_back({5, 0, false});
+        if (replica && any_stream) cands.push_back({5, 0, true});
     }
     {
         const int32_t v0 = h->kernel_variant;

@@ -114,7 +114,7 @@ struct ReplicaArgs {
     const float *beta32;
     double *E;             // [replica]
     const uint32_t *tptr;  // device sweep counter
-    int64_t Nh, n_rep;
+    int64_t Nh, r_base, r_end;  // replicas [r_base, r_end) of the launch
     int32_t L, Lh, pp, ZB, tpr, RB, n_blocks;
     int32_t slots_per_sample, T, n_hb, n_or;
     uint32_t key0, key1, uid_base;

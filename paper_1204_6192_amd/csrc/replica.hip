@@ -35,10 +35,10 @@ __device__ __forceinline__ void replica_body(const ReplicaArgs &a, const int lb,
     const int rb = __builtin_amdgcn_readfirstlane(tid / a.tpr);
     const int rem = tid - rb * a.tpr;
     const int zz = rem / a.pp, pq = rem - zz * a.pp;
-    const int64_t r_lane = (int64_t)lb * a.RB + rb;
-    const bool mine = rb < a.RB && r_lane < a.n_rep;      // the wave has a replica
+    const int64_t r_lane = a.r_base + (int64_t)lb * a.RB + rb;
+    const bool mine = rb < a.RB && r_lane < a.r_end;      // the wave has a replica
     const bool active = mine && zz < a.ZB;
-    const int64_t r = mine ? r_lane : 0;
+    const int64_t r = mine ? r_lane : a.r_base;
     const int64_t d = r / a.slots_per_sample;
     const int sis = (int)(r - d * a.slots_per_sample);
     const int L = a.L, Lh = a.Lh;

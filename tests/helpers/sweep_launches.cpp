@@ -6,7 +6,7 @@
 //
 // Reads one case per line from standard input,
 //   storage n_hb n_or variant batch overlap sweeps  n_groups  (L samples copies rungs field)...
-// and prints "ok" or what is wrong for each.
+// and prints "ok" or what is wrong for each; overlap = 2: and the halves have to be in effect.
 #include <hip/hip_runtime.h>
 #define __align__(n) __attribute__((aligned(n)))
 #define HIP_SYMBOL(x) static_cast<const void *>(x)
@@ -27,7 +27,8 @@ hsg_lattice *g_h = nullptr;
 std::vector<std::vector<Rep>> g_reps;  // [group][replica]
 std::string g_bad;
 uint32_t g_t = 0;  // the counter that every launch of the sweep has to read
-int g_ended = 0;   // work of the sweeps' ends: samples whose ladders have been walked
+int g_ended = 0;   // work of the sweeps' ends: replicas whose ladders have been walked
+int g_steps = 0;   // counters that the sweep's ends stepped
 
 void bad(const std::string &s)
 {
@@ -122,7 +123,9 @@ hipError_t launch_replica(const MultiReplicaArgs &m, int, bool, unsigned, size_t
     for (int i = 0; i < m.n_groups; ++i) {
         const ReplicaArgs &a = m.g[i];
         const size_t k = group_of(a.spins);
-        for (int64_t r = 0; r < a.n_rep; ++r) {
+        const int64_t blocks = (i + 1 < m.n_groups ? m.block_start[i + 1] : m.n_blocks) - m.block_start[i];
+        if (blocks != a.n_blocks || blocks * a.RB < a.r_end - a.r_base) bad("a replica launch of too few work-groups");
+        for (int64_t r = a.r_base; r < a.r_end; ++r) {
             for (int j = 0; j < 2 * a.n_hb; ++j) half_sweep(k, r, 0, (uint32_t)(j / 2), j & 1, a.tptr);
             for (int j = 0; j < 2 * a.n_or; ++j) half_sweep(k, r, 1, 0, j & 1, a.tptr);
             energies(k)[r] = true_energy(k, r);
@@ -159,7 +162,12 @@ hipError_t launch_sweep_end(const MultiLadderArgs &m, hipStream_t)
         }
         g_ended += (int)n;
     }
-    if (m.advance) *m.advance = *m.tptr + 1;
+    if (m.advance) {
+        *m.advance = *m.tptr + 1;
+        if (m.ticket != reinterpret_cast<uint32_t *>(g_h->state) + 2 + (m.advance - reinterpret_cast<uint32_t *>(g_h->state)))
+            bad("the halves share a ticket");
+        g_steps += 1;
+    }
     return hipSuccess;
 }
 
@@ -171,6 +179,7 @@ hipError_t launch_copy_u32(const uint32_t *src, uint32_t *dst, hipStream_t)
 hipError_t launch_advance(uint32_t *p, hipStream_t)
 {
     *p += 1;
+    g_steps += 1;
     return hipSuccess;
 }
 
@@ -298,14 +307,14 @@ std::string run(std::istringstream &in)
         g_h = h;
         g_bad.clear();
         if (hsg_set_kernel(h, variant) != HSG_OK || hsg_set_batch(h, batch) != HSG_OK ||
-            hsg_set_overlap(h, overlap) != HSG_OK)
+            hsg_set_overlap(h, overlap != 0) != HSG_OK)
             bad(hsg_last_error());
         uint64_t want = 0;
         for (int j = 0; j < 2 * n_hb; ++j) want = join(want, code(0, (uint32_t)(j / 2), j & 1));
         for (int j = 0; j < 2 * n_or; ++j) want = join(want, code(1, 0, j & 1));
         for (int s = 0; s < sweeps; ++s) {
             g_t = (uint32_t)s;
-            g_ended = 0;
+            g_ended = g_steps = 0;
             g_reps.assign(h->lay.g.size(), {});
             for (size_t k = 0; k < h->lay.g.size(); ++k) {
                 const Group &g = h->lay.g[k];
@@ -318,6 +327,7 @@ std::string run(std::istringstream &in)
             for (size_t k = 0; k < g_reps.size(); ++k)
                 for (const Rep &x : g_reps[k])
                     if (x.seq != want || x.n != 2 * (n_hb + n_or)) bad("a replica got other half-sweeps");
+            if (overlap == 2 && g_steps != 2) bad("no halves");
             if (g_ended != (int)sz.n_replicas) bad("ladders left out, or walked twice");
             if (*reinterpret_cast<uint32_t *>(h->state) != (uint32_t)s + 1) bad("the counter was not advanced");
         }

@@ -68,3 +68,14 @@ def test_several_sizes(check):
                           [(30, 60), (32, 60), (36, 60)], [(8, 3), (18, 9), (30, 100)], [(24, 70), (28, 75), (32, 280)]):
                 cases.append((storage, n_hb, n_or, variant, batch, overlap, [(L, 2, 1, n // 2 + 1, 0) for L, n in sizes]))
     assert check(cases) == []
+
+
+def test_halves_in_effect(check):
+    """Sizes with the spins in LDS beside sizes of the marches still sweep as two halves;
+    halves of one and of two samples."""
+    cases = []
+    for storage, (n_hb, n_or), variant in itertools.product((F32, F16, QANGLE), MIXES, (0, 2, 3, 4, 5)):
+        for sizes in ([(12, 2, 3), (16, 3, 3), (24, 2, 40), (48, 3, 9)], [(8, 2, 1), (32, 5, 100)], [(36, 2, 3)],
+                      [(16, 2, 2), (20, 3, 30), (128, 2, 1)]):
+            cases.append((storage, n_hb, n_or, variant, -1, 2, [(L, D, 1, T, 0) for L, D, T in sizes]))
+    assert check(cases) == []
