@@ -961,14 +961,10 @@ void half_range(const Group &g, int c, int64_t &r0, int64_t &r1)
     r1 = d1 * g.O * g.T;
 }
 
-// The half-sweeps and energies of one sweep of every group use_replica selects, for the
-// samples of half c. Threads per replica, and so the order of the energies' sums, go by
-// all replicas.
-hsg_status run_replica(hsg_lattice *h, int c, hipStream_t s)
+// The LDS launches of the lattice sizes gs, for the samples of half c; sub: L = 4, four
+// replicas per wave.
+hsg_status launch_replicas(hsg_lattice *h, const std::vector<const Group *> &gs, bool sub, int c, hipStream_t s)
 {
-    std::vector<const Group *> gs;
-    for (const Group &g : h->lay.g)
-        if (use_replica(h, g)) gs.push_back(&g);
     for (size_t k0 = 0; k0 < gs.size(); k0 += hsg::kMaxStreamGroups) {
         const size_t k1 = std::min(gs.size(), k0 + hsg::kMaxStreamGroups);
         size_t lds = 0;
@@ -987,6 +983,10 @@ hsg_status run_replica(hsg_lattice *h, int c, hipStream_t s)
         const int cap = share <= 1 ? 1024 : share == 2 ? 512 : 256;
         int32_t threads = 0;
         for (size_t k = k0; k < k1; ++k) threads = std::max(threads, replica_threads(*gs[k], cap, nullptr));
+        if (sub) {
+            threads = 64;
+            lds = 4 * replica_lds_bytes(*gs[k0]);
+        }
         hsg::MultiReplicaArgs m{};
         int64_t blocks = 0;
         for (size_t k = k0; k < k1; ++k) {
@@ -1005,7 +1005,8 @@ hsg_status run_replica(hsg_lattice *h, int c, hipStream_t s)
             a.L = g.L;
             a.Lh = g.L / 2;
             a.pp = (g.L / 2) * (g.L / 2);
-            a.tpr = replica_threads(g, cap, &a.ZB);
+            a.tpr = sub ? 16 : replica_threads(g, cap, &a.ZB);
+            if (sub) a.ZB = 4;
             a.RB = (int32_t)std::min<size_t>((size_t)(threads / a.tpr), lds / replica_lds_bytes(g));
             a.slots_per_sample = g.O * g.T;
             a.T = g.T;
@@ -1027,6 +1028,31 @@ hsg_status run_replica(hsg_lattice *h, int c, hipStream_t s)
         if (e != hipSuccess) return hip_fail(e, "replica sweep launch");
     }
     return HSG_OK;
+}
+
+// The half-sweeps and energies of one sweep of every group use_replica selects, for the
+// samples of half c. Threads per replica, and so the order of the energies' sums, go by
+// all replicas.
+hsg_status run_replica(hsg_lattice *h, int c, hipStream_t s)
+{
+    // Replicas of L = 4 have 16 site pairs: four per wave in a launch of their own, a
+    // wave per work-group (us per sweep in float32, against a wave per replica: 8
+    // replicas 13.7 : 15.5, 4096 19 : 26, 65536 78 : 222; two or four waves per
+    // work-group 83 and 84). Beside other sizes only for so many that the further
+    // launch, 4 us, is less.
+    std::vector<const Group *> fours, gs;
+    int64_t n_fours = 0;
+    for (const Group &g : h->lay.g) {
+        if (!use_replica(h, g)) continue;
+        (g.L == 4 ? fours : gs).push_back(&g);
+        n_fours += g.L == 4 ? g.n_rep : 0;
+    }
+    if (gs.empty() || n_fours >= 4096) {
+        hsg_status st = fours.empty() ? HSG_OK : launch_replicas(h, fours, true, c, s);
+        return st != HSG_OK || gs.empty() ? st : launch_replicas(h, gs, false, c, s);
+    }
+    gs.insert(gs.end(), fours.begin(), fours.end());
+    return launch_replicas(h, gs, false, c, s);
 }
 
 // Energy partial sums per replica that a sweep's updates leave for group g: 0 where the

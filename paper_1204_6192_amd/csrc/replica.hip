@@ -25,14 +25,15 @@
 
 namespace hsg {
 
-template <int STORE, bool FIELD, bool JB, bool HW, bool PAIRED>
+// SUB: four replicas of L = 4 per wave, 16 threads each (rows of 4 need PAIRED).
+template <int STORE, bool FIELD, bool JB, bool HW, bool PAIRED, bool SUB>
 __device__ __forceinline__ void replica_body(const ReplicaArgs &a, const int lb, float *lds, double *red)
 {
     using C = Codec<STORE>;
     using T = typename C::T;
     const int tid = (int)threadIdx.x;
     // whole waves per replica, so everything that depends on it alone is uniform
-    const int rb = __builtin_amdgcn_readfirstlane(tid / a.tpr);
+    const int rb = SUB ? tid / a.tpr : __builtin_amdgcn_readfirstlane(tid / a.tpr);
     const int rem = tid - rb * a.tpr;
     const int zz = rem / a.pp, pq = rem - zz * a.pp;
     const int64_t r_lane = a.r_base + (int64_t)lb * a.RB + rb;
@@ -129,6 +130,12 @@ __device__ __forceinline__ void replica_body(const ReplicaArgs &a, const int lb,
         }
         __syncthreads();
     }
+    if constexpr (SUB) {  // the replica's energy: its quarter of the wave
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) e += __shfl_xor(e, off, 64);
+        if (mine && rem == 0) a.E[r] = e;
+        return;
+    }
     // the replica's energy: waves, then its waves in order
     e = wave_sum(e);
     if ((tid & 63) == 0) red[tid >> 6] = e;
@@ -140,25 +147,29 @@ __device__ __forceinline__ void replica_body(const ReplicaArgs &a, const int lb,
     }
 }
 
-template <int STORE, bool FIELD, bool JB, bool HW, bool PAIRED>
-__global__ __launch_bounds__(1024) void k_replica_sweep(MultiReplicaArgs m)
+template <int STORE, bool FIELD, bool JB, bool HW, bool PAIRED, bool SUB>
+__global__ __launch_bounds__(SUB ? 64 : 1024) void k_replica_sweep(MultiReplicaArgs m)
 {
     extern __shared__ __align__(16) float lds[];
     __shared__ double red[16];
     const int b = xcd_remap((int)blockIdx.x, m.n_blocks);
     int k = 0;
     while (k + 1 < m.n_groups && b >= m.block_start[k + 1]) ++k;
-    replica_body<STORE, FIELD, JB, HW, PAIRED>(m.g[k], b - m.block_start[k], lds, red);
+    replica_body<STORE, FIELD, JB, HW, PAIRED, SUB>(m.g[k], b - m.block_start[k], lds, red);
 }
 
 template <int STORE>
-static hipError_t launch_replica_s(const MultiReplicaArgs &m, bool field, bool jb, bool hw, bool paired,
+static hipError_t launch_replica_s(const MultiReplicaArgs &m, bool field, bool jb, bool hw, bool paired, bool sub,
                                    unsigned threads, size_t lds, hipStream_t s)
 {
     const dim3 grid((unsigned)m.n_blocks), block(threads);
-#define HSG_P(F, J, H, P) hipLaunchKernelGGL((k_replica_sweep<STORE, F, J, H, P>), grid, block, lds, s, m)
+#define HSG_P(F, J, H, P, S) hipLaunchKernelGGL((k_replica_sweep<STORE, F, J, H, P, S>), grid, block, lds, s, m)
 #define HSG_PP(F, J, H) \
-    do { if (paired) HSG_P(F, J, H, true); else HSG_P(F, J, H, false); } while (0)
+    do { \
+        if (sub) HSG_P(F, J, H, true, true); \
+        else if (paired) HSG_P(F, J, H, true, false); \
+        else HSG_P(F, J, H, false, false); \
+    } while (0)
 #define HSG_PH(F, J) \
     do { if (hw) HSG_PP(F, J, true); else HSG_PP(F, J, false); } while (0)
     if (field) {
@@ -178,9 +189,10 @@ hipError_t launch_replica(const MultiReplicaArgs &m, int storage, bool hw, unsig
     if (m.n_groups < 1 || m.n_groups > kMaxStreamGroups || threads == 0 || threads > 1024 || threads % 64 != 0)
         return hipErrorInvalidValue;
     bool field = false, jb = false, paired = true;
+    const bool sub = m.g[0].tpr == 16;
     for (int k = 0; k < m.n_groups; ++k) {
         const ReplicaArgs &a = m.g[k];
-        if (a.tpr % 64 != 0 || a.ZB * a.pp > a.tpr || (unsigned)(a.RB * a.tpr) > threads ||
+        if ((sub ? a.tpr != 16 || a.L != 4 || threads != 64 : a.tpr % 64 != 0) || a.ZB * a.pp > a.tpr || (unsigned)(a.RB * a.tpr) > threads ||
             (size_t)a.RB * 6 * a.Nh * sizeof(float) > lds)
             return hipErrorInvalidValue;
         field = field || a.Hp != nullptr;
@@ -188,10 +200,10 @@ hipError_t launch_replica(const MultiReplicaArgs &m, int storage, bool hw, unsig
         paired = paired && a.L % 4 == 0;
     }
     switch (storage) {
-    case 0: return launch_replica_s<0>(m, field, jb, hw, paired, threads, lds, s);
-    case 1: return launch_replica_s<1>(m, field, jb, hw, paired, threads, lds, s);
-    case 2: return launch_replica_s<2>(m, field, jb, hw, paired, threads, lds, s);
-    case 3: return launch_replica_s<3>(m, field, jb, hw, paired, threads, lds, s);
+    case 0: return launch_replica_s<0>(m, field, jb, hw, paired, sub, threads, lds, s);
+    case 1: return launch_replica_s<1>(m, field, jb, hw, paired, sub, threads, lds, s);
+    case 2: return launch_replica_s<2>(m, field, jb, hw, paired, sub, threads, lds, s);
+    case 3: return launch_replica_s<3>(m, field, jb, hw, paired, sub, threads, lds, s);
     default: return hipErrorInvalidValue;
     }
 }

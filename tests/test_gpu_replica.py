@@ -70,3 +70,22 @@ def test_replica_sweeps_of_several_sizes(hsg, storage):
     a, E = _run(hsg, groups, 0, storage, 1, 4, 0, 3)
     b, _ = _run(hsg, groups, 1, storage, 1, 4, 0, 3)
     _check(a, b, E)
+
+
+# L = 4, four replicas per wave: one replica, remainders, several groups, a launch of its
+# own beside other sizes (4100 replicas) and one with them (3)
+@pytest.mark.parametrize("sizes", [((4, 1, 1, 1),), ((4, 4097, 1, 1),), ((4, 5, 1, 1), (4, 2, 2, 3)),
+                                   ((4, 1025, 2, 2), (8, 2, 2, 3)), ((4, 3, 1, 1), (6, 2, 1, 3))])
+@pytest.mark.parametrize("storage,field,couplings,n_hb,n_or,math",
+                         [("f32", None, "gaussian", 1, 4, 0), ("f16", ("gaussian", 0.2), "bimodal", 2, 1, 1),
+                          ("qangle", None, "gaussian", 1, 0, 0)])
+def test_smallest_lattices(hsg, sizes, storage, field, couplings, n_hb, n_or, math):
+    rng = np.random.Generator(np.random.Philox(inputs.INSTANCE_SEED_BASE + 98))
+    groups, uid = [], 0
+    for L, D, O, T in sizes:
+        groups.append(inputs.make_group(rng, L, D, O, inputs.geometric_ladder(0.1, 0.6 if T > 1 else 0.1, T),
+                                        couplings=couplings, field=field, sample_uid_base=uid))
+        uid += D
+    a, E = _run(hsg, groups, 0, storage, n_hb, n_or, math, 2)
+    b, _ = _run(hsg, groups, 1, storage, n_hb, n_or, math, 2)
+    _check(a, b, E)
