@@ -622,8 +622,6 @@ hsg_status run_half_sweep(hsg_lattice *h, int kind, int parity, int rep, bool en
     return run_groups(h, kind, parity, rep, energy, 0, [](const Group &) { return true; }, s);
 }
 
-size_t plane_lds_bytes(const Group &g, int groups) { return (size_t)(groups == 1 ? 4 : 11) * 6 * g.L * g.L; }
-
 // One pair (groups = 1) or two over-relaxation pairs (groups = 2) in one walk of
 // whole planes (launch_plane_march), where a plane's site pairs fit the work-group
 // (1024 and 256 threads) and the staged planes its LDS, and where that is the faster
@@ -655,7 +653,7 @@ bool use_plane(const hsg_lattice *h, const Group &g, int kind, int groups, bool 
 {
     if ((h->kernel_variant != 0 && h->kernel_variant < 4) || g.L < 24) return false;
     const int pp = (g.L / 2) * (g.L / 2), waves = (pp + 63) / 64;
-    if (pp > (groups == 1 ? 1024 : 256) || plane_lds_bytes(g, groups) + 256 > h->max_lds) return false;
+    if (pp > (groups == 1 ? 1024 : 256) || hsg::plane_march_lds(g.L, groups) + 256 > h->max_lds) return false;
     const int c = store_class(h);
     const bool several = waves <= 8;  // a CU holds more than one work-group
     const int64_t slots = 256 * ((n + 255) / 256);  // of whole rounds
@@ -718,7 +716,10 @@ hsg_status run_plane(hsg_lattice *h, int kind, int rep, int groups, bool energy,
         const int pp = (g.L / 2) * (g.L / 2), tpg = (pp + 63) / 64 * 64;
         const int64_t nb = (r1 < 0 ? g.n_rep : r1) - r0;
         if (nb > 0x7FFFFFFFll) return fail(HSG_E_SIZE, "grid too large");
-        // one launch per lattice size: the sizes differ in threads and LDS
+        // Sizes of one thread count share a launch, L % 4 = 2 beside 0 too, though it then
+        // takes the wider reads of neither: few replicas run side by side so (128 each of
+        // L = 30 and 32 in float32 206 us per sweep, in launches of their own 297), many take
+        // the same time (1024 each 1372 : 1377; 512 each of L = 24 and 26 462 : 393).
         if (m.n_groups == hsg::kMaxStreamGroups || (m.n_groups > 0 && (unsigned)(groups * tpg) != threads)) {
             const hsg_status st = flush();
             if (st != HSG_OK) return st;
@@ -748,7 +749,7 @@ hsg_status run_plane(hsg_lattice *h, int kind, int rep, int groups, bool energy,
         m.g[m.n_groups++] = a;
         blocks += nb;
         threads = std::max(threads, (unsigned)(groups * tpg));
-        lds = std::max(lds, plane_lds_bytes(g, groups));
+        lds = std::max(lds, hsg::plane_march_lds(g.L, groups));
     }
     return flush();
 }

@@ -130,7 +130,8 @@ hipError_t launch_replica(const MultiReplicaArgs &m, int storage, bool hw, unsig
 // A pair of half-sweeps (groups = 1) or two over-relaxation pairs (groups = 2) in one
 // walk of whole planes, a replica per work-group (plane_march.h): tpg threads (whole
 // waves) per group for the pp = (L/2)^2 site pairs of a plane and parity. Launch with
-// groups * tpg threads and (4 or 11) * 6 L^2 bytes of LDS. The energies go to E.
+// groups * tpg threads, the same for every lattice size of a launch, and
+// plane_march_lds(L, groups) bytes of LDS. The energies go to E.
 struct PlaneArgs {
     void *spins;
     const float *J6;
@@ -150,6 +151,7 @@ struct MultiPlaneArgs {
     int32_t block_start[kMaxStreamGroups + 1];
     PlaneArgs g[kMaxStreamGroups];
 };
+inline size_t plane_march_lds(int64_t L, int groups) { return (size_t)(groups == 1 ? 4 : 11) * 6 * L * L; }
 hipError_t launch_plane_march(const MultiPlaneArgs &m, int storage, int kind, int groups, bool energy,
                               unsigned threads, size_t lds, hipStream_t s);
 

@@ -36,9 +36,6 @@
 
 namespace hsg {
 
-// LDS planes (one parity) of a launch of G groups.
-__host__ __device__ constexpr int plane_march_planes(int G) { return G == 1 ? 4 : 11; }
-
 template <int STORE, int KIND, int G, int GRP, bool ENERGY, bool FIELD, bool JB, bool PAIRED>
 __device__ __forceinline__ void march_group(const PlaneArgs &a, const int64_t r, float *lds, double *red)
 {
@@ -263,8 +260,6 @@ __global__ __launch_bounds__(G == 1 ? 1024 : 512, 4) void k_plane_march(MultiPla
     if constexpr (G == 2) {
         if (g == 1) march_group<STORE, KIND, G, 1, ENERGY, FIELD, JB, PAIRED>(a, r, lds, red);
     }
-    if (g >= G)  // waves that this lattice size does not need: only the barriers
-        for (int z = 0; z <= (G == 1 ? a.L + 2 : a.L + 7); ++z) __syncthreads();
     if (ENERGY) {  // the last group's waves, in order
         __syncthreads();
         if (threadIdx.x == 0) {

@@ -18,8 +18,8 @@ hipError_t launch_plane_march(const MultiPlaneArgs &m, int storage, int kind, in
         const PlaneArgs &a = m.g[k];
         // L >= 8: a plane that goes home in the first steps is back there before it
         // is read again; 32-bit byte offsets within a replica and a sample
-        if (a.L < 8 || a.L > 512 || a.tpg % 64 != 0 || a.pp > a.tpg || (unsigned)(groups * a.tpg) > threads ||
-            (size_t)(groups == 1 ? 4 : 11) * 6 * a.L * a.L > lds)
+        if (a.L < 8 || a.L > 512 || a.tpg % 64 != 0 || a.pp > a.tpg || (unsigned)(groups * a.tpg) != threads ||
+            plane_march_lds(a.L, groups) > lds)
             return hipErrorInvalidValue;
         field = field || a.Hp != nullptr;
         jb = jb || a.Jbits != nullptr;
