@@ -536,16 +536,17 @@ int store_class(const hsg_lattice *h)
 // without a field, 2 and 32 replicas to a sample). By these lines and use_plane's a
 // launch takes on average 0 to 2 % longer than by the best way at each point (a pair of
 // compressed spins with a field 3 to 6 %). In us, gather against the best other way:
-//   L <= 32, over-relaxation by replicas: two pairs L = 32 f32 32 replicas 33 : 42, 64
-//     55 : 41; a pair L = 24 bf16 96 18 : 24, 256 31 : 25; the heat bath by sites: f32
-//     L = 24 256 replicas (3.5 M) 50 : 64, L = 32 256 (8.4 M) 84 : 84, 384 (12.6 M)
-//     134 : 106.
-//   above, by sites: a pair f32 L = 48 32 replicas (3.5 M) 45 : 46, bf16 L = 72 16 (6.0 M)
-//     39 : 42, L = 36 256 (11.9 M) 67 : 46; the heat bath f32 L = 44 96 (8.2 M) 88 : 89,
-//     bf16 L = 40 224 (14.3 M) 115 : 124, L = 48 160 (17.7 M) 149 : 130. Where rows make
-//     whole waves (L % 64 == 0) the march is faster: L = 64, a pair f32 12 (3.1 M)
-//     41 : 37, bf16 24 (6.3 M) 41 : 42, 32 51 : 45, the heat bath f32 24 74 : 70, bf16 32
-//     (8.4 M) 80 : 71.
+//   L <= 32, over-relaxation by replicas: two pairs L = 32 f32 32 replicas 26 : 41, 64
+//     44 : 43; a pair L = 24 f32 128 20 : 25, 192 27 : 26, bf16 96 18 : 24, 256 31 : 25; the
+//     heat bath by sites: f32 L = 24 256 replicas (3.5 M) 42 : 64, L = 32 384 (12.6 M)
+//     117 : 106, 512 159 : 110; bf16 L = 32 448 and L = 28 600 at par.
+//   above, by sites: a pair f32 L = 48 48 replicas (5.3 M) 47 : 54, L = 36 192 (9.0 M)
+//     69 : 51; bf16 L = 72 16 (6.0 M) 39 : 42, L = 36 256 (11.9 M) 67 : 46; the heat bath f32
+//     L = 44 128 (10.9 M) 91 : 91, L = 52 128 (18 M) 181 : 161, bf16 L = 40 224 (14.3 M)
+//     115 : 124, L = 48 160 (17.7 M) 149 : 130. Where rows make whole waves
+//     (L % 64 == 0) the march is faster: L = 64, a pair f32 24 (6.3 M) 52 : 55, 32 66 : 62,
+//     bf16 24 41 : 42, 32 51 : 45, the heat bath f32 24 60 : 69, 32 (8.4 M) 76 : 73, bf16 32
+//     80 : 71.
 bool use_gather(const hsg_lattice *h, const Group &g, int kind, int pairs, int64_t n)
 {
     if (!use_stream(h, g)) return true;
@@ -554,13 +555,13 @@ bool use_gather(const hsg_lattice *h, const Group &g, int kind, int pairs, int64
     const int64_t sites = n * g.N;
     const bool waves = g.L % 64 == 0;
     if (g.L <= 32) {
-        static constexpr int64_t or_line[2][2][3] = {{{64, 128, 192}, {160, 320, 384}},  // a pair: no field, field
-                                                     {{48, 64, 96}, {64, 128, 160}}};    // two pairs
+        static constexpr int64_t or_line[2][2][3] = {{{128, 128, 192}, {224, 320, 384}},  // a pair: no field, field
+                                                     {{64, 64, 96}, {96, 128, 160}}};     // two pairs
         if (kind == 1) return n <= or_line[pairs - 1][g.field ? 1 : 0][c];
-        return sites <= (c == 0 ? 9000000 : 15000000);
+        return sites <= 15000000;
     }
-    if (kind == 1) return sites <= (c == 0 ? (waves ? 2800000 : 3400000) : (waves ? 6500000 : 9000000));
-    return sites <= (c == 0 ? (waves ? 5500000 : 9000000) : (waves ? 7000000 : 13000000));
+    if (kind == 1) return sites <= (waves ? 6500000 : c == 0 ? 7000000 : 9000000);
+    return sites <= (waves ? 7000000 : 13000000);
 }
 
 // Launches one half-sweep of parity `parity` (fuse = 0), one fused pair
@@ -629,12 +630,12 @@ hsg_status run_half_sweep(hsg_lattice *h, int kind, int parity, int rep, bool en
 // fewer replicas than CUs takes as long as one of 256, and where a work-group has 9
 // to 16 waves a CU holds one: its time goes by rounds of 256. The lines are drawn as
 // use_gather's are. In us, this walk against the best of the other ways:
-//   L % 4 == 2, against gather passes: two pairs L = 30 f32 96 replicas 49 : 67, with a
-//     field 79 : 69, 160 83 : 103; a pair f32 L = 46 96 89 : 94, 320 (of 512 slots)
-//     308 : 384, with a field 192 242 : 245, 256 264 : 322. The heat bath f32 L = 50 160
-//     224 : 234, L = 34 448 152 : 194; compressed spins gain from 512 on, but not in
-//     work-groups of 5 and 6 waves (L = 34, 38); with a field nothing does (f32 L = 34
-//     1024 661 : 462).
+//   L % 4 == 2, against gather passes: two pairs L = 30 f32 96 replicas 49 : 51, 128
+//     50 : 63, with a field 128 81 : 83, 160 83 : 98; a pair f32 L = 34 160 44 : 52, L = 46 96
+//     90 : 71, 128 132 : 120, 320 (of 512 slots) 308 : 339, with a field 192 241 : 223, 256
+//     269 : 301, L = 34 448 204 : 209. The heat bath f32 L = 50 160 228 : 201, 192 227 : 242,
+//     L = 34 448 152 : 174; compressed spins gain from 512 on, but not in work-groups of 5
+//     and 6 waves (L = 34, 38); with a field nothing does (f32 L = 34 1024 666 : 446).
 //   L <= 32, L % 4 == 0: two pairs f32 L = 32 256 replicas 64 : 80, 1024 309 : 293, 8192
 //     2377 : 2170 (there the fused march keeps more bytes in flight), with energies,
 //     whose sums cost this walk's 128 registers more, 1024 324 : 294; with a field 8192
@@ -643,10 +644,11 @@ hsg_status run_half_sweep(hsg_lattice *h, int kind, int parity, int rep, bool en
 //     more. A pair f32 256 46 : 51, 2048 507 : 486; bf16 L = 28 1024 113 : 135. With a
 //     field a pair and the heat bath are the march's (f32 2048 550 : 528).
 //   L = 36 to 64, L % 4 == 0, against single passes: a pair f32 L = 44 160 replicas
-//     114 : 128, with a field L = 36 224 105 : 113, L = 64 256 486 : 673; bf16 L = 40 192
+//     114 : 127, with a field L = 36 224 107 : 105, 256 and more 0.8 to 0.95, L = 64 256
+//     without 486 : 673; bf16 L = 40 192
 //     49 : 61; compressed with a field 0.8 to 1.3 of their time, not by any simple line;
 //     quantised angles L = 48 (9 waves) 384 185 : 149, 512 259 : 304.
-//     The heat bath f32 L = 40 768 350 : 424, L = 36 (6 waves) 384 178 : 151; bf16 L = 64
+//     The heat bath f32 L = 40 768 350 : 424, L = 36 (6 waves) 384 179 : 160; bf16 L = 64
 //     256 362 : 389, L = 48 (9 waves, so 9 of a CU's 16) 592 : 528; quantised angles
 //     L = 36 384 199 : 152, L = 64 256 404 : 390.
 bool use_plane(const hsg_lattice *h, const Group &g, int kind, int groups, bool energy, int64_t n)
@@ -661,12 +663,12 @@ bool use_plane(const hsg_lattice *h, const Group &g, int kind, int groups, bool 
     if (!g.stream_ok) {
         if (kind == 0) {
             if (g.field) return false;
-            if (several) return c == 0 ? n >= 384 : n >= 512 && waves != 5 && waves != 6;
-            return c == 0 ? n >= 144 && (n <= 256 || 4 * n >= 3 * slots) : waves >= 13 && n >= 208 && (n <= 256 || full);
+            if (several) return c == 0 ? n >= 448 : n >= 512 && waves != 5 && waves != 6;
+            return c == 0 ? n >= 176 && (n <= 256 || 4 * n >= 3 * slots) : waves >= 13 && n >= 208 && (n <= 256 || full);
         }
-        static constexpr int64_t least[3][2][3] = {{{96, 112, 144}, {112, 144, 176}},   // two pairs: no field, field
-                                                   {{96, 192, 192}, {256, 384, 384}},   // a pair, several per CU
-                                                   {{96, 144, 144}, {176, 208, 208}}};  // a pair, one per CU
+        static constexpr int64_t least[3][2][3] = {{{112, 112, 144}, {144, 144, 176}},   // two pairs: no field, field
+                                                   {{160, 192, 192}, {448, 384, 384}},   // a pair, several per CU
+                                                   {{112, 144, 144}, {208, 208, 208}}};  // a pair, one per CU
         if (n < least[groups == 2 ? 0 : several ? 1 : 2][g.field ? 1 : 0][c]) return false;
         if (groups == 2 || several || n <= 256) return true;
         return c == 0 && !g.field ? true : c == 0 || !g.field ? 4 * n >= 3 * slots : full;
