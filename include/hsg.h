@@ -329,8 +329,8 @@ hsg_status hsg_get_tuning(const hsg_lattice *h, int32_t *variant, int32_t *slots
  * 256 (row bands with two halo rows; one of the four tallest); z_slabs = 1, 2,
  * 4 or 8 slabs of at least 8 planes that a single-pass launch splits the
  * z-march into. tile_y = z_slabs = 0 restores the default (the tallest band, or
- * two rows for L >= 128 from 23 million sites on; slabs until a launch has
- * about 4096 work-groups). Fused pairs and two-pair
+ * two rows for L >= 128 from 23 million sites on with float couplings; slabs until
+ * a launch has about 4096 work-groups). Fused pairs and two-pair
  * launches always march whole planes in one slab. HSG_E_INVALID for a bad
  * handle, group or shape; HSG_E_UNSUPPORTED for a group with L % 4 != 0. */
 hsg_status hsg_set_geometry(hsg_lattice *h, int32_t group, int32_t tile_y, int32_t z_slabs);

@@ -162,16 +162,19 @@ std::vector<std::pair<int, int>> geometry_candidates(const Group &g)
 }
 
 // Default z-march geometry for lattice size L: the whole plane where it fits,
-// otherwise the tallest row band, but bands of two rows for many sites of L >= 128,
-// where a work-group then takes several replicas, whose couplings and field it reads
-// once; single half-sweeps split z into slabs until the launch has about 4096
-// work-groups, keeping slabs >= 16 planes. Tallest bands against two rows, us per sweep
-// of 1 heat-bath and 4 over-relaxation pairs: L = 128 32 replicas f32 with a field
+// otherwise the tallest row band, but bands of two rows for many sites of L >= 128 with
+// float couplings, where a work-group then takes several replicas, whose couplings and
+// field it reads once; single half-sweeps split z into slabs until the launch has about
+// 4096 work-groups, keeping slabs >= 16 planes. Tallest bands against two rows, us per
+// sweep of 1 heat-bath and 4 over-relaxation pairs: L = 128 32 replicas f32 with a field
 // 3702 : 2715 (3606 before spins stood by pairs), f16 2075 : 1615 (2026), quantised
 // angles 1832 : 1449; L = 144 8 (23.9 M sites) f32 1123 : 1096, f16 788 : 660, quantised
 // angles 741 : 681; L = 256 8 f32 with a field 7244 : 5631 (6709). Below the line either
 // may win: L = 132 8 (18.4 M) f32 831 : 887, L = 144 4 525 : 593, L = 192 3 1013 : 1056,
-// L = 128 8 771 : 561.
+// L = 128 8 771 : 561. Sign bits are a 24th of those bytes, and the halo rows of flat
+// bands cost more than sharing them gives: L = 128 32 f32 2407 : 2501, quantised angles
+// 1287 : 1345, L = 144 8 654 : 740, L = 192 16 2489 : 2735 (with a field f32 L = 128
+// 2698 : 2587, quantised angles L = 192 2899 : 3107).
 void stream_geometry(Group &g)
 {
     g.stream_ok = (g.L % 4) == 0;
@@ -181,7 +184,7 @@ void stream_geometry(Group &g)
         g.stream_ok = false;
         return;
     }
-    const bool flat = g.L >= 128 && g.n_rep * g.N >= 23000000;
+    const bool flat = g.L >= 128 && g.ckind == 0 && g.n_rep * g.N >= 23000000;
     const int ty = flat ? cands.back().first : cands.front().first;
     const int rb = hsg::kBlock / ((g.L / 4) * ty);
     const int64_t base = (g.n_rep + rb - 1) / rb * (g.L / ty);

@@ -131,3 +131,11 @@ def test_flat_bands_bit_identical(hsg, L, D, T, storage, field):
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
     assert torch.allclose(a[3], b[3], rtol=1e-10, atol=1e-9)
     assert torch.allclose(a[3], E, rtol=1e-10, atol=1e-9)
+
+
+# sign-bit couplings are too few bytes to be worth the halo rows of flat bands
+@pytest.mark.parametrize("L,rows", [(128, 8), (144, 6)])
+def test_sign_bits_keep_tall_bands(hsg, L, rows):
+    lat = hsg.Lattice([_group(L, 1, 1, 12, None, "bimodal")], storage="qangle")
+    assert lat.get_geometry(0)[0] == rows
+    lat.close()
