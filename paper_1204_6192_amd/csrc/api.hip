@@ -626,6 +626,34 @@ hsg_status run_half_sweep(hsg_lattice *h, int kind, int parity, int rep, bool en
     return run_groups(h, kind, parity, rep, energy, 0, [](const Group &) { return true; }, s);
 }
 
+// use_plane from L = 36 on (L % 4 == 0) with couplings of one sign bit: single passes then
+// read a quarter of the couplings' bytes less per pair, while the walk's chain of steps
+// stays, so that its rounds have to be fuller. In us per pair, this walk against single
+// passes, 36 to 64 in steps of 4, 160 to 1024 replicas: f32 L = 36 192 67 : 58, 256
+// 69 : 70, with a field 320 98 : 88, 384 98 : 123, L = 48 192 179 : 140, 512 420 : 445;
+// bf16 L = 44 320 102 : 88, 384 103 : 119, L = 36 448 76 : 94, 640 122 : 115, 768
+// 125 : 127, 1024 248 : 226, L = 48 384 180 : 149, 1024 492 : 460, L = 52 192 100 : 94, 224 103 : 131, L = 64
+// 192 200 : 184, 224 205 : 232; quantised angles L = 40 256 78 : 83, 320 108 : 99, 384
+// 108 : 116, L = 48 256 108 : 112, 1024 505 : 414, L = 64 384 398 : 363, 448 413 : 412. The
+// heat bath f32 L = 44 256 198 : 146, 512 277 : 303, 640 425 : 383, 1024 552 : 589; bf16
+// L = 60 512 679 : 644.
+bool plane_of_signs(int c, int kind, bool field, int waves, int64_t n)
+{
+    const int64_t slots = 256 * ((n + 255) / 256), slots2 = 512 * ((n + 511) / 512);
+    const bool several = waves <= 8, full = 20 * n >= 19 * slots;
+    if (kind != 1) return c == 0 && !field && waves != 6 && (several ? 20 * n >= 19 * slots2 : waves >= 13 && full);
+    if (field && c != 0) return false;
+    if (several) {
+        if (c == 0) return n >= (!field ? 224 : waves == 6 ? 352 : 288);
+        if (waves == 6) return n > 384 && (n <= 512 || (n > 640 && n <= 768));
+        return n >= 384 || (c == 2 && n >= 224 && n <= 256);
+    }
+    if (c == 0) return field && waves == 9 ? full : 4 * n >= 3 * slots;
+    if (waves == 9) return c == 2 && n <= 256 && full;
+    if (c == 2) return waves < 13 ? full : 5 * n >= 4 * slots;
+    return waves >= 13 && waves <= 15 ? 4 * n >= 3 * slots : 8 * n >= 7 * slots;
+}
+
 // One pair (groups = 1) or two over-relaxation pairs (groups = 2) in one walk of
 // whole planes (launch_plane_march), where a plane's site pairs fit the work-group
 // (1024 and 256 threads) and the staged planes its LDS, and where that is the faster
@@ -682,6 +710,7 @@ bool use_plane(const hsg_lattice *h, const Group &g, int kind, int groups, bool 
         if (groups == 2) return c == 1 || !g.field || g.L >= 28 || energy || n <= 768;
         return !g.field && (kind == 0 || c != 0 || n <= 512);
     }
+    if (g.ckind == 1) return plane_of_signs(c, kind, g.field, waves, n);
     if (kind == 1) {
         if (g.field && c != 0) return false;
         if (several) return n >= (g.field ? 224 : 160);

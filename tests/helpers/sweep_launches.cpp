@@ -6,6 +6,7 @@
 //
 // Reads one case per line from standard input,
 //   storage n_hb n_or variant batch overlap sweeps  n_groups  (L samples copies rungs field)...
+// (field: 1 with a field, + 2 with couplings of one sign bit)
 // and prints "ok" or what is wrong for each; overlap = 2: and the halves have to be in effect.
 #include <hip/hip_runtime.h>
 #define __align__(n) __attribute__((aligned(n)))
@@ -199,8 +200,8 @@ hipError_t launch_tile_visit(const TileArgs &, int, bool, bool, bool, unsigned, 
 }
 hipError_t launch_invert_maps(const int32_t *, int32_t *, int64_t, int32_t, hipStream_t) { return hipErrorUnknown; }
 hipError_t launch_unpack_spins(const PackArgs &, int, hipStream_t) { return hipErrorUnknown; }
-hipError_t launch_check_pm1(const float *, int64_t, int32_t *, hipStream_t) { return hipErrorUnknown; }
-hipError_t launch_pack_jbits(const float *, uint8_t *, int64_t, int32_t, hipStream_t) { return hipErrorUnknown; }
+hipError_t launch_check_pm1(const float *, int64_t, int32_t *, hipStream_t) { return hipSuccess; }
+hipError_t launch_pack_jbits(const float *, uint8_t *, int64_t, int32_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_pack_field(const PackArgs &, hipStream_t) { return hipSuccess; }
 hipError_t launch_pack_spins(const PackArgs &, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_pack_couplings(const PackArgs &, hipStream_t) { return hipSuccess; }
@@ -280,6 +281,8 @@ std::string run(std::istringstream &in)
     for (auto &g : gd) {
         g = hsg_group_desc{};
         in >> g.L >> g.n_samples >> g.n_copies >> g.n_temps >> g.has_field;
+        g.coupling_kind = g.has_field >> 1;
+        g.has_field &= 1;
         g.temps = temps.data();
         g.sample_uid_base = uid;
         uid += (uint32_t)g.n_samples;

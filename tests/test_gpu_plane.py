@@ -139,3 +139,17 @@ def test_sign_bits_keep_tall_bands(hsg, L, rows):
     lat = hsg.Lattice([_group(L, 1, 1, 12, None, "bimodal")], storage="qangle")
     assert lat.get_geometry(0)[0] == rows
     lat.close()
+
+
+# both sides of the walk's lines with sign bits (the walk: the second of each pair)
+@pytest.mark.parametrize("L,n,storage,field", [(36, 384, "f16", None), (36, 385, "f16", None), (40, 257, "qangle", None),
+                                               (40, 256, "qangle", None), (44, 287, "f32", ("gaussian", 0.2)),
+                                               (44, 288, "f32", ("gaussian", 0.2)), (52, 223, "bf16", None),
+                                               (52, 224, "bf16", None)])
+def test_sign_bits_bit_identical(hsg, L, n, storage, field):
+    g = _group(L, n, 1, 1, field, "bimodal")
+    a, E = _run(hsg, [g], 0, storage, 1, 1, 0)
+    b, _ = _run(hsg, [g], 1, storage, 1, 1, 0)
+    assert torch.equal(a[0], b[0])
+    assert torch.allclose(a[3], b[3], rtol=1e-10, atol=1e-9)
+    assert torch.allclose(a[3], E, rtol=1e-10, atol=1e-9)

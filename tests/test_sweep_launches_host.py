@@ -79,3 +79,17 @@ def test_halves_in_effect(check):
                       [(16, 2, 2), (20, 3, 30), (128, 2, 1)]):
             cases.append((storage, n_hb, n_or, variant, -1, 2, [(L, D, 1, T, 0) for L, D, T in sizes]))
     assert check(cases) == []
+
+
+@pytest.mark.parametrize("storage", [F32, F16, QANGLE])
+def test_sign_bits(check, storage):
+    """Couplings of one sign bit draw the walk's lines elsewhere: replica counts on both
+    sides of them, whole, in batches and as halves."""
+    cases = []
+    for L, n, field, (n_hb, n_or), batch in itertools.product(
+            (36, 40, 48, 52, 56, 64), (190, 200, 224, 256, 260, 350, 352, 384, 400, 512, 640), (2, 3), MIXES, (-1, 64, 200)):
+        if batch < n:
+            cases.append((storage, n_hb, n_or, 0, batch, 0, [(L, n, 1, 1, field)]))
+        if batch < 0:
+            cases.append((storage, n_hb, n_or, 0, -1, 1, [(L, 4, 1, n // 4, field)]))
+    assert check(cases) == []
