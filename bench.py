@@ -520,7 +520,7 @@ def main():
     elif args.autotune <= 0 and args.config == "uneven":
         lat.set_overlap(1)
     variant, slots, two_streams = lat.get_tuning()
-    log(f"launch choice: kernel variant {variant} (0 = automatic, the two-pair z-march), slots per item "
+    log(f"launch choice: kernel variant {variant} (0 = automatic), slots per item "
         f"{slots}, two streams {two_streams}")
     torch.cuda.synchronize()
 

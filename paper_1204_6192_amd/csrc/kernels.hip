@@ -1104,7 +1104,9 @@ __global__ __launch_bounds__(128) void k_kmodes_finish(KmodeArgs a)
 // float64 rounding. A work-group's sums go to the partial of its band. (Unlike
 // the copy-pair and energy marches these take no z-slabs: their per-work-group
 // start, the phase tables and the reduction of 63 or 21 sums, cost more than
-// the extra work-groups gain, 593 against 631 us on the large workload.)
+// the extra work-groups gain, 593 against 631 us on the large workload, whose sixteen
+// bands fill the card without. Few items of one band each leave CUs idle: 128 of L = 32
+// take 43 us, the chiral march 56.)
 template <int STORE>
 __global__ __launch_bounds__(kBlock) void k_qk_stream(KmodeArgs a)
 {
@@ -1609,13 +1611,14 @@ __global__ __launch_bounds__(256) void k_pair_overlaps_finish(PairOvArgs a)
 
 // The copy-pair sums as a z-march where kmode_rows(L) > 0: one work-group per
 // (sample, rung, band of kmode_rows(L) rows, z-slab of L / march_slabs(L, D T)
-// planes) and copy pair (grid column y),
+// planes) and copy pair (grid column y; so with O copies a copy is read O - 1 times:
+// 16 samples of 8 rungs of L = 32 with four copies, 201 MB, fetch 604 MB in 90 us),
 // the thread of row y and quarter q holding the sites x = 4q .. 4q + 3 of
 // plane z as z advances, the next plane's loads issued a step ahead. Per step
 // the thread forms the local overlaps s(a) . s(b) of its four sites in float64
 // and adds them with weights 1, cos kx and sin kx, the first also with cos kz
 // and sin kz; the k_y terms are cos ky and sin ky times the unweighted sum at
-// the end (x and y stay fixed per thread). Every spin is read once. The sums
+// the end (x and y stay fixed per thread). The sums
 // run in another order than k_pair_overlaps', so the two agree to float64
 // rounding. A work-group's sums go to the partial of its band and slab.
 template <int STORE>

@@ -18,8 +18,9 @@
 // same bits.
 //
 // Single passes are bound by HBM with float32 spins (a pass of 96 replicas of L = 64
-// with a field, 472 MB, in 113 us: 4.2 TB/s) and by VALU with quantised angles (issued
-// in every cycle) and in the heat bath. So the index arithmetic of a step is kept
+// with a field, 472 MB, in 113 us: 4.2 TB/s) and by VALU with quantised angles (131
+// instructions per over-relaxation update at 3.5e13 lanes/s, what fused multiply-adds
+// reach) and in the heat bath (275 at 4.1e13). So the index arithmetic of a step is kept
 // small: planes as uniform offsets, LDS sites as three consecutive floats (one address
 // per pair) and rolling offsets instead of selects, which took an over-relaxation pair
 // of 32 replicas of L = 128 with quantised angles from 243 to 229 us, of 96 replicas of
