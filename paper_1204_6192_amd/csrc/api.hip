@@ -676,13 +676,14 @@ bool plane_of_signs(int c, int kind, bool field, int waves, int64_t n)
 //     field a pair and the heat bath are the march's (f32 2048 550 : 528).
 //   L = 36 to 64, L % 4 == 0, against single passes: a pair f32 L = 44 160 replicas
 //     114 : 127, with a field L = 36 224 107 : 105, 256 and more 0.8 to 0.95, L = 64 256
-//     without 486 : 673; bf16 L = 40 192
-//     49 : 61; compressed with a field 0.8 to 1.3 of their time, not by any simple line;
-//     quantised angles L = 48 (9 waves) 384 185 : 149, 512 259 : 304.
+//     without 486 : 673; bf16 L = 40 192 49 : 61; compressed with a field 0.8 to 1.3 of
+//     their time, not by any simple line; quantised angles L = 48 (9 waves) 384 185 : 149,
+//     512 259 : 304, L = 52 320 271 : 257, 384 272 : 290.
 //     The heat bath f32 L = 40 768 350 : 424, L = 36 (6 waves) 384 179 : 160, 512
 //     187 : 232, 768 289 : 321, 1024 446 : 426; bf16 L = 40 384 199 : 171, 512 211 : 236,
-//     768 314 : 343, 1024 427 : 441, L = 36 768 1.03 to 1.10 of the passes; L = 64 256 362 : 389, L = 48 (9 waves, so 9 of a CU's 16) 592 : 528; quantised angles
-//     L = 36 384 199 : 152, L = 64 256 404 : 390.
+//     1024 427 : 441, L = 36 768 1.03 to 1.1 of their time, L = 64 256 362 : 389, L = 48 (9
+//     waves, so 9 of a CU's 16) 592 : 528; quantised angles L = 36 384 199 : 152, L = 64 256
+//     404 : 390.
 bool use_plane(const hsg_lattice *h, const Group &g, int kind, int groups, bool energy, int64_t n)
 {
     if ((h->kernel_variant != 0 && h->kernel_variant < 4) || g.L < 24) return false;
@@ -715,7 +716,7 @@ bool use_plane(const hsg_lattice *h, const Group &g, int kind, int groups, bool 
     if (kind == 1) {
         if (g.field && c != 0) return false;
         if (several) return n >= (g.field ? 224 : 160);
-        return c == 2 && waves < 13 ? full : 4 * n >= 3 * slots;
+        return c == 2 && waves == 9 ? full : 4 * n >= 3 * slots;
     }
     if (g.field || c == 2) return false;
     if (several && waves == 6) return c == 0 && full && n >= 512 && n <= 768;
